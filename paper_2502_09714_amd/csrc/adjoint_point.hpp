@@ -142,6 +142,51 @@ __device__ inline void normal_flux_vjp(const T* u, const T n[3], const MatP<T>& 
   stress_vjp(u, m, law, ls, gu, gmu);
 }
 
+// largest eigenvalue of a symmetric 3x3 matrix (trigonometric closed form)
+template <class T>
+__device__ inline T sym3_lmax(T a00, T a11, T a22, T a01, T a02, T a12) {
+  const T q = (a00 + a11 + a22) / T(3);
+  const T p1 = a01 * a01 + a02 * a02 + a12 * a12;
+  const T b00 = a00 - q, b11 = a11 - q, b22 = a22 - q;
+  const T p2 = b00 * b00 + b11 * b11 + b22 * b22 + T(2) * p1;
+  if (!(p2 > T(0))) return q;
+  const T p = sqrt(p2 / T(6));
+  const T ip = T(1) / p;
+  const T c00 = b00 * ip, c11 = b11 * ip, c22 = b22 * ip, c01 = a01 * ip, c02 = a02 * ip,
+          c12 = a12 * ip;
+  T r = T(0.5) * (c00 * (c11 * c22 - c12 * c12) - c01 * (c01 * c22 - c12 * c02) +
+                  c02 * (c01 * c12 - c11 * c02));
+  r = r < T(-1) ? T(-1) : (r > T(1) ? T(1) : r);
+  const T phi = acos(r) / T(3);
+  return q + T(2) * p * cos(phi);
+}
+
+// (The adjoint keeps the 3 x 3 form: which side's speed is the larger one at a
+// face point decides where the derivative goes, and near a tie that choice
+// follows the last bits of both speeds.)
+// rho * acoustic tensor n . (d sigma / d eps) . n of the CDM law (symmetric)
+template <class T>
+__device__ inline void acoustic_rhoQ(const T* u, const T n[3], const MatP<T>& m, const Law<T>& law,
+                                     T Q[3][3]) {
+  Parts<T> p = cdm_parts(u, law);
+  const T agr = p.ac * m.gr;
+  const T h = (m.mu + p.ac * m.xi0 * m.gr) - T(0.5) * agr * p.xi;
+  // (eps n) of the scaled strain; the eps/sqrt(I2) terms are scale free
+  const T im = p.im;
+  const T en[3] = {(u[0] * n[0] + u[3] * n[1] + u[5] * n[2]) * im,
+                   (u[3] * n[0] + u[1] * n[1] + u[4] * n[2]) * im,
+                   (u[5] * n[0] + u[4] * n[1] + u[2] * n[2]) * im};
+  const T is = p.guard ? T(0) : T(1) / p.sp;
+  const T c1 = agr * is;                       // coefficient of n (eps n) + (eps n) n
+  const T c2 = agr * p.I1p * is * is * is;     // coefficient of (eps n)(eps n)
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+      Q[i][k] = m.lam * n[i] * n[k] + h * ((i == k ? T(1) : T(0)) + n[i] * n[k]) -
+                c1 * (n[i] * en[k] + en[i] * n[k]) + c2 * en[i] * en[k];
+}
+
 // c = sqrt(lambda_max(rho Q)/rho) and its derivatives with respect to the
 // state (10) and mu0.  With v the unit eigenvector of lambda_max, d lambda =
 // v^T d(rho Q) v, and
