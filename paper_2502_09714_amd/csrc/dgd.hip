@@ -14,6 +14,7 @@
 #include "adjoint_kernels.hpp"
 #include "kernels.hpp"
 #include "refgen.hpp"
+#include "step_kernels.hpp"
 
 using namespace dgd;
 
@@ -73,7 +74,10 @@ struct dgd_handle {
   size_t tsize = 8;  // bytes of the working type
   // reference data on the device
   DevBuf Vpk, Kpk, Spk, Fpk, Lpk, Ppk, Vd, wqd, Pwd, betad, KPpk;
-  bool vol3 = false;      // volume terms three elements per wavefront
+  DevBuf Kck, Ktl, PXpk, Psrc, mixP, mixV;   // Cauchy-Kovalevskaya step (step_kernels.hpp)
+  size_t dz_elem = 0;     // bytes of one element's time derivatives
+  double points_dt = 0.0;      // step of the last step's derivatives
+  bool points_in_uz = false;   // the last step left time-point states in Uz, not derivatives in Dz
   int predictor = 0;      // 0: linearised Cauchy-Kovalevskaya, 1: Picard iteration
   int picard_iters = 0;
   // host copies of the connectivity (neighbour of every element face, face list)
@@ -83,9 +87,9 @@ struct dgd_handle {
   int nclusters = 0;
   double lts_dt0 = 0.0;
   std::vector<signed char> cl_h;
-  DevBuf ecl, Dall, facc;
-  std::vector<DevBuf> lts_el, lts_tay, lts_fl, lts_acc;
-  std::vector<long long> n_el, n_tay, n_fl, n_acc;
+  DevBuf ecl, facc;
+  std::vector<DevBuf> lts_el, lts_fl, lts_acc;
+  std::vector<long long> n_el, n_fl, n_acc;
   double lts_tp[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   int kpl = 0;  // padded mode count of the time-point state layout
   double inv_wsum = 6.0, phi0_mean = 0.0;
@@ -99,7 +103,7 @@ struct dgd_handle {
   std::vector<double> rho_h;
   int law = 0;   // 0: continuum damage (Eq. cdb-model), 1: internal variable (Eq. ivm-model)
   // state
-  DevBuf U9[2], Ua[2], Uz, flag, tmp;   // tmp: per-call host transfers
+  DevBuf U9[2], Ua[2], Dz, Uz, flag, tmp;   // tmp: per-call host transfers
   int cur = 0;
   double dt = 0.0, amax = 0.5, t = 0.0;
   long long steps_since_check = 0, check_every = 64;
@@ -135,12 +139,12 @@ struct dgd_handle {
                      &s_elem, &s_M6, &s_dphi, &s_onset, &s_param, &s_rhoJ, &r_elem, &r_phi, &seis,
                      &VTpk, &STpk, &PTpk, &KTpk, &lam[0], &lam[1], &gtr, &gmuf, &lzf, &gmu, &gcd, &adjW9,
                      &adjWa, &dlds, &seg9, &sega, &seguz, &segd, &segacc, &save9, &savea, &st9, &sta,
-                     &KPpk, &ecl, &Dall, &facc, &Vpk32, &Kpk32, &Spk32, &Fpk32, &Lpk32, &Ppk32,
+                     &KPpk, &ecl, &facc, &Kck, &Ktl, &PXpk, &Psrc, &mixP, &mixV, &Dz, &Vpk32, &Kpk32, &Spk32, &Fpk32, &Lpk32, &Ppk32,
                      &KPpk32};
     for (DevBuf* b : all) b->release();
     for (DevBuf& b : ck9) b.release();
     for (DevBuf& b : cka) b.release();
-    for (auto* v : {&lts_el, &lts_tay, &lts_fl, &lts_acc})
+    for (auto* v : {&lts_el, &lts_fl, &lts_acc})
       for (DevBuf& b : *v) b.release();
     for (auto& u : ev_used) {
       (void)hipEventDestroy(u.second.first);
@@ -334,6 +338,76 @@ dgd_status build_packed(dgd_handle* h) {
   return DGD_OK;
 }
 
+// operators of the Cauchy-Kovalevskaya step's kernels (step_kernels.hpp)
+template <int N, int P>
+dgd_status build_step_packs(dgd_handle* h) {
+  using DM = Dims<N>;
+  using AF = typename HostAF<P>::type;
+  using T = typename Prec<P>::T;
+  constexpr int PA = Accurate<P>::value;
+  constexpr int KS = Prec<P>::KS, L = DM::L, Q = DM::Q, MT = DM::MT;
+  constexpr int KSL = round_up(L, KS) / KS, Q4 = (Q + 3) / 4;
+  const RefData& r = h->ref;
+  // row 16 t + m of a pack whose product's rows become the next k order
+  auto row = [](int m) { return (m & ~15) + mperm<P>(m & 15); };
+  constexpr int KSA = round_up(L, Prec<PA>::KS) / Prec<PA>::KS;
+  std::vector<AF> kc;
+  std::vector<typename HostAF<PA>::type> kt;
+  for (int e = 0; e < 3; ++e) {
+    append(kc, pack_A<P>(
+                   [&](int m, int kk) {
+                     const int k = row(m);
+                     return (k < L && kk < L && r.deg[k] < r.deg[kk]) ? r.K[((size_t)e * L + k) * L + kk]
+                                                                     : 0.0;
+                   },
+                   MT, KSL));
+    append(kt, pack_A<PA>(
+                   [&](int m, int kk) {
+                     return (m < L && kk < L && r.deg[kk] < r.deg[m]) ? r.K[((size_t)e * L + kk) * L + m]
+                                                                     : 0.0;
+                   },
+                   MT, KSA));
+  }
+  std::vector<typename HostAF<PA>::type> px;
+  for (int c = 0; c < DM::NCH; ++c)
+    for (int t = 0; t < MT; ++t)
+      for (int s = 0; s < 16; ++s)
+        for (int lane = 0; lane < 64; ++lane) {
+          const int l = 16 * t + mperm<PA>(lane & 15);
+          const int q = 64 * c + 16 * (s / 4) + 4 * (lane >> 4) + s % 4;
+          px.push_back((typename HostAF<PA>::type)((l < L && q < Q) ? r.Pw[(size_t)l * Q + q] : 0.0));
+        }
+  std::vector<T> ps((size_t)Q4 * L * 4, T(0));
+  for (int q = 0; q < Q; ++q)
+    for (int l = 0; l < L; ++l) ps[((size_t)(q / 4) * L + l) * 4 + q % 4] = (T)r.Pw[(size_t)l * Q + q];
+  // quantity mixing: lane (g, n) holds row p = qperm(n), column j = 4 i + g of
+  // sum_d Theta^-1_ed W_d.  Strain rows: -1/2 on the velocities; velocity rows:
+  // -1/rho times the averaged tangent (prediction, columns strain and damage)
+  // or the stress itself (volume: columns 3..8 of (v, sigma, rate)).
+  const int vi[6] = {0, 1, 2, 0, 1, 2}, vj[6] = {0, 1, 2, 1, 2, 0};
+  std::vector<int> mp(9 * 64, 42);       // 42: zero, 43: 1/2, 44: 1 (of minus the matrix)
+  std::vector<T> mv(9 * 64, T(0));
+  for (int i = 0; i < 3; ++i)
+    for (int d = 0; d < 3; ++d)
+      for (int lane = 0; lane < 64; ++lane) {
+        const int p = qperm<T>(lane & 15), j = 4 * i + (lane >> 4), at = (i * 3 + d) * 64 + lane;
+        if (p < 6) {
+          auto half = [&](int v) { return (vi[p] == v && vj[p] == d) + (vj[p] == v && vi[p] == d); };
+          if (j >= 6 && j < 9) mp[at] = 42 + half(j - 6);
+          if (j < 3) mv[at] = T(-0.5) * half(j);
+        } else if (p < 9) {
+          if (j < 6 || j == 9) mp[at] = sym_idx(p - 6, d) * 7 + (j < 6 ? j : 6);
+          if (j >= 3 && j < 9 && j - 3 == sym_idx(p - 6, d)) mv[at] = T(-1);
+        }
+      }
+  dgd_status st;
+  if ((st = upload(h, h->Kck, kc)) || (st = upload(h, h->Ktl, kt)) || (st = upload(h, h->PXpk, px)) ||
+      (st = upload(h, h->Psrc, ps)) || (st = upload(h, h->mixP, mp)) || (st = upload(h, h->mixV, mv)))
+    return st;
+  h->dz_elem = (size_t)Deriv<N, P>::NF * 64 * sizeof(AF);
+  return DGD_OK;
+}
+
 hipEvent_t take_event(dgd_handle* h) {
   if (!h->ev_pool.empty()) {
     hipEvent_t e = h->ev_pool.back();
@@ -361,6 +435,19 @@ void timed(dgd_handle* h, int k, F launch) {
   launch();
   (void)hipEventRecord(b, h->stream);
   h->ev_used.push_back({k, {a, b}});
+}
+
+// the step and the times of its time points
+template <int P> void set_dt(StepArgs<P>& a, double dt) {
+  using T = typename Prec<P>::T;
+  a.dt = dt;
+  for (int z = 0; z < 8; ++z) a.hz[z] = a.tau[z] * (T)dt;
+  // (the rule's weights sum to 1 and it integrates the powers up to N exactly)
+  double f = 1.0;
+  for (int i = 0; i < 8; ++i) {
+    a.wint[i] = (T)f;
+    f *= dt / (i + 2);
+  }
 }
 
 template <int N, int P>
@@ -402,74 +489,97 @@ StepArgs<P> make_args(dgd_handle* h) {
   a.ecl = nullptr;
   a.lts_c = -1;
   a.facc = nullptr;
-  a.O9 = nullptr;
-  a.Oa = nullptr;
+  a.Dz = (AF*)h->Dz.p;
+  a.Kck = (const AF*)h->Kck.p;
+  a.Ktl = (const typename Prec<Accurate<P>::value>::AF*)h->Ktl.p;
+  a.PXpk = (const typename Prec<Accurate<P>::value>::AF*)h->PXpk.p;
+  a.Psrc = (const T*)h->Psrc.p;
+  a.mixP = (const int*)h->mixP.p;
+  a.mixV = (const T*)h->mixV.p;
+  set_dt<P>(a, h->dt);
   return a;
 }
 
-// volume and source terms of the listed elements (all without a list): three
-// elements per wavefront where that layout is used, else one
-template <int N, int P>
-void launch_volume(dgd_handle* h, const StepArgs<P>& a, bool ivm) {
+template <int N, int P, class LW>
+void launch_ck(dgd_handle* h, const StepArgs<P>& a) {
   const long long n = a.elist ? a.nlist : a.E;
-  if (h->vol3) {
-    const long long ng = (n + 2) / 3;
-    const dim3 grid((unsigned)(8 * ((ng + 7) / 8)));
-    if (ivm)
-      hipLaunchKernelGGL((k_volume3<N, P, IvmLaw>), grid, dim3(64), 0, h->stream, a);
-    else
-      hipLaunchKernelGGL((k_volume3<N, P, CdmLaw>), grid, dim3(64), 0, h->stream, a);
-  } else {
-    const dim3 grid((unsigned)(8 * ((n + 7) / 8)));
-    if (ivm)
-      hipLaunchKernelGGL((k_volume<N, P, IvmLaw>), grid, dim3(64), 0, h->stream, a);
-    else
-      hipLaunchKernelGGL((k_volume<N, P, CdmLaw>), grid, dim3(64), 0, h->stream, a);
-  }
+  timed(h, 0, [&] {
+    hipLaunchKernelGGL((k_ck<N, P, LW>), dim3((unsigned)(8 * ((n + 7) / 8))), dim3(64), 0,
+                       h->stream, a);
+  });
+}
+
+template <int N, int P, class LW>
+void launch_face(dgd_handle* h, const StepArgs<P>& a, long long n, const int* list,
+                 const ClusterOffsets& offs) {
+  timed(h, 1, [&] {
+    hipLaunchKernelGGL((k_face<N, P, LW>), dim3((unsigned)(8 * ((n + 7) / 8))), dim3(64), 0,
+                       h->stream, a, (const int*)h->faces.p, n,
+                       (typename Prec<P>::T*)h->fflux.p, list, offs);
+  });
+}
+
+template <int N, int P, class LW>
+void launch_update(dgd_handle* h, const StepArgs<P>& a) {
+  const long long n = a.elist ? a.nlist : a.E;
+  timed(h, 9, [&] {
+    hipLaunchKernelGGL((k_update<N, P, LW>), dim3((unsigned)(8 * ((n + 7) / 8))), dim3(64), 0,
+                       h->stream, a, (const int*)h->fmap.p, (const typename Prec<P>::T*)h->fflux.p);
+  });
+}
+
+// one step with the Picard predictor: time-point states through HBM
+template <int N, int P, class LW>
+void picard_step(dgd_handle* h, const StepArgs<P>& a) {
+  using T = typename Prec<P>::T;
+  const dim3 grid((unsigned)(8 * ((h->ne + 7) / 8))), block(64);
+  const dim3 fgrid((unsigned)(8 * ((h->nfaces + 7) / 8)));
+  PicardArgs<P> pa;
+  pa.KPpk = (const typename Prec<P>::AF*)h->KPpk.p;
+  pa.iters = h->picard_iters > 0 ? h->picard_iters : N + 1;
+  for (int z = 0; z < 8; ++z)
+    for (int j = 0; j < 8; ++j)
+      pa.om[z][j] = (z < h->ref.Nt && j < h->ref.Nt) ? (T)h->ref.Om[z * h->ref.Nt + j] : T(0);
+  timed(h, 0, [&] {
+    hipLaunchKernelGGL((k_predict_picard<N, P, LW>), grid, block, 0, h->stream, a, pa);
+  });
+  timed(h, 9, [&] { hipLaunchKernelGGL((k_volume<N, P, LW>), grid, block, 0, h->stream, a); });
+  timed(h, 1, [&] {
+    hipLaunchKernelGGL((k_face_flux<N, P, LW>), fgrid, block, 0, h->stream, a,
+                       (const int*)h->faces.p, h->nfaces, (T*)h->fflux.p);
+  });
+  timed(h, 8, [&] {
+    hipLaunchKernelGGL((k_lift_update<N, P>), grid, block, 0, h->stream, a, (const int*)h->fmap.p,
+                       (const T*)h->fflux.p);
+  });
+}
+
+template <int N, int P, class LW>
+void ck_step(dgd_handle* h, const StepArgs<P>& a) {
+  launch_ck<N, P, LW>(h, a);
+  launch_face<N, P, LW>(h, a, h->nfaces, nullptr, ClusterOffsets{});
+  launch_update<N, P, LW>(h, a);
 }
 
 template <int N, int P>
 dgd_status step_impl(dgd_handle* h, long long nsteps) {
   using T = typename Prec<P>::T;
-  const long long per = (h->ne + 7) / 8;
-  const dim3 grid((unsigned)(8 * per)), block(64);
   const bool ivm = h->law == 1;
   for (long long it = 0; it < nsteps; ++it) {
-    StepArgs<P> a = make_args<N, P>(h);
-    timed(h, 0, [&] {
-      if (h->predictor == 1) {
-        PicardArgs<P> pa;
-        pa.KPpk = (const typename Prec<P>::AF*)h->KPpk.p;
-        pa.iters = h->picard_iters > 0 ? h->picard_iters : N + 1;
-        for (int z = 0; z < 8; ++z)
-          for (int j = 0; j < 8; ++j)
-            pa.om[z][j] = (z < h->ref.Nt && j < h->ref.Nt) ? (T)h->ref.Om[z * h->ref.Nt + j] : T(0);
-        if (ivm)
-          hipLaunchKernelGGL((k_predict_picard<N, P, IvmLaw>), grid, block, 0, h->stream, a, pa);
-        else
-          hipLaunchKernelGGL((k_predict_picard<N, P, CdmLaw>), grid, block, 0, h->stream, a, pa);
-      } else if (ivm) {
-        hipLaunchKernelGGL((k_predict<N, P, IvmLaw>), grid, block, 0, h->stream, a);
-      } else {
-        hipLaunchKernelGGL((k_predict<N, P, CdmLaw>), grid, block, 0, h->stream, a);
-      }
-    });
-    timed(h, 9, [&] { launch_volume<N, P>(h, a, ivm); });
-    const long long fper = (h->nfaces + 7) / 8;
-    timed(h, 1, [&] {
+    const StepArgs<P> a = make_args<N, P>(h);
+    h->points_in_uz = h->predictor == 1;
+    h->points_dt = h->dt;
+    if (h->predictor == 1) {
       if (ivm)
-        hipLaunchKernelGGL((k_face_flux<N, P, IvmLaw>), dim3((unsigned)(8 * fper)), block, 0,
-                           h->stream, a, (const int*)h->faces.p, h->nfaces, (T*)h->fflux.p,
-                           (const int*)nullptr);
+        picard_step<N, P, IvmLaw>(h, a);
       else
-        hipLaunchKernelGGL((k_face_flux<N, P>), dim3((unsigned)(8 * fper)), block, 0,
-                           h->stream, a, (const int*)h->faces.p, h->nfaces, (T*)h->fflux.p,
-                           (const int*)nullptr);
-    });
-    timed(h, 8, [&] {
-      hipLaunchKernelGGL((k_lift_update<N, P>), grid, block, 0, h->stream, a,
-                         (const int*)h->fmap.p, (const T*)h->fflux.p);
-    });
+        picard_step<N, P, CdmLaw>(h, a);
+    } else {
+      if (ivm)
+        ck_step<N, P, IvmStep>(h, a);
+      else
+        ck_step<N, P, CdmStep>(h, a);
+    }
     if (h->nsrc > 0) {
       SrcArgs s;
       s.nsrc = h->nsrc;
@@ -510,75 +620,44 @@ dgd_status step_impl(dgd_handle* h, long long nsteps) {
 // ---------------------------------------------------------------- local time stepping
 // One step of cluster c over [t, t + dt0 2^c] (rate-2 clusters, the finer
 // cluster's two steps nested inside; see dgd_set_clusters).
-template <int N, int P>
+template <int N, int P, class LW>
 dgd_status lts_advance(dgd_handle* h, int c, double t) {
   using T = typename Prec<P>::T;
-  const dim3 block(64);
-  auto grid_of = [](long long n) { return dim3((unsigned)(8 * ((n + 7) / 8))); };
   const double dtc = h->lts_dt0 * (double)(1LL << c);
   StepArgs<P> a = make_args<N, P>(h);
   a.ecl = (const signed char*)h->ecl.p;
-  a.Dkeep = (T*)h->Dall.p;
-  a.Akeep = nullptr;
-  a.dt = dtc;
-  const bool ivm = h->law == 1;
+  set_dt<P>(a, dtc);
+  a.elist = (const int*)h->lts_el[c].p;
+  a.nlist = h->n_el[c];
   if (h->n_el[c] > 0) {
-    a.elist = (const int*)h->lts_el[c].p;
-    a.nlist = h->n_el[c];
-    timed(h, 0, [&] {
-      if (ivm)
-        hipLaunchKernelGGL((k_predict<N, P, IvmLaw>), grid_of(a.nlist), block, 0, h->stream, a);
-      else
-        hipLaunchKernelGGL((k_predict<N, P, CdmLaw>), grid_of(a.nlist), block, 0, h->stream, a);
-    });
+    launch_ck<N, P, LW>(h, a);
     HIPCHK(h, hipGetLastError());
   }
   h->lts_tp[c] = t;
   dgd_status s;
   if (c > 0) {
-    if ((s = lts_advance<N, P>(h, c - 1, t)) || (s = lts_advance<N, P>(h, c - 1, t + 0.5 * dtc)))
+    if ((s = lts_advance<N, P, LW>(h, c - 1, t)) ||
+        (s = lts_advance<N, P, LW>(h, c - 1, t + 0.5 * dtc)))
       return s;
   }
   if (h->n_el[c] == 0) return DGD_OK;
-  // states at this cluster's time points: its own and its coarser neighbours'
+  // fluxes of the faces this cluster computes, each side's derivatives taken
+  // from its own prediction; integrals kept for the coarser side
   ClusterOffsets offs;
   for (int k = 0; k < 8; ++k) offs.v[k] = k < h->nclusters ? t - h->lts_tp[k] : 0.0;
-  a.elist = (const int*)h->lts_tay[c].p;
-  a.nlist = h->n_tay[c];
-  timed(h, 0, [&] {
-    hipLaunchKernelGGL((k_taylor<N, P>), grid_of(a.nlist), block, 0, h->stream, a, offs);
-  });
-  // fluxes of the faces this cluster computes; integrals kept for the coarser side
-  if (h->n_fl[c] > 0) {
-    timed(h, 1, [&] {
-      if (ivm)
-        hipLaunchKernelGGL((k_face_flux<N, P, IvmLaw>), grid_of(h->n_fl[c]), block, 0, h->stream,
-                           a, (const int*)h->faces.p, h->n_fl[c], (T*)h->fflux.p,
-                           (const int*)h->lts_fl[c].p);
-      else
-        hipLaunchKernelGGL((k_face_flux<N, P, CdmLaw>), grid_of(h->n_fl[c]), block, 0, h->stream,
-                           a, (const int*)h->faces.p, h->n_fl[c], (T*)h->fflux.p,
-                           (const int*)h->lts_fl[c].p);
-    });
-  }
+  if (h->n_fl[c] > 0) launch_face<N, P, LW>(h, a, h->n_fl[c], (const int*)h->lts_fl[c].p, offs);
   if (h->n_acc[c] > 0) {
     const long long n = h->n_acc[c] * h->ref.Ns * 10;
     hipLaunchKernelGGL((k_face_accumulate<T>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0,
                        h->stream, h->n_acc[c], (const int*)h->lts_acc[c].p, h->ref.Ns, dtc,
                        (const T*)h->fflux.p, (T*)h->facc.p);
   }
-  // volume and source terms, then the faces and the update in place
-  a.elist = (const int*)h->lts_el[c].p;
-  a.nlist = h->n_el[c];
-  timed(h, 9, [&] { launch_volume<N, P>(h, a, ivm); });
+  // faces, volume and source terms and the update, in place
   a.lts_c = c;
   a.facc = (T*)h->facc.p;
-  a.O9 = (T*)h->U9[h->cur].p;
-  a.Oa = (double*)h->Ua[h->cur].p;
-  timed(h, 8, [&] {
-    hipLaunchKernelGGL((k_lift_update<N, P>), grid_of(a.nlist), block, 0, h->stream, a,
-                       (const int*)h->fmap.p, (const T*)h->fflux.p);
-  });
+  a.W9 = (T*)h->U9[h->cur].p;
+  a.Wa = (double*)h->Ua[h->cur].p;
+  launch_update<N, P, LW>(h, a);
   if (h->nsrc > 0) {
     // the point sources of this cluster's elements, over its step
     SrcArgs sa;
@@ -607,9 +686,11 @@ dgd_status lts_advance(dgd_handle* h, int c, double t) {
 template <int N, int P> struct LtsFn {
   static dgd_status run(dgd_handle* h, long long nmacro) {
     using T = typename Prec<P>::T;
+    h->points_in_uz = false;
     const double mdt = h->lts_dt0 * (double)(1LL << (h->nclusters - 1));
     for (long long k = 0; k < nmacro; ++k) {
-      dgd_status s = lts_advance<N, P>(h, h->nclusters - 1, h->t);
+      dgd_status s = h->law == 1 ? lts_advance<N, P, IvmStep>(h, h->nclusters - 1, h->t)
+                                 : lts_advance<N, P, CdmStep>(h, h->nclusters - 1, h->t);
       if (s) return s;
       h->t += mdt;
       if (h->nrec > 0) {
@@ -640,19 +721,32 @@ dgd_status dispatch(dgd_handle* h, Args... args) {
 }
 
 template <int N, int P> struct BuildFn {
-  static dgd_status run(dgd_handle* h) { return build_packed<N, P>(h); }
+  static dgd_status run(dgd_handle* h) {
+    const dgd_status s = build_packed<N, P>(h);
+    return s ? s : build_step_packs<N, P>(h);
+  }
 };
 template <int N, int P> struct StepFn {
   static dgd_status run(dgd_handle* h, long long n) { return step_impl<N, P>(h, n); }
 };
 
-// the predictor of the current state only (time-point states and, when the
-// handle asks for them, the kept derivatives); state and time unchanged
+// the adjoint's prediction of the current state (time-point states and, when
+// the handle asks for them, the kept derivatives); state and time unchanged
 template <int N, int P> struct PredictFn {
   static dgd_status run(dgd_handle* h) {
     const long long per = (h->ne + 7) / 8;
     StepArgs<P> a = make_args<N, P>(h);
     hipLaunchKernelGGL((k_predict<N, P>), dim3((unsigned)(8 * per)), dim3(64), 0, h->stream, a);
+    HIPCHK(h, hipGetLastError());
+    return DGD_OK;
+  }
+};
+
+template <int N, int P> struct TimePointsFn {
+  static dgd_status run(dgd_handle* h, double* out) {
+    StepArgs<P> a = make_args<N, P>(h);
+    set_dt<P>(a, h->points_dt);
+    hipLaunchKernelGGL((k_time_points<N, P>), dim3((unsigned)h->ne), dim3(64), 0, h->stream, a, out);
     HIPCHK(h, hipGetLastError());
     return DGD_OK;
   }
@@ -689,10 +783,27 @@ dgd_status ensure_adjoint_packs(dgd_handle* h) {
   return s;
 }
 
+// bytes of the time-point states of all elements, [E][Nt][L][10], and of the
+// zeroed tail after them that the matrix cores' in-place reads of the last
+// element's padding rows reach (KPL * 16 entries)
+size_t uz_bytes(const dgd_handle* h) {
+  return (size_t)h->ne * h->ref.Nt * h->ref.L * 10 * h->tsize;
+}
+size_t uz_tail(const dgd_handle* h) { return (size_t)h->kpl * 16 * h->tsize; }
+
+// a buffer of `slots` consecutive time-point-state arrays and the zeroed tail
+dgd_status alloc_uz(dgd_handle* h, DevBuf& b, size_t slots) {
+  dgd_status s = dalloc(h, b, slots * uz_bytes(h) + uz_tail(h));
+  if (s) return s;
+  HIPCHK(h, hipMemsetAsync(b.p, 0, b.n, h->stream));
+  return DGD_OK;
+}
+
 dgd_status alloc_adjoint(dgd_handle* h) {
   const size_t E = (size_t)h->ne, L = h->ref.L;
   dgd_status s;
   if ((s = ensure_adjoint_packs(h))) return s;
+  if (!h->Uz.p && (s = alloc_uz(h, h->Uz, 1))) return s;
   if ((s = dalloc(h, h->lam[0], lam_elems(h) * h->tsize)) ||
       (s = dalloc(h, h->lam[1], lam_elems(h) * h->tsize)) ||
       (s = dalloc(h, h->gtr, (size_t)h->nfaces * 2 * h->ref.Nt * h->ref.Ns * 10 * h->tsize)) ||
@@ -937,22 +1048,6 @@ dgd_status ensure_seis(dgd_handle* h, long long extra) {
   return DGD_OK;
 }
 
-// bytes of the time-point states of all elements, [E][Nt][L][10], and of the
-// zeroed tail after them that the matrix cores' in-place reads of the last
-// element's padding rows reach (KPL * 16 entries)
-size_t uz_bytes(const dgd_handle* h) {
-  return (size_t)h->ne * h->ref.Nt * h->ref.L * 10 * h->tsize;
-}
-size_t uz_tail(const dgd_handle* h) { return (size_t)h->kpl * 16 * h->tsize; }
-
-// a buffer of `slots` consecutive time-point-state arrays and the zeroed tail
-dgd_status alloc_uz(dgd_handle* h, DevBuf& b, size_t slots) {
-  dgd_status s = dalloc(h, b, slots * uz_bytes(h) + uz_tail(h));
-  if (s) return s;
-  HIPCHK(h, hipMemsetAsync(b.p, 0, b.n, h->stream));
-  return DGD_OK;
-}
-
 dgd_status alloc_state(dgd_handle* h) {
   const size_t L = h->ref.L, E = (size_t)h->ne;
   dgd_status s;
@@ -960,7 +1055,15 @@ dgd_status alloc_state(dgd_handle* h) {
     if ((s = dalloc(h, h->U9[i], E * 9 * L * h->tsize))) return s;
     if ((s = dalloc(h, h->Ua[i], E * L * sizeof(double)))) return s;
   }
-  if ((s = alloc_uz(h, h->Uz, 1))) return s;
+  if ((s = dalloc(h, h->Dz, E * h->dz_elem))) return s;
+  HIPCHK(h, hipMemsetAsync(h->Dz.p, 0, h->Dz.n, h->stream));
+  h->points_in_uz = false;
+  // time-point states: only the Picard predictor and the adjoint keep them
+  if (h->predictor == 1) {
+    if ((s = alloc_uz(h, h->Uz, 1))) return s;
+  } else {
+    h->Uz.release();
+  }
   if ((s = dalloc(h, h->fflux, (size_t)h->nfaces * h->ref.Ns * 10 * h->tsize))) return s;
   if ((s = dalloc(h, h->flag, sizeof(int)))) return s;
   HIPCHK(h, hipMemsetAsync(h->flag.p, 0, sizeof(int), h->stream));
@@ -997,10 +1100,6 @@ dgd_status dgd_create(int N, int precision, void* hip_stream, dgd_handle** out) 
   h->prec = precision;
   h->stream = (hipStream_t)hip_stream;
   h->tsize = precision == DGD_FP64 ? 8 : 4;
-  // volume terms three elements per wavefront where that measured faster
-  // (FP32 at degree 4: 118 against 133 ms per step on 5,308,416 tets; slower
-  // in FP64 and with the split BF16 operands)
-  h->vol3 = precision == DGD_FP32 && N == 4;
   if (hipGetDevice(&h->device) != hipSuccess ||
       scratch_address(h->device, &h->noalloc_part) != hipSuccess) {
     delete h;
@@ -1407,6 +1506,10 @@ dgd_status dgd_set_predictor(dgd_handle* h, int kind, int iterations) {
   if ((kind != DGD_PREDICT_CK && kind != DGD_PREDICT_PICARD) || iterations < 0)
     return fail(h, DGD_EINVAL, "predictor kind 0 or 1 and iterations >= 0 needed");
   invalidate_tape(h);
+  if (kind == DGD_PREDICT_PICARD && h->have_mesh && !h->Uz.p) {
+    const dgd_status s = alloc_uz(h, h->Uz, 1);
+    if (s) return s;
+  }
   h->predictor = kind;
   h->picard_iters = iterations;
   return DGD_OK;
@@ -1416,7 +1519,7 @@ dgd_status dgd_set_clusters(dgd_handle* h, const int32_t* cluster, double dt0) {
   if (!h) return DGD_EINVAL;
   if (!h->have_mesh) return fail(h, DGD_ESTATE, "set_mesh first");
   invalidate_tape(h);
-  for (auto* v : {&h->lts_el, &h->lts_tay, &h->lts_fl, &h->lts_acc})
+  for (auto* v : {&h->lts_el, &h->lts_fl, &h->lts_acc})
     for (DevBuf& b : *v) b.release();
   h->nclusters = 0;
   h->cl_h.clear();
@@ -1435,24 +1538,8 @@ dgd_status dgd_set_clusters(dgd_handle* h, const int32_t* cluster, double dt0) {
     if (nb >= 0 && std::abs((int)cl[ef / 4] - (int)cl[nb]) > 1)
       return fail(h, DGD_EINVAL, "face neighbours more than one cluster apart");
   }
-  std::vector<std::vector<int>> el(C), tay(C), fl(C), acc(C);
+  std::vector<std::vector<int>> el(C), fl(C), acc(C);
   for (long long e = 0; e < ne; ++e) el[cl[e]].push_back((int)e);
-  for (int c = 0; c < C; ++c) {
-    tay[c] = el[c];
-    if (c + 1 < C) {
-      std::vector<int> extra;
-      for (int e : el[c + 1])
-        for (int f = 0; f < 4; ++f) {
-          const int nb = h->nbr_h[(size_t)e * 4 + f];
-          if (nb >= 0 && cl[nb] == c) {
-            extra.push_back(e);
-            break;
-          }
-        }
-      tay[c].insert(tay[c].end(), extra.begin(), extra.end());
-      std::sort(tay[c].begin(), tay[c].end());
-    }
-  }
   for (long long fid = 0; fid < h->nfaces; ++fid) {
     const int ef = h->faces_h[fid * 2], of = h->faces_h[fid * 2 + 1];
     const int c1 = cl[ef >> 2];
@@ -1465,20 +1552,17 @@ dgd_status dgd_set_clusters(dgd_handle* h, const int32_t* cluster, double dt0) {
     if (c1 != c2) acc[cm].push_back((int)fid);
   }
   h->lts_el.resize(C);
-  h->lts_tay.resize(C);
   h->lts_fl.resize(C);
   h->lts_acc.resize(C);
   h->n_el.assign(C, 0);
-  h->n_tay.assign(C, 0);
   h->n_fl.assign(C, 0);
   h->n_acc.assign(C, 0);
   dgd_status s;
   for (int c = 0; c < C; ++c) {
-    if ((s = upload(h, h->lts_el[c], el[c])) || (s = upload(h, h->lts_tay[c], tay[c])) ||
-        (s = upload(h, h->lts_fl[c], fl[c])) || (s = upload(h, h->lts_acc[c], acc[c])))
+    if ((s = upload(h, h->lts_el[c], el[c])) || (s = upload(h, h->lts_fl[c], fl[c])) ||
+        (s = upload(h, h->lts_acc[c], acc[c])))
       return s;
     h->n_el[c] = (long long)el[c].size();
-    h->n_tay[c] = (long long)tay[c].size();
     h->n_fl[c] = (long long)fl[c].size();
     h->n_acc[c] = (long long)acc[c].size();
   }
@@ -1536,9 +1620,7 @@ dgd_status dgd_step_lts(dgd_handle* h, int64_t nmacro) {
     return fail(h, DGD_ESTATE, "mesh, material, params and state are needed before step");
   if (h->predictor != 0)
     return fail(h, DGD_EINVAL, "local time stepping uses the Cauchy-Kovalevskaya predictor");
-  const size_t E = (size_t)h->ne;
   dgd_status s;
-  if ((s = dalloc(h, h->Dall, E * h->N * h->kpl * 16 * h->tsize))) return s;
   if (h->facc.n != (size_t)h->nfaces * h->ref.Ns * 10 * h->tsize) {
     if ((s = dalloc(h, h->facc, (size_t)h->nfaces * h->ref.Ns * 10 * h->tsize))) return s;
     HIPCHK(h, hipMemsetAsync(h->facc.p, 0, h->facc.n, h->stream));
@@ -1772,6 +1854,15 @@ dgd_status dgd_get_kernel_times(dgd_handle* h, double* ms, int64_t* launches) {
 dgd_status dgd_get_time_point_states(dgd_handle* h, double* out) {
   if (!h || !out) return DGD_EINVAL;
   if (!h->have_state) return fail(h, DGD_ESTATE, "no state");
+  if (!h->points_in_uz) {
+    const size_t n = (size_t)h->ne * h->ref.Nt * 10 * h->ref.L;
+    dgd_status s = dalloc(h, h->tmp, n * sizeof(double));
+    if (s || (s = dispatch<TimePointsFn>(h, (double*)h->tmp.p))) return s;
+    HIPCHK(h, hipMemcpyAsync(out, h->tmp.p, n * sizeof(double), hipMemcpyDeviceToHost, h->stream));
+    HIPCHK(h, hipStreamSynchronize(h->stream));
+    h->tmp.release();
+    return DGD_OK;
+  }
   // device layout [e][z][l][10] -> [e][z][p][l]
   const size_t L = h->ref.L, Nt = h->ref.Nt;
   const size_t n = (size_t)h->ne * Nt * L * 10;
@@ -1986,12 +2077,11 @@ dgd_status dgd_backward(dgd_handle* h, const double* dl_dseis, double* grad_mu0,
           h->d_keep = (char*)h->segd.p + (size_t)(j - j0) * db;
           h->acc_keep = (char*)h->segacc.p + (size_t)(j - j0) * ab;
         }
-        // the segment's last state is not stepped further: its prediction suffices
-        s = (j + 1 < j1) ? dispatch<StepFn>(h, 1) : dispatch<PredictFn>(h);
+        s = dispatch<PredictFn>(h);
         h->uz_override = h->d_keep = h->acc_keep = nullptr;
-      } else if (j + 1 < j1) {
-        s = dispatch<StepFn>(h, 1);
       }
+      // (the segment's last state is not stepped further)
+      if (s == DGD_OK && j + 1 < j1) s = dispatch<StepFn>(h, 1);
     }
     h->profiling = prof;
     for (long long j = j1 - 1; j >= j0 && s == DGD_OK; --j) {

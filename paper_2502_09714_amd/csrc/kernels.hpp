@@ -78,16 +78,24 @@ template <int P> struct StepArgs {
   T tau[8], gamma[8];
   int* flag;
   // local time stepping: the elements a launch covers (null: all E), the
-  // cluster of every element, the cluster being corrected (-1: global step),
-  // flux integrals accumulated for the coarser side of cluster boundaries
-  // [face][Ns][10], and where the final update goes (null: W9 / Wa)
+  // cluster of every element, the cluster being corrected (-1: global step)
+  // and the flux integrals accumulated for the coarser side of cluster
+  // boundaries [face][Ns][10]
   const int* elist;
   long long nlist;
   const signed char* ecl;
   int lts_c;
   T* facc;
-  T* O9;
-  double* Oa;
+  // Cauchy-Kovalevskaya step (step_kernels.hpp)
+  AF* Dz;               // [E][fragments][64] time derivatives of the prediction
+  const AF* Kck;        // K^e, rows in accumulator order [e][tile][kstep]
+  const typename Prec<Accurate<P>::value>::AF* Ktl;    // transposed K^e [e][tile][kstep]
+  const typename Prec<Accurate<P>::value>::AF* PXpk;   // Pw per chunk, k order of the point integrals
+  const T* Psrc;        // Pw as [point / 4][mode][4]
+  const int* mixP;      // [3][3][64] which averaged-tangent entry a lane's A*_e entry takes
+  const T* mixV;        // [3][3][64] its weight in the volume term
+  T hz[8];              // tau_z dt
+  T wint[8];            // sum_z gamma_z hz^i / i!
 };
 
 // element of this workgroup (-1: none), through the element list if any
@@ -786,204 +794,6 @@ void k_volume(StepArgs<P> a) {
 }
 
 
-// ---- volume and source terms, three elements per wavefront -----------------------
-// The same computation as k_volume with the 10 quantities of three elements
-// side by side in the columns of every reference-matrix contraction (column
-// 10 j + p for element j, quantity p; 30 of 32 columns used): each A fragment
-// feeds two matrix-core products for three elements instead of one product
-// (10 of 16 columns) for one.
-// Column 32 of X (the padding column, never written by the matrix stages)
-// holds Theta^-1 of the three elements in rows 0..26 and their materials in
-// rows 27..50, so that the LDS of one wavefront stays within a twelfth of a
-// compute unit's (three wavefronts per SIMD at degree 4).
-template <int N, int P> struct Vol3LDS {
-  using T = typename Prec<P>::T;
-  static constexpr int RS = 33;                     // 32 columns, odd stride
-  static constexpr int KPL = round_up(Dims<N>::L, Prec<P>::KS);
-  static constexpr int XR = 64 > KPL ? 64 : KPL;
-  static_assert(XR >= 51, "Theta^-1 and materials fit the padding column of X");
-  T X[XR * RS];                                     // point values / integrands of a chunk
-  T W[KPL * RS];                                    // time-point states of the three elements
-  __device__ T& J(int j, int k) { return X[(9 * j + k) * RS + 32]; }
-  __device__ T& M(int j, int k) { return X[(27 + 8 * j + k) * RS + 32]; }
-};
-
-template <int N, int P, class LW = CdmLaw>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2)))
-void k_volume3(StepArgs<P> a) {
-  using PR = Prec<P>;
-  using T = typename PR::T;
-  using Acc = typename PR::Acc;
-  constexpr int PA_ = Accurate<P>::value;
-  using PA = Prec<PA_>;
-  using DM = Dims<N>;
-  constexpr int L = DM::L, Q = DM::Q, Nt = DM::Nt, NCH = DM::NCH, MT = DM::MT;
-  constexpr int KS = PR::KS, KPL = round_up(L, KS), KSL = KPL / KS;
-  constexpr int KSQ = 64 / KS, KSQA = 64 / PA::KS;
-  constexpr int DPL = KPL * 16 / 64;
-  using SL = Vol3LDS<N, P>;
-  constexpr int RS = SL::RS;
-  __shared__ SL S;
-  T* const sX = S.X;
-  T* const sW = S.W;
-
-  const int lane = threadIdx.x;
-  const long long n = a.elist ? a.nlist : a.E;
-  const long long ng = (n + 2) / 3;
-  const long long per = (ng + 7) / 8;
-  const long long g = (long long)(blockIdx.x % 8) * per + blockIdx.x / 8;
-  if (g >= ng) return;
-  long long el[3];
-#pragma unroll
-  for (int j = 0; j < 3; ++j) {
-    const long long i = 3 * g + j;
-    el[j] = i < n ? (a.elist ? (long long)a.elist[i] : i) : -1;
-  }
-  const Law<T> law{a.amax, a.smin};
-  if (lane < 24) {
-    const long long ej = el[lane / 8] >= 0 ? el[lane / 8] : el[0];
-    S.M(lane / 8, lane % 8) = (T)a.mat[ej * 8 + lane % 8];
-  }
-  auto mat_of = [&](int j) {
-    MatP<T> mm;
-    mm.rho = S.M(j, 0);
-    mm.lam = S.M(j, 1);
-    mm.mu = S.M(j, 2);
-    mm.gr = S.M(j, 3);
-    mm.xi0 = S.M(j, 4);
-    mm.cd = S.M(j, 5);
-    return mm;
-  };
-  if (lane < 27) {
-    const long long ej = el[lane / 9];
-    S.J(lane / 9, lane % 9) = ej >= 0 ? (T)a.geo[ej * 16 + lane % 9] : T(0);
-  }
-  for (int i = lane; i < KPL * RS; i += 64) sW[i] = T(0);
-
-
-  T vs[NCH][3][3], ss[NCH][3][6], sacc[NCH][3];
-#pragma unroll
-  for (int c = 0; c < NCH; ++c)
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      sacc[c][j] = T(0);
-#pragma unroll
-      for (int k = 0; k < 3; ++k) vs[c][j][k] = T(0);
-#pragma unroll
-      for (int k = 0; k < 6; ++k) ss[c][j][k] = T(0);
-    }
-  for (int z = 0; z < Nt; ++z) {
-    const T gz = a.gamma[z];
-    __syncthreads();
-    // the three elements' time-point states, quantities side by side
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      // (rows L..KPL-1 keep the zeros set at the start)
-      const T* Uz = a.Uz + (size_t)(el[j] >= 0 ? el[j] : el[0]) * DM::UZE + z * DM::UZT;
-#pragma unroll
-      for (int q = 0; q < (DM::UZT + 63) / 64; ++q) {
-        const int idx = lane + 64 * q;
-        if (idx < DM::UZT) sW[(idx / 10) * RS + 10 * j + idx % 10] = el[j] >= 0 ? Uz[idx] : T(0);
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-      Acc C[4][2];
-      zero_C2<P, 4>(C);
-      wave_gemm2<P, 4, KSL, RS>(a.Vpk + (size_t)c * 4 * KSL * 64, sW, C, lane);
-      store_C2<P, 4, RS>(C, sX, 64, T(1), lane);
-      __syncthreads();
-      if (64 * c + lane < Q) {
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-          T u[10];
-#pragma unroll
-          for (int k = 0; k < 10; ++k) u[k] = sX[lane * RS + 10 * j + k];
-          T sig[6];
-          sacc[c][j] += gz * LW::stress_rate(u, mat_of(j), law, sig);
-#pragma unroll
-          for (int k = 0; k < 6; ++k) ss[c][j][k] += gz * sig[k];
-#pragma unroll
-          for (int k = 0; k < 3; ++k) vs[c][j][k] += gz * u[6 + k];
-        }
-      }
-      __syncthreads();
-    }
-  }
-
-  // damage source first (its accumulators are free again before those of
-  // the volume contraction are taken): the three elements' rate integrals in
-  // columns 0..2 of one 16-column tile, projected, times dt, to columns 0..2
-  // of W (the damage columns 10 j + 9 of the volume contraction are zero: no
-  // damage flux)
-  {
-    typename PA::Acc Sc[MT];
-    zero_C<PA_, MT>(Sc);
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-      __syncthreads();
-#pragma unroll
-      for (int k = 0; k < 16; ++k) sX[lane * RS + k] = k < 3 ? sacc[c][k] : T(0);
-      __syncthreads();
-      wave_gemm<PA_, MT, KSQA, RS>(a.Ppk + (size_t)c * MT * KSQA * 64, sX, Sc, lane);
-    }
-    store_C<PA_, MT, RS, 3>(Sc, sW, L, (T)a.dt, lane);
-  }
-
-  // volume contraction sum_e Sw^e G^e
-  Acc Vc[MT][2];
-  zero_C2<P, MT>(Vc);
-#pragma unroll 1
-  for (int ee = 0; ee < 3; ++ee) {
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-#pragma unroll
-      for (int j = 0; j < 3; ++j) {
-        const T ir = T(1) / S.M(j, 0);
-        T Jr[3];
-#pragma unroll
-        for (int d = 0; d < 3; ++d) Jr[d] = S.J(j, ee * 3 + d);
-        T* row = sX + lane * RS + 10 * j;
-#pragma unroll
-        for (int p = 0; p < 6; ++p) {
-          const int ii = kVI[p], jj = kVJ[p];
-          row[p] = T(-0.5) * (Jr[jj] * vs[c][j][ii] + Jr[ii] * vs[c][j][jj]);
-        }
-#pragma unroll
-        for (int ii = 0; ii < 3; ++ii) {
-          T t = T(0);
-#pragma unroll
-          for (int d = 0; d < 3; ++d) t += Jr[d] * ss[c][j][sym_idx(ii, d)];
-          row[6 + ii] = -ir * t;
-        }
-        row[9] = T(0);
-      }
-      sX[lane * RS + 30] = T(0);
-      sX[lane * RS + 31] = T(0);
-      __syncthreads();
-      wave_gemm2<P, MT, KSQ, RS>(a.Spk + (size_t)(ee * NCH + c) * MT * KSQ * 64, sX, Vc, lane);
-      __syncthreads();
-    }
-  }
-  store_C2<P, MT, RS>(Vc, sX, L, (T)a.dt, lane);
-  __syncthreads();
-  // U^n + volume for the nine wave quantities; the damage increment joins the
-  // FP64 damage plane
-#pragma unroll
-  for (int j = 0; j < 3; ++j) {
-    if (el[j] < 0) continue;
-    const long long e = el[j];
-    const T* U9 = a.U9 + e * 9 * L;
-    T* W9 = a.W9 + e * 9 * L;
-    for (int idx = lane; idx < 9 * L; idx += 64) {
-      const int p = idx / L, l = idx - p * L;
-      W9[idx] = U9[idx] + sX[l * RS + 10 * j + p];
-    }
-    if (lane < L) a.Wa[e * L + lane] = a.Ua[e * L + lane] + (double)sW[lane * RS + j];
-  }
-}
-
 // One wavefront per face (interior faces once, boundary faces once): traces of
 // both sides at the shared face points for every time point, LLF (or
 // boundary) flux with the normal of the face's first element, time quadrature.
@@ -1006,8 +816,8 @@ template <int N, int P> struct FaceWaves {
 
 template <int N, int P, class LW = CdmLaw>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(FaceWaves<N, P>::value)))
-void k_face_flux(StepArgs<P> a, const int* faces, long long nfaces, typename Prec<P>::T* fflux,
-                 const int* flist) {
+void k_face_flux(StepArgs<P> a, const int* faces, long long nfaces,
+                 typename Prec<P>::T* fflux) {
   using PR = Prec<P>;
   using T = typename PR::T;
   using Acc = typename PR::Acc;
@@ -1022,9 +832,8 @@ void k_face_flux(StepArgs<P> a, const int* faces, long long nfaces, typename Pre
   __shared__ T sTp[Nt * TS];
 
   const int lane = threadIdx.x;
-  long long fid = elem_of_block(nfaces);
+  const long long fid = elem_of_block(nfaces);
   if (fid >= nfaces) return;
-  if (flist) fid = flist[fid];
   const int ef = faces[fid * 2], of = faces[fid * 2 + 1];
   const long long e = ef >> 2;
   const int f = ef & 3;
@@ -1129,30 +938,19 @@ __global__ __launch_bounds__(64) void k_lift_update(StepArgs<P> a, const int* fm
   const long long e = elem_index(a);
   if (e < 0) return;
   // every HBM load is issued before the first use: the four faces' fluxes
-  // (gathered by face) and the partial update.  Under local time stepping a
-  // face shared with the finer cluster brings the flux integral that cluster
-  // accumulated over its two steps (already scaled by its step), and clears it.
+  // (gathered by face) and the partial update
   T fv[4][FPL], sc[4];
   int sp[4];
 #pragma unroll
   for (int f = 0; f < 4; ++f) {
     const int fm = fmap[e * 4 + f];
     sp[f] = conn_perm(a.conn[(e * 4 + f) * 2 + 1]);
-    const int nb = a.conn[(e * 4 + f) * 2];
-    const bool fine = a.lts_c > 0 && nb >= 0 && a.ecl[nb] == a.lts_c - 1;
-    sc[f] = (T)((fm & 1 ? -1.0 : 1.0) * a.fgeo[(e * 4 + f) * 4 + 3] * (fine ? 1.0 : a.dt));
-    T* fl = (fine ? a.facc : (T*)fflux) + (size_t)(fm >> 1) * Ns * 10;
+    sc[f] = (T)((fm & 1 ? -1.0 : 1.0) * a.fgeo[(e * 4 + f) * 4 + 3] * a.dt);
+    const T* fl = fflux + (size_t)(fm >> 1) * Ns * 10;
 #pragma unroll
     for (int j = 0; j < FPL; ++j) {
       const int idx = lane + 64 * j;
       fv[f][j] = idx < Ns * 10 ? fl[idx] : T(0);
-    }
-    if (fine) {
-#pragma unroll
-      for (int j = 0; j < FPL; ++j) {
-        const int idx = lane + 64 * j;
-        if (idx < Ns * 10) fl[idx] = T(0);
-      }
     }
   }
   T* W9 = a.W9 + e * 9 * L;
@@ -1184,8 +982,6 @@ __global__ __launch_bounds__(64) void k_lift_update(StepArgs<P> a, const int* fm
   store_C<P, MT>(Fc, sF, L, T(1), lane);
   __syncthreads();
   bool bad = false;
-  T* O9 = (a.O9 ? a.O9 : a.W9) + e * 9 * L;
-  double* Oa = a.Oa ? a.Oa : a.Wa;
 #pragma unroll
   for (int j = 0; j < WPL; ++j) {
     const int idx = lane + 64 * j;
@@ -1193,63 +989,15 @@ __global__ __launch_bounds__(64) void k_lift_update(StepArgs<P> a, const int* fm
       const int p = idx / L, l = idx - p * L;
       const T v = wv[j] - sF[l * R + p];
       bad |= !isfinite(v);
-      O9[idx] = v;
+      W9[idx] = v;
     }
   }
   if (lane < L) {
     const double v = wa - (double)sF[lane * R + 9];
     bad |= !isfinite(v);
-    Oa[e * L + lane] = v;
+    a.Wa[e * L + lane] = v;
   }
   if (bad) a.flag[0] = 1;
-}
-
-// Local time stepping: the state of each listed element at the time points
-// t_pred + off + tau_z dt of the cluster being corrected, from its kept
-// prediction (D^0 = its state, D^1..D^N kept by k_predict), written to Uz in
-// the [l][16] layout; off is the time since the element's own prediction.
-// The Taylor sum is formed exactly as in k_predict.
-struct ClusterOffsets { double v[8]; };   // time since each cluster's prediction
-
-template <int N, int P>
-__global__ __launch_bounds__(64) void k_taylor(StepArgs<P> a, ClusterOffsets offs) {
-  using T = typename Prec<P>::T;
-  using DM = Dims<N>;
-  constexpr int L = DM::L, Nt = DM::Nt;
-  constexpr int KPL = round_up(L, Prec<P>::KS), DPL = KPL * 16 / 64;
-  const int lane = threadIdx.x;
-  const long long e = elem_index(a);
-  if (e < 0) return;
-  const double off = offs.v[a.ecl[e]];
-  const T* U9 = a.U9 + e * 9 * L;
-  const T* De = a.Dkeep + (size_t)e * N * KPL * 16;
-  T d[N + 1][DPL];
-#pragma unroll
-  for (int j = 0; j < DPL; ++j) {
-    const int idx = lane + 64 * j, l = idx >> 4, p = idx & 15;
-    d[0][j] = (l < L && p < 10) ? (p < 9 ? U9[p * L + l] : (T)a.Ua[e * L + l]) : T(0);
-  }
-#pragma unroll
-  for (int i = 1; i <= N; ++i)
-#pragma unroll
-    for (int j = 0; j < DPL; ++j) d[i][j] = De[(i - 1) * KPL * 16 + lane + 64 * j];
-  T* Uzo = a.Uz + (size_t)e * DM::UZE;
-#pragma unroll
-  for (int z = 0; z < Nt; ++z) {
-    T cz[N + 1];
-    cz[0] = T(1);
-    const T h = a.tau[z] * (T)a.dt + (T)off;   // as k_predict's when off = 0
-#pragma unroll
-    for (int i = 1; i <= N; ++i) cz[i] = cz[i - 1] * h / T(i);
-#pragma unroll
-    for (int j = 0; j < DPL; ++j) {
-      T v = T(0);
-#pragma unroll
-      for (int i = 0; i <= N; ++i) v += cz[i] * d[i][j];
-      const int idx = lane + 64 * j, l = idx >> 4, p = idx & 15;
-      if (l < L && p < 10) Uzo[z * DM::UZT + l * 10 + p] = v;
-    }
-  }
 }
 
 // Local time stepping: faces between the cluster being corrected and the next

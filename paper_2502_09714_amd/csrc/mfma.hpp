@@ -192,7 +192,7 @@ __device__ inline void wave_gemm(const typename Prec<P>::AF* __restrict__ Apk,
     return;
   }
   // A fragments of step s + PD requested before the products of step s (see
-  // wave_gemm2)
+  // below)
   constexpr int PD = DGD_PF_STEPS, NB = PD + 1;
   AF a[NB][MT];
 #pragma unroll
@@ -222,7 +222,7 @@ __device__ inline void wave_gemm_shared_a(const typename Prec<P>::AF* __restrict
   using PR = Prec<P>;
   using AF = typename PR::AF;
   // A and B fragments (A from L2/HBM, B from HBM or LDS) PD steps ahead (see
-  // wave_gemm2); the NZ x MT products of a step cover their latency
+  // below); the NZ x MT products of a step cover their latency
   constexpr int PD = DGD_PF_SHARED, NB = PD + 1;
   AF a[NB][MT], b[NB][NZ];
 #pragma unroll
@@ -272,67 +272,6 @@ __device__ inline void wave_gemm_tiles(const typename Prec<P>::AF* __restrict__ 
   }
 }
 
-// C += A x B for a B of 32 columns (two 16-column tiles, row stride RS): each
-// A fragment feeds two matrix-core products.
-template <int P, int MT, int KSTEPS, int RS>
-__device__ inline void wave_gemm2(const typename Prec<P>::AF* __restrict__ Apk,
-                                  const typename Prec<P>::T* B, typename Prec<P>::Acc (&C)[MT][2],
-                                  int lane) {
-  using PR = Prec<P>;
-  using AF = typename PR::AF;
-  // A fragments come from L2/HBM: those of step s + PD are requested before
-  // the products of step s are issued (the scheduling fence keeps the
-  // compiler from sinking the loads down to their use), so that PD steps of
-  // matrix-core work cover their latency
-  constexpr int PD = DGD_PF_STEPS, NB = PD + 1;
-  AF a[NB][MT];
-#pragma unroll
-  for (int s = 0; s < PD && s < KSTEPS; ++s)
-#pragma unroll
-    for (int t = 0; t < MT; ++t) a[s % NB][t] = Apk[((size_t)t * KSTEPS + s) * 64 + lane];
-#pragma unroll
-  for (int s = 0; s < KSTEPS; ++s) {
-    if (s + PD < KSTEPS) {
-#pragma unroll
-      for (int t = 0; t < MT; ++t)
-        a[(s + PD) % NB][t] = Apk[((size_t)t * KSTEPS + s + PD) * 64 + lane];
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    const AF b0 = PR::template loadB<RS>(B, s, lane);
-    const AF b1 = PR::template loadB<RS>(B + 16, s, lane);
-#pragma unroll
-    for (int t = 0; t < MT; ++t) {
-      C[t][0] = PR::mma(a[s % NB][t], b0, C[t][0]);
-      C[t][1] = PR::mma(a[s % NB][t], b1, C[t][1]);
-    }
-  }
-}
-
-template <int P, int MT>
-__device__ inline void zero_C2(typename Prec<P>::Acc (&C)[MT][2]) {
-#pragma unroll
-  for (int t = 0; t < MT; ++t)
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) C[t][h][i] = 0;
-}
-
-// Store 32-column C tiles to a [rows][RS] matrix, rows >= rmax dropped, times scale.
-template <int P, int MT, int RS>
-__device__ inline void store_C2(const typename Prec<P>::Acc (&C)[MT][2], typename Prec<P>::T* dst,
-                                int rmax, typename Prec<P>::T scale, int lane) {
-#pragma unroll
-  for (int t = 0; t < MT; ++t)
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int r = 16 * t + Prec<P>::crow(lane, i);
-        if (r < rmax) dst[r * RS + 16 * h + (lane & 15)] = scale * C[t][h][i];
-      }
-}
-
 // C += A x B with B[k][n] = (n == 9) ? v[k] : 0 (a vector placed in the damage column)
 template <int P, int MT, int KSTEPS>
 __device__ inline void wave_gemm_col9(const typename Prec<P>::AF* __restrict__ Apk,
@@ -341,7 +280,7 @@ __device__ inline void wave_gemm_col9(const typename Prec<P>::AF* __restrict__ A
   using PR = Prec<P>;
   using AF = typename PR::AF;
   // A fragments of step s + PD requested before the products of step s (see
-  // wave_gemm2)
+  // below)
   constexpr int PD = DGD_PF_STEPS, NB = PD + 1;
   AF a[NB][MT];
 #pragma unroll

@@ -410,6 +410,216 @@ __device__ inline void boundary_flux(int kind, const T* u, const T n[3], const M
   F[9] = T(0);
 }
 
+// ---- the laws as the step kernels evaluate them ------------------------------------
+// The same functions with the products of material constants formed once per
+// wavefront, hardware reciprocals and square roots (1 ulp in FP32; two Newton
+// steps in FP64) and the invariants shared by what one point needs.  Those
+// kernels are bound by vector issue: FP32 matrix products run on the same ALUs.
+__device__ inline float rcp1(float x) { return __builtin_amdgcn_rcpf(x); }
+__device__ inline double rcp1(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(fma(-x, r, 1.0), r, r);
+  return fma(fma(-x, r, 1.0), r, r);
+}
+__device__ inline float sqrt1(float x) { return __builtin_amdgcn_sqrtf(x); }
+__device__ inline double sqrt1(double x) { return sqrt(x); }
+
+// material constants: ir = 1/rho, mu2 = 2 mu0; CDM: xx = 2 xi0, rc = C_d gamma_r;
+// IVM: gr = gamma_b, rc = 1/(gamma_b tau_b)
+template <class T> struct StepMat { T ir, lam, mu2, gr, xi0, xx, rc; };
+
+// normal n of a face and the strain rows of its flux for the velocity v
+template <class T>
+__device__ inline void strain_flux(const T* v, const T n[3], T F[10]) {
+  F[0] = -v[0] * n[0];
+  F[1] = -v[1] * n[1];
+  F[2] = -v[2] * n[2];
+  F[3] = T(-0.5) * (v[0] * n[1] + v[1] * n[0]);
+  F[4] = T(-0.5) * (v[1] * n[2] + v[2] * n[1]);
+  F[5] = T(-0.5) * (v[2] * n[0] + v[0] * n[2]);
+}
+
+struct CdmStep {
+  using Plain = CdmLaw;
+  template <class T> struct Inv { T I1, s, xi, is, I1p, im, ac; };
+  template <class T>
+  __device__ static StepMat<T> constants(const MatP<T>& m) {
+    return {T(1) / m.rho, m.lam, T(2) * m.mu, m.gr, m.xi0, T(2) * m.xi0, m.cd * m.gr};
+  }
+  // invariants of the strain scaled by its largest entry; is = 1/s' is zero (and
+  // with it xi) and s is zero in the guard sqrt(I2) <= smin
+  template <class T>
+  __device__ static Inv<T> invariants(const T* u, const Law<T>& law) {
+    Inv<T> v;
+    const T mx = fmax(fmax(fmax(fabs(u[0]), fabs(u[1])), fmax(fabs(u[2]), fabs(u[3]))),
+                      fmax(fabs(u[4]), fabs(u[5])));
+    v.im = mx > law.smin * T(0.25) ? rcp1(mx) : T(0);
+    const T e0 = u[0] * v.im, e1 = u[1] * v.im, e2 = u[2] * v.im, e3 = u[3] * v.im,
+            e4 = u[4] * v.im, e5 = u[5] * v.im;
+    const T sp = sqrt1(e0 * e0 + e1 * e1 + e2 * e2 + T(2) * (e3 * e3 + e4 * e4 + e5 * e5));
+    const T s = mx * sp;
+    const bool on = s > law.smin;
+    v.s = on ? s : T(0);
+    v.is = on ? rcp1(sp) : T(0);
+    v.I1p = e0 + e1 + e2;
+    v.xi = v.I1p * v.is;
+    v.I1 = u[0] + u[1] + u[2];
+    v.ac = fmin(fmax(u[9], T(0)), law.amax);
+    return v;
+  }
+  template <class T>
+  __device__ static void stress(const Inv<T>& v, const T* u, const StepMat<T>& m, T sig[6]) {
+    const T agr = v.ac * m.gr;
+    const T iso = m.lam * v.I1 - agr * v.s, c = m.mu2 + agr * (m.xx - v.xi);
+#pragma unroll
+    for (int k = 0; k < 6; ++k) sig[k] = k < 3 ? c * u[k] + iso : c * u[k];
+  }
+  template <class T> __device__ static T rate(const Inv<T>& v, const StepMat<T>& m) {
+    return m.rc * (v.s * v.s) * fmax(v.xi - m.xi0, T(0));
+  }
+  // Cell average of the tangent from NACC sums over the points: weight times
+  // coef, a gamma_r eps_k / s, a gamma_r I1 eps_k eps_q / s^3 (k <= q) and the
+  // damage column's parts (35 sums for the 42 entries).
+  static constexpr int NACC = 35;
+  // position of the pair k <= q among the 21
+  __device__ static constexpr int pair(int k, int q) { return 7 + k * 6 - k * (k - 1) / 2 + (q - k); }
+  template <class T>
+  __device__ static void tangent_add(const Inv<T>& v, const T* u, const StepMat<T>& m,
+                                     const Law<T>& law, T w, T (&acc)[NACC]) {
+    const T agr = v.ac * m.gr;
+    acc[0] += w * (m.mu2 + agr * (m.xx - v.xi));
+    const T c1 = w * agr * v.is, c2 = c1 * v.xi * v.is;
+    T ep[6];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) ep[k] = u[k] * v.im;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+      acc[1 + k] += c1 * ep[k];
+      const T ck = c2 * ep[k];
+#pragma unroll
+      for (int q = k; q < 6; ++q) acc[pair(k, q)] += ck * ep[q];
+    }
+    const T dw = (u[9] >= T(0) && u[9] <= law.amax) ? w * m.gr : T(0);
+    acc[28] += dw * v.s;
+    const T cb = dw * (m.xx - v.xi);
+#pragma unroll
+    for (int k = 0; k < 6; ++k) acc[29 + k] += cb * u[k];
+  }
+  // entry (k, q) of the average from the sums (weights summing to 1)
+  template <class T>
+  __device__ static T tangent_entry(const T* acc, const StepMat<T>& m, int k, int q) {
+    if (q == 6) return acc[29 + k] - (k < 3 ? acc[28] : T(0));
+    const T w = q < 3 ? T(1) : T(2);
+    T v = w * acc[k < q ? pair(k, q) : pair(q, k)];
+    if (k == q) v += acc[0];
+    if (k < 3 && q < 3) v += m.lam;
+    if (k < 3) v -= w * acc[1 + q];
+    if (q < 3) v -= acc[1 + k];
+    return v;
+  }
+  // larger of the two materials' squared Lax-Friedrichs speeds at the mean state
+  // (acoustic_plane and llf_speed above; the plane is the strain's, not the
+  // material's)
+  template <class T>
+  __device__ static T speed2(const T* u, const T n[3], const StepMat<T>& ma, const StepMat<T>& mb,
+                             bool same, const Law<T>& law) {
+    const Inv<T> v = invariants(u, law);
+    const T e0 = (u[0] * n[0] + u[3] * n[1] + u[5] * n[2]) * v.im,
+            e1 = (u[3] * n[0] + u[1] * n[1] + u[4] * n[2]) * v.im,
+            e2 = (u[5] * n[0] + u[4] * n[1] + u[2] * n[2]) * v.im;
+    const T an = e0 * n[0] + e1 * n[1] + e2 * n[2];
+    const T t0 = e0 - an * n[0], t1 = e1 - an * n[1], t2 = e2 - an * n[2];
+    const T b2 = t0 * t0 + t1 * t1 + t2 * t2, k2 = v.xi * v.is;
+    auto one = [&](const StepMat<T>& m) {
+      const T agr = v.ac * m.gr;
+      const T h = T(0.5) * (m.mu2 + agr * (m.xx - v.xi));
+      const T c1 = agr * v.is, c2 = c1 * k2;
+      const T q12 = c2 * an - c1;
+      const T m11 = (m.lam + h) + an * (q12 - c1), m22 = c2 * b2;
+      const T d = T(0.5) * (m11 - m22);
+      const T l = T(0.5) * (m11 + m22) + sqrt1(d * d + b2 * (q12 * q12));
+      return (h + fmax(l, T(0))) * m.ir;
+    };
+    const T a = one(ma);
+    return fmax(same ? a : fmax(a, one(mb)), T(0));
+  }
+};
+
+struct IvmStep {
+  using Plain = IvmLaw;
+  template <class T> struct Inv { T I1, I2, g, ac; };
+  template <class T>
+  __device__ static StepMat<T> constants(const MatP<T>& m) {
+    return {T(1) / m.rho, m.lam, T(2) * m.mu, m.gr, T(0), T(0), m.cd};
+  }
+  template <class T>
+  __device__ static Inv<T> invariants(const T* u, const Law<T>& law) {
+    Inv<T> v;
+    v.I1 = u[0] + u[1] + u[2];
+    v.I2 = u[0] * u[0] + u[1] * u[1] + u[2] * u[2] +
+           T(2) * (u[3] * u[3] + u[4] * u[4] + u[5] * u[5]);
+    v.ac = fmin(fmax(u[9], T(0)), law.amax);
+    v.g = T(1) - v.ac;
+    return v;
+  }
+  template <class T>
+  __device__ static void stress(const Inv<T>& v, const T* u, const StepMat<T>& m, T sig[6]) {
+    const T c = m.mu2 * v.g, iso = m.lam * v.g * v.I1;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) sig[k] = k < 3 ? c * u[k] + iso : c * u[k];
+  }
+  template <class T> __device__ static T rate(const Inv<T>& v, const StepMat<T>& m) {
+    const T q = v.ac * rcp1(v.g);
+    return m.rc * (T(0.5) * (m.lam * v.I1 * v.I1 + m.mu2 * v.I2) - m.gr * q * q);
+  }
+  // cell average of the tangent from NACC sums (see CdmStep)
+  static constexpr int NACC = 7;
+  template <class T>
+  __device__ static void tangent_add(const Inv<T>& v, const T* u, const StepMat<T>&,
+                                     const Law<T>& law, T w, T (&acc)[NACC]) {
+    acc[0] += w * v.g;
+    const T dw = (u[9] >= T(0) && u[9] <= law.amax) ? w : T(0);
+#pragma unroll
+    for (int k = 0; k < 6; ++k) acc[1 + k] += dw * u[k];
+  }
+  template <class T>
+  __device__ static T tangent_entry(const T* acc, const StepMat<T>& m, int k, int q) {
+    if (q == 6)
+      return -(m.mu2 * acc[1 + k] + (k < 3 ? m.lam * (acc[1] + acc[2] + acc[3]) : T(0)));
+    return acc[0] * ((k == q ? m.mu2 : T(0)) + (k < 3 && q < 3 ? m.lam : T(0)));
+  }
+  // the acoustic tensor is that of the damaged isotropic moduli
+  template <class T>
+  __device__ static T speed2(const T* u, const T*, const StepMat<T>& ma, const StepMat<T>& mb, bool,
+                             const Law<T>& law) {
+    const T g = T(1) - fmin(fmax(u[9], T(0)), law.amax);
+    return fmax(g * fmax((ma.lam + ma.mu2) * ma.ir, (mb.lam + mb.mu2) * mb.ir), T(0));
+  }
+};
+
+// Local Lax-Friedrichs flux at one face point: the strain rows are linear in the
+// velocity, so they take the mean state's; the velocity rows the mean of sigma n / rho.
+template <class LW, class T>
+__device__ inline void llf_flux_step(const T* um, const T* up, const T n[3], const StepMat<T>& ma,
+                                     const StepMat<T>& mb, bool same, const Law<T>& law, T F[10]) {
+  T sa[6], sb[6], ub[10];
+  LW::stress(LW::invariants(um, law), um, ma, sa);
+  LW::stress(LW::invariants(up, law), up, mb, sb);
+#pragma unroll
+  for (int k = 0; k < 10; ++k) ub[k] = T(0.5) * (um[k] + up[k]);
+  const T hc = T(0.5) * sqrt1(LW::speed2(ub, n, ma, mb, same, law));
+  strain_flux(ub + 6, n, F);
+  const T ia = T(-0.5) * ma.ir, ib = T(-0.5) * mb.ir;
+#pragma unroll
+  for (int k = 0; k < 6; ++k) sa[k] = ia * sa[k] + ib * sb[k];
+  F[6] = sa[0] * n[0] + sa[3] * n[1] + sa[5] * n[2];
+  F[7] = sa[3] * n[0] + sa[1] * n[1] + sa[4] * n[2];
+  F[8] = sa[5] * n[0] + sa[4] * n[1] + sa[2] * n[2];
+  F[9] = T(0);
+#pragma unroll
+  for (int k = 0; k < 10; ++k) F[k] += hc * (um[k] - up[k]);
+}
+
 // strain-energy density W (FP64 diagnostics)
 __device__ inline double cdm_energy(const double* u, const MatP<double>& m,
                                     const Law<double>& law) {
