@@ -67,6 +67,7 @@ struct DevBuf {
 
 struct dgd_handle {
   int N = 0, prec = 0, device = 0;
+  int ncu = 256;          // compute units of the device
   hipStream_t stream = nullptr;
   double* noalloc_part = nullptr;   // this device's static partial-sum buffer
   std::string err;
@@ -74,7 +75,8 @@ struct dgd_handle {
   size_t tsize = 8;  // bytes of the working type
   // reference data on the device
   DevBuf Vpk, Kpk, Spk, Fpk, Lpk, Ppk, Vd, wqd, Pwd, betad, KPpk;
-  DevBuf Kck, Ktl, PXpk, Psrc, mixP, mixV;   // Cauchy-Kovalevskaya step (step_kernels.hpp)
+  // Cauchy-Kovalevskaya step (step_kernels.hpp)
+  DevBuf Vw, Vt, Kw, Kt, Ktw, PXw, PXleft, Rw, Fst, Psi, Psrc, mixP, mixV;
   size_t dz_elem = 0;     // bytes of one element's time derivatives
   double points_dt = 0.0;      // step of the last step's derivatives
   bool points_in_uz = false;   // the last step left time-point states in Uz, not derivatives in Dz
@@ -139,7 +141,8 @@ struct dgd_handle {
                      &s_elem, &s_M6, &s_dphi, &s_onset, &s_param, &s_rhoJ, &r_elem, &r_phi, &seis,
                      &VTpk, &STpk, &PTpk, &KTpk, &lam[0], &lam[1], &gtr, &gmuf, &lzf, &gmu, &gcd, &adjW9,
                      &adjWa, &dlds, &seg9, &sega, &seguz, &segd, &segacc, &save9, &savea, &st9, &sta,
-                     &KPpk, &ecl, &facc, &Kck, &Ktl, &PXpk, &Psrc, &mixP, &mixV, &Dz, &Vpk32, &Kpk32, &Spk32, &Fpk32, &Lpk32, &Ppk32,
+                     &KPpk, &ecl, &facc, &Vw, &Vt, &Kw, &Kt, &Ktw, &PXw,
+                     &PXleft, &Rw, &Fst, &Psi, &Psrc, &mixP, &mixV, &Dz, &Vpk32, &Kpk32, &Spk32, &Fpk32, &Lpk32, &Ppk32,
                      &KPpk32};
     for (DevBuf* b : all) b->release();
     for (DevBuf& b : ck9) b.release();
@@ -338,46 +341,145 @@ dgd_status build_packed(dgd_handle* h) {
   return DGD_OK;
 }
 
+// one wide fragment of a contraction of form M, appended to out: val(n, g, j) is
+// the entry of lane (g, n), j its place among the lane's entries
+template <int M, class F>
+void append_frag(std::vector<char>& out, F val) {
+  if constexpr (M == PREC_X3) {
+    uint16_t v[3][64][8];
+    for (int lane = 0; lane < 64; ++lane)
+      for (int j = 0; j < 8; ++j) {
+        float x = (float)val(lane & 15, lane >> 4, j);
+        for (int k = 0; k < 3; ++k) {
+          v[k][lane][j] = bf16_bits(x);
+          x -= bf16_value(v[k][lane][j]);
+        }
+      }
+    out.insert(out.end(), (const char*)v, (const char*)v + sizeof v);
+  } else {
+    typename Prec<M>::T v[64];
+    for (int lane = 0; lane < 64; ++lane)
+      v[lane] = (typename Prec<M>::T)val(lane & 15, lane >> 4, 0);
+    out.insert(out.end(), (const char*)v, (const char*)v + sizeof v);
+  }
+}
+
+// Orthonormal polynomials of degree <= N on the face, at its points, with respect
+// to the weights beta: psi[m][i] (modified Gram-Schmidt, twice, on monomials)
+std::vector<std::vector<double>> face_modes(const RefData& r) {
+  std::vector<std::vector<double>> psi;
+  for (int d = 0; d <= r.N; ++d)
+    for (int b = 0; b <= d; ++b) {
+      std::vector<double> v(r.Ns);
+      for (int i = 0; i < r.Ns; ++i)
+        v[i] = std::pow(r.eta[2 * i] - 1.0 / 3, d - b) * std::pow(r.eta[2 * i + 1] - 1.0 / 3, b);
+      for (int pass = 0; pass < 2; ++pass) {
+        for (const auto& w : psi) {
+          double s = 0.0;
+          for (int i = 0; i < r.Ns; ++i) s += r.beta[i] * v[i] * w[i];
+          for (int i = 0; i < r.Ns; ++i) v[i] -= s * w[i];
+        }
+        double s = 0.0;
+        for (int i = 0; i < r.Ns; ++i) s += r.beta[i] * v[i] * v[i];
+        for (double& x : v) x /= std::sqrt(s);
+      }
+      psi.push_back(v);
+    }
+  return psi;
+}
+
 // operators of the Cauchy-Kovalevskaya step's kernels (step_kernels.hpp)
 template <int N, int P>
 dgd_status build_step_packs(dgd_handle* h) {
   using DM = Dims<N>;
-  using AF = typename HostAF<P>::type;
   using T = typename Prec<P>::T;
-  constexpr int PA = Accurate<P>::value;
-  constexpr int KS = Prec<P>::KS, L = DM::L, Q = DM::Q, MT = DM::MT;
-  constexpr int KSL = round_up(L, KS) / KS, Q4 = (Q + 3) / 4;
+  constexpr int M = MatForm<N, P>::value;
+  constexpr bool X3 = M == PREC_X3;
+  constexpr int L = DM::L, Q = DM::Q, Ns = DM::Ns, MT = DM::MT, NCH = DM::NCH, NST = DM::NST;
+  constexpr int NT1 = (modes_upto(N - 1) + 15) / 16, Q4 = (Q + 3) / 4, NM2 = FaceModes<N>::value;
+  using SL = Steps<M, L>;
   const RefData& r = h->ref;
-  // row 16 t + m of a pack whose product's rows become the next k order
-  auto row = [](int m) { return (m & ~15) + mperm<P>(m & 15); };
-  constexpr int KSA = round_up(L, Prec<PA>::KS) / Prec<PA>::KS;
-  std::vector<AF> kc;
-  std::vector<typename HostAF<PA>::type> kt;
-  for (int e = 0; e < 3; ++e) {
-    append(kc, pack_A<P>(
-                   [&](int m, int kk) {
-                     const int k = row(m);
-                     return (k < L && kk < L && r.deg[k] < r.deg[kk]) ? r.K[((size_t)e * L + k) * L + kk]
-                                                                     : 0.0;
-                   },
-                   MT, KSL));
-    append(kt, pack_A<PA>(
-                   [&](int m, int kk) {
-                     return (m < L && kk < L && r.deg[kk] < r.deg[m]) ? r.K[((size_t)e * L + kk) * L + m]
-                                                                     : 0.0;
-                   },
-                   MT, KSA));
+  // row of entry j of wide step s (contractions over modes) and of a leftover step
+  auto mode = [](int s, int g, int j) { return X3 ? 32 * s + 16 * (j >> 2) + 4 * g + (j & 3) : 4 * s + g; };
+  auto V = [&](int q, int l) { return (q < Q && l < L) ? r.V[(size_t)q * L + l] : 0.0; };
+  auto K = [&](int e, int k, int l) {
+    return (k < L && l < L && r.deg[k] < r.deg[l]) ? r.K[((size_t)e * L + k) * L + l] : 0.0;
+  };
+  auto Pw = [&](int l, int q) { return (l < L && q < Q) ? r.Pw[(size_t)l * Q + q] : 0.0; };
+  std::vector<char> vw, kw, ktw, pw, rw;
+  std::vector<T> vt, kt, pl, fs, psi, ps((size_t)Q4 * L * 4, T(0));
+  auto tail = [](std::vector<T>& out, auto val) {
+    for (int lane = 0; lane < 64; ++lane) out.push_back((T)val(lane & 15, lane >> 4));
+  };
+  for (int t = 0; t < NCH * 4; ++t)
+    for (int s = 0; s < SL::WIDE; ++s)
+      append_frag<M>(vw, [&](int n, int g, int j) { return V(16 * t + n, mode(s, g, j)); });
+  if constexpr (SL::TAIL)
+    for (int t = 0; t < NCH * 4; ++t)
+      tail(vt, [&](int n, int g) { return V(16 * t + n, 32 * SL::WIDE + g); });
+  if constexpr (X3 && Deriv<N>::rows(16 * (Deriv<N>::NT - 1)) <= 4)
+    for (int t = 0; t < NCH * 4; ++t) tail(vt, [&](int n, int g) { return V(16 * t + n, g); });
+  for (int e = 0; e < 3; ++e)
+    for (int t = 0; t < NT1; ++t) {
+      for (int s = 0; s < SL::WIDE; ++s)
+        append_frag<M>(kw, [&](int n, int g, int j) { return K(e, mperm<N, M>(t, n), mode(s, g, j)); });
+      if constexpr (SL::TAIL)
+        tail(kt, [&](int n, int g) { return K(e, mperm<N, M>(t, n), 32 * SL::WIDE + g); });
+    }
+  constexpr auto list = kt_list<N, M>();
+  for (int k = 0; k < list.n; ++k)
+    append_frag<M>(ktw, [&](int n, int g, int j) {
+      return K(list.e[k], mode(list.s[k], g, j), 16 * list.t[k] + n);
+    });
+  for (int c = 0; c < NCH; ++c)
+    for (int s = 0; s < (X3 ? 2 : 16); ++s)
+      for (int t = 0; t < ProjTiles<N>::MTP; ++t)
+        append_frag<M>(pw, [&](int n, int g, int j) {
+          const int q = 64 * c + (X3 ? 32 * s + 8 * g + j : 16 * (s / 4) + 4 * g + s % 4);
+          return Pw(mperm<N, M>(t, n), q);
+        });
+  for (int c = 0; c < NCH; ++c)
+    for (int k = 0; k < ProjTiles<N>::LEFT; ++k)
+      for (int q = 0; q < 64; ++q) pl.push_back((T)Pw(16 * ProjTiles<N>::MTP + k, 64 * c + q));
+  const std::vector<std::vector<double>> fm = face_modes(r);
+  for (int ff = 0; ff < 24; ++ff) {
+    const double* F = &r.F[(size_t)ff * Ns * L];
+    // lift of face mode m: sum_i beta_i psi_m(eta_i) phi_l(x_i)
+    auto R = [&](int l, int m) {
+      if (l >= L || m >= NM2) return 0.0;
+      double s = 0.0;
+      for (int i = 0; i < Ns; ++i) s += r.beta[i] * fm[m][i] * F[i * L + l];
+      return s;
+    };
+    for (int t = 0; t < MT; ++t) {
+      if constexpr (X3) {
+        uint16_t v[3][64][4];
+        for (int lane = 0; lane < 64; ++lane)
+          for (int j = 0; j < 4; ++j) {
+            float x = (float)R(16 * t + (lane & 15), 4 * (lane >> 4) + j);
+            for (int k = 0; k < 3; ++k) {
+              v[k][lane][j] = bf16_bits(x);
+              x -= bf16_value(v[k][lane][j]);
+            }
+          }
+        rw.insert(rw.end(), (const char*)v, (const char*)v + sizeof v);
+      } else {
+        for (int s = 0; s < (NM2 + 3) / 4; ++s)
+          append_frag<M>(rw, [&](int n, int g, int) { return R(16 * t + n, 4 * s + g); });
+      }
+    }
+    for (int t = 0; t < NST; ++t)
+      for (int s = 0; s < (L + 3) / 4; ++s)
+        tail(fs, [&](int n, int g) {
+          const int i = 16 * t + n, l = 4 * s + g;
+          return (i < Ns && l < L) ? F[i * L + l] : 0.0;
+        });
   }
-  std::vector<typename HostAF<PA>::type> px;
-  for (int c = 0; c < DM::NCH; ++c)
-    for (int t = 0; t < MT; ++t)
-      for (int s = 0; s < 16; ++s)
-        for (int lane = 0; lane < 64; ++lane) {
-          const int l = 16 * t + mperm<PA>(lane & 15);
-          const int q = 64 * c + 16 * (s / 4) + 4 * (lane >> 4) + s % 4;
-          px.push_back((typename HostAF<PA>::type)((l < L && q < Q) ? r.Pw[(size_t)l * Q + q] : 0.0));
-        }
-  std::vector<T> ps((size_t)Q4 * L * 4, T(0));
+  for (int s = 0; s < (Ns + 3) / 4; ++s)
+    tail(psi, [&](int n, int g) {
+      const int i = 4 * s + g;
+      return (n < NM2 && i < Ns) ? r.beta[i] * fm[n][i] : 0.0;
+    });
   for (int q = 0; q < Q; ++q)
     for (int l = 0; l < L; ++l) ps[((size_t)(q / 4) * L + l) * 4 + q % 4] = (T)r.Pw[(size_t)l * Q + q];
   // quantity mixing: lane (g, n) holds row p = qperm(n), column j = 4 i + g of
@@ -401,10 +503,13 @@ dgd_status build_step_packs(dgd_handle* h) {
         }
       }
   dgd_status st;
-  if ((st = upload(h, h->Kck, kc)) || (st = upload(h, h->Ktl, kt)) || (st = upload(h, h->PXpk, px)) ||
-      (st = upload(h, h->Psrc, ps)) || (st = upload(h, h->mixP, mp)) || (st = upload(h, h->mixV, mv)))
+  if ((st = upload(h, h->Vw, vw)) || (st = upload(h, h->Vt, vt)) || (st = upload(h, h->Kw, kw)) ||
+      (st = upload(h, h->Kt, kt)) || (st = upload(h, h->Ktw, ktw)) || (st = upload(h, h->PXw, pw)) ||
+      (st = upload(h, h->PXleft, pl)) || (st = upload(h, h->Rw, rw)) || (st = upload(h, h->Fst, fs)) ||
+      (st = upload(h, h->Psi, psi)) || (st = upload(h, h->Psrc, ps)) || (st = upload(h, h->mixP, mp)) ||
+      (st = upload(h, h->mixV, mv)))
     return st;
-  h->dz_elem = (size_t)Deriv<N, P>::NF * 64 * sizeof(AF);
+  h->dz_elem = (size_t)Deriv<N>::NF * 64 * sizeof(T);
   return DGD_OK;
 }
 
@@ -437,11 +542,20 @@ void timed(dgd_handle* h, int k, F launch) {
   h->ev_used.push_back({k, {a, b}});
 }
 
+// Precision the Cauchy-Kovalevskaya step runs in: split-BF16 handles take the FP32
+// kernels, whose contractions are three-way split BF16 products from degree 3 on
+// (the same state, FP32 with FP64 damage).
+template <int P> struct StepPrec {
+  static constexpr int value = P == PREC_BF16 ? PREC_F32 : P;
+};
+
 // the step and the times of its time points
 template <int P> void set_dt(StepArgs<P>& a, double dt) {
   using T = typename Prec<P>::T;
   a.dt = dt;
   for (int z = 0; z < 8; ++z) a.hz[z] = a.tau[z] * (T)dt;
+  for (int z = 0; z < 5; ++z)
+    for (int i = 0; i < 4; ++i) a.hzi[z][i] = a.hz[z] * T(1.0 / (i + 1));
   // (the rule's weights sum to 1 and it integrates the powers up to N exactly)
   double f = 1.0;
   for (int i = 0; i < 8; ++i) {
@@ -489,10 +603,17 @@ StepArgs<P> make_args(dgd_handle* h) {
   a.ecl = nullptr;
   a.lts_c = -1;
   a.facc = nullptr;
-  a.Dz = (AF*)h->Dz.p;
-  a.Kck = (const AF*)h->Kck.p;
-  a.Ktl = (const typename Prec<Accurate<P>::value>::AF*)h->Ktl.p;
-  a.PXpk = (const typename Prec<Accurate<P>::value>::AF*)h->PXpk.p;
+  a.Dz = (T*)h->Dz.p;
+  a.Vw = h->Vw.p;
+  a.Vt = (const T*)h->Vt.p;
+  a.Kw = h->Kw.p;
+  a.Kt = (const T*)h->Kt.p;
+  a.Ktw = h->Ktw.p;
+  a.PXw = h->PXw.p;
+  a.PXleft = (const T*)h->PXleft.p;
+  a.Rw = h->Rw.p;
+  a.Fst = (const T*)h->Fst.p;
+  a.Psi = (const T*)h->Psi.p;
   a.Psrc = (const T*)h->Psrc.p;
   a.mixP = (const int*)h->mixP.p;
   a.mixV = (const T*)h->mixV.p;
@@ -500,11 +621,20 @@ StepArgs<P> make_args(dgd_handle* h) {
   return a;
 }
 
+// workgroups of a launch over n elements: one per element, or, where a workgroup
+// keeps the reference matrices in LDS and walks over elements, one per compute
+// unit (fewer when its first wavefronts alone cover the elements)
+dim3 element_grid(const dgd_handle* h, long long n, int wpb) {
+  const long long all = (n + 7) / 8;
+  return dim3((unsigned)(8 * (wpb == 1 ? all : std::min<long long>(all, (h->ncu + 7) / 8))));
+}
+
 template <int N, int P, class LW>
 void launch_ck(dgd_handle* h, const StepArgs<P>& a) {
   const long long n = a.elist ? a.nlist : a.E;
+  using TB = CkTabs<N, P>;
   timed(h, 0, [&] {
-    hipLaunchKernelGGL((k_ck<N, P, LW>), dim3((unsigned)(8 * ((n + 7) / 8))), dim3(64), 0,
+    hipLaunchKernelGGL((k_ck<N, P, LW>), element_grid(h, n, TB::wpb), dim3(64 * TB::wpb), 0,
                        h->stream, a);
   });
 }
@@ -522,9 +652,11 @@ void launch_face(dgd_handle* h, const StepArgs<P>& a, long long n, const int* li
 template <int N, int P, class LW>
 void launch_update(dgd_handle* h, const StepArgs<P>& a) {
   const long long n = a.elist ? a.nlist : a.E;
+  using TB = UpdTabs<N, P>;
   timed(h, 9, [&] {
-    hipLaunchKernelGGL((k_update<N, P, LW>), dim3((unsigned)(8 * ((n + 7) / 8))), dim3(64), 0,
-                       h->stream, a, (const int*)h->fmap.p, (const typename Prec<P>::T*)h->fflux.p);
+    hipLaunchKernelGGL((k_update<N, P, LW>), element_grid(h, n, TB::wpb), dim3(64 * TB::wpb),
+                       0, h->stream, a, (const int*)h->fmap.p,
+                       (const typename Prec<P>::T*)h->fflux.p);
   });
 }
 
@@ -566,19 +698,21 @@ dgd_status step_impl(dgd_handle* h, long long nsteps) {
   using T = typename Prec<P>::T;
   const bool ivm = h->law == 1;
   for (long long it = 0; it < nsteps; ++it) {
-    const StepArgs<P> a = make_args<N, P>(h);
     h->points_in_uz = h->predictor == 1;
     h->points_dt = h->dt;
     if (h->predictor == 1) {
+      const StepArgs<P> a = make_args<N, P>(h);
       if (ivm)
         picard_step<N, P, IvmLaw>(h, a);
       else
         picard_step<N, P, CdmLaw>(h, a);
     } else {
+      constexpr int SP = StepPrec<P>::value;
+      const StepArgs<SP> a = make_args<N, SP>(h);
       if (ivm)
-        ck_step<N, P, IvmStep>(h, a);
+        ck_step<N, SP, IvmStep>(h, a);
       else
-        ck_step<N, P, CdmStep>(h, a);
+        ck_step<N, SP, CdmStep>(h, a);
     }
     if (h->nsrc > 0) {
       SrcArgs s;
@@ -647,9 +781,10 @@ dgd_status lts_advance(dgd_handle* h, int c, double t) {
   for (int k = 0; k < 8; ++k) offs.v[k] = k < h->nclusters ? t - h->lts_tp[k] : 0.0;
   if (h->n_fl[c] > 0) launch_face<N, P, LW>(h, a, h->n_fl[c], (const int*)h->lts_fl[c].p, offs);
   if (h->n_acc[c] > 0) {
-    const long long n = h->n_acc[c] * h->ref.Ns * 10;
+    constexpr int NM2 = FaceModes<N>::value;
+    const long long n = h->n_acc[c] * NM2 * 10;
     hipLaunchKernelGGL((k_face_accumulate<T>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0,
-                       h->stream, h->n_acc[c], (const int*)h->lts_acc[c].p, h->ref.Ns, dtc,
+                       h->stream, h->n_acc[c], (const int*)h->lts_acc[c].p, NM2, dtc,
                        (const T*)h->fflux.p, (T*)h->facc.p);
   }
   // faces, volume and source terms and the update, in place
@@ -689,8 +824,9 @@ template <int N, int P> struct LtsFn {
     h->points_in_uz = false;
     const double mdt = h->lts_dt0 * (double)(1LL << (h->nclusters - 1));
     for (long long k = 0; k < nmacro; ++k) {
-      dgd_status s = h->law == 1 ? lts_advance<N, P, IvmStep>(h, h->nclusters - 1, h->t)
-                                 : lts_advance<N, P, CdmStep>(h, h->nclusters - 1, h->t);
+      constexpr int SP = StepPrec<P>::value;
+      dgd_status s = h->law == 1 ? lts_advance<N, SP, IvmStep>(h, h->nclusters - 1, h->t)
+                                 : lts_advance<N, SP, CdmStep>(h, h->nclusters - 1, h->t);
       if (s) return s;
       h->t += mdt;
       if (h->nrec > 0) {
@@ -723,7 +859,7 @@ dgd_status dispatch(dgd_handle* h, Args... args) {
 template <int N, int P> struct BuildFn {
   static dgd_status run(dgd_handle* h) {
     const dgd_status s = build_packed<N, P>(h);
-    return s ? s : build_step_packs<N, P>(h);
+    return s ? s : build_step_packs<N, StepPrec<P>::value>(h);
   }
 };
 template <int N, int P> struct StepFn {
@@ -744,9 +880,10 @@ template <int N, int P> struct PredictFn {
 
 template <int N, int P> struct TimePointsFn {
   static dgd_status run(dgd_handle* h, double* out) {
-    StepArgs<P> a = make_args<N, P>(h);
-    set_dt<P>(a, h->points_dt);
-    hipLaunchKernelGGL((k_time_points<N, P>), dim3((unsigned)h->ne), dim3(64), 0, h->stream, a, out);
+    constexpr int SP = StepPrec<P>::value;
+    StepArgs<SP> a = make_args<N, SP>(h);
+    set_dt<SP>(a, h->points_dt);
+    hipLaunchKernelGGL((k_time_points<N, SP>), dim3((unsigned)h->ne), dim3(64), 0, h->stream, a, out);
     HIPCHK(h, hipGetLastError());
     return DGD_OK;
   }
@@ -1101,6 +1238,7 @@ dgd_status dgd_create(int N, int precision, void* hip_stream, dgd_handle** out) 
   h->stream = (hipStream_t)hip_stream;
   h->tsize = precision == DGD_FP64 ? 8 : 4;
   if (hipGetDevice(&h->device) != hipSuccess ||
+      hipDeviceGetAttribute(&h->ncu, hipDeviceAttributeMultiprocessorCount, h->device) != hipSuccess ||
       scratch_address(h->device, &h->noalloc_part) != hipSuccess) {
     delete h;
     return DGD_EDEVICE;

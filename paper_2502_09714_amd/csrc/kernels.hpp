@@ -86,15 +86,25 @@ template <int P> struct StepArgs {
   const signed char* ecl;
   int lts_c;
   T* facc;
-  // Cauchy-Kovalevskaya step (step_kernels.hpp)
-  AF* Dz;               // [E][fragments][64] time derivatives of the prediction
-  const AF* Kck;        // K^e, rows in accumulator order [e][tile][kstep]
-  const typename Prec<Accurate<P>::value>::AF* Ktl;    // transposed K^e [e][tile][kstep]
-  const typename Prec<Accurate<P>::value>::AF* PXpk;   // Pw per chunk, k order of the point integrals
+  // Cauchy-Kovalevskaya step (step_kernels.hpp): time derivatives of the
+  // prediction [E][fragments][64] and the packed operators, wide fragments (w)
+  // and the FP32 steps of leftover rows (t) apart
+  T* Dz;
+  const void* Vw;       // nodal evaluation [chunk][16-point tile][step]
+  const T* Vt;
+  const void* Kw;       // K^e [e][tile][step]
+  const T* Kt;
+  const void* Ktw;      // transposed K^e, in the order of kt_list
+  const void* PXw;      // projection of the point integrals
+  const T* PXleft;      // its last modes [chunk][mode][64]
+  const void* Rw;       // lift of the face modes [face][permutation][tile]
+  const T* Fst;         // face traces [face][permutation][tile][step]
+  const T* Psi;         // projection of point fluxes on the face modes [step]
   const T* Psrc;        // Pw as [point / 4][mode][4]
   const int* mixP;      // [3][3][64] which averaged-tangent entry a lane's A*_e entry takes
   const T* mixV;        // [3][3][64] its weight in the volume term
   T hz[8];              // tau_z dt
+  T hzi[5][4];          // tau_z dt / (i + 1)
   T wint[8];            // sum_z gamma_z hz^i / i!
 };
 

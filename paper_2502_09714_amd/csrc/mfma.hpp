@@ -46,6 +46,7 @@ namespace dgd {
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef short bf16x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 // high and low BF16 parts of four FP32 values (one matrix-core fragment)
 struct __attribute__((aligned(16))) bf16s {
@@ -71,7 +72,7 @@ __device__ inline bf16s split4(float x0, float x1, float x2, float x3) {
   return r;
 }
 
-enum { PREC_F64 = 0, PREC_F32 = 1, PREC_BF16 = 2 };
+enum { PREC_F64 = 0, PREC_F32 = 1, PREC_BF16 = 2, PREC_X3 = 3 };
 
 __host__ __device__ inline uint16_t f32_to_bf16(float x) {
   // round to nearest even (inputs are finite)
@@ -152,6 +153,64 @@ template <> struct Prec<PREC_BF16> {
     const bool on = (lane & 15) == 9;
     return split4(on ? v[k0] : 0.0f, on ? v[k0 + 1] : 0.0f, on ? v[k0 + 2] : 0.0f,
                   on ? v[k0 + 3] : 0.0f);
+  }
+};
+
+// FP32 values as three BF16 parts, x = h + m + l (8 significant bits each, exact
+// while x is above 2^-110), for v_mfma_f32_16x16x32_bf16.  The lane's eight
+// entries of a 32-term step are k = 16 (j / 4) + 4 (lane / 16) + j % 4: two
+// 16-row accumulator tiles one after the other.
+struct bf16t {
+  bf16x8 h, m, l;
+};
+
+// Seven instructions per pair: the part taken off is subtracted by the BF16 dot
+// product, without unpacking it.  (The selectors are opaque: as literals they
+// become the inline constant -1.0, which fills the high half of the pair.)
+__device__ inline bf16t split8(const float* x) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  unsigned u0 = 0xbf80u, u1 = 0xbf800000u;      // (-1, 0), (0, -1)
+  asm("" : "+s"(u0));
+  asm("" : "+s"(u1));
+  const bf16x2 c0 = __builtin_bit_cast(bf16x2, u0), c1 = __builtin_bit_cast(bf16x2, u1);
+  bf16t r;
+#pragma unroll
+  for (int j = 0; j < 8; j += 2) {
+    f32x2 d = {x[j], x[j + 1]};
+    const bf16x2 h = __builtin_convertvector(d, bf16x2);
+    d = {__builtin_amdgcn_fdot2_f32_bf16(h, c0, x[j], false),
+         __builtin_amdgcn_fdot2_f32_bf16(h, c1, x[j + 1], false)};
+    const bf16x2 m = __builtin_convertvector(d, bf16x2);
+    d = {__builtin_amdgcn_fdot2_f32_bf16(m, c0, d[0], false),
+         __builtin_amdgcn_fdot2_f32_bf16(m, c1, d[1], false)};
+    const bf16x2 l = __builtin_convertvector(d, bf16x2);
+    r.h[j] = h[0];
+    r.h[j + 1] = h[1];
+    r.m[j] = m[0];
+    r.m[j + 1] = m[1];
+    r.l[j] = l[0];
+    r.l[j + 1] = l[1];
+  }
+  return r;
+}
+
+template <> struct Prec<PREC_X3> {
+  using T = float;
+  using Acc = f32x4;
+  using AF = bf16t;
+  static constexpr int KS = 32;
+  __device__ static inline int crow(int lane, int i) { return 4 * (lane >> 4) + i; }
+  // products in the order of growing weight: l h, h l, m m, m h, h m, h h
+  __device__ static inline Acc product(int q, const AF& a, const AF& b, Acc c) {
+    const bf16x8& x = q == 0 ? a.l : (q == 2 || q == 3 ? a.m : a.h);
+    const bf16x8& y = q == 1 ? b.l : (q == 2 || q == 4 ? b.m : b.h);
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, y, c, 0, 0, 0);
+  }
+  __device__ static inline Acc mma(const AF& a, const AF& b, Acc c) {
+#pragma unroll
+    for (int q = 0; q < 6; ++q) c = product(q, a, b, c);
+    return c;
   }
 };
 

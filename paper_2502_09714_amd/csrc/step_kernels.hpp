@@ -28,28 +28,50 @@ __host__ __device__ constexpr int mode_degree(int l) {
   return d;
 }
 
-// Wavefronts per SIMD the kernels are compiled for, and how many fragments ahead
-// of their use they request the reference matrices.
-template <int N, int P> struct StepTune {
-  static constexpr int w_ck = P == PREC_F64 ? 2 : 4, w_face = P == PREC_F64 ? 2 : 4,
-                       w_update = 2;
-  static constexpr int pd_ck = 4, pd_face = 6, pd_update = P == PREC_F64 ? 4 : 10;
+// Form of the reference-matrix contractions of a step.
+// FP64 products and FP32 16x16x4 products run on the vector ALUs (measured: a
+// stream of them and a stream of vector FMAs on one SIMD take the sum of their
+// times); the BF16 matrix cores run beside them.  From degree 3 on the FP32 and
+// split-BF16 handles therefore contract on the BF16 matrix cores with three-way
+// split operands (Prec<PREC_X3>): x = h + m + l exactly, and the six products of
+// weight >= 2^-18, 2^-27 of |a||b| and less left out: not less accurate than FP32
+// products (their sums round once per 32 terms).  A 32-term step costs 96 cycles
+// of the matrix cores where eight FP32 steps cost 256 cycles of the vector ALUs.
+// Below degree 3 a contraction has 4 or 10 terms and FP32 steps are shorter.
+template <int N, int P> struct MatForm {
+  static constexpr int value = P == PREC_F32 && N >= 3 ? PREC_X3 : P;
+};
+
+// Steps of a contraction over R rows: WIDE fragments of Prec<M>::KS rows each,
+// and in the three-way form, where 1..4 rows are left over, one FP32 step (TAIL).
+// NREG: registers per lane of an operand.
+template <int M, int R> struct Steps {
+  static constexpr bool TAIL = M == PREC_X3 && R % 32 > 0 && R % 32 <= 4;
+  static constexpr int KS = Prec<M>::KS;
+  static constexpr int WIDE = TAIL ? R / 32 : (R + KS - 1) / KS;
+  static constexpr int NREG = M == PREC_X3 ? 8 * WIDE + TAIL : WIDE;
+  // row held by operand register r of lane group g
+  __host__ __device__ static constexpr int row(int r, int g) {
+    if (M != PREC_X3) return 4 * r + g;
+    return r < 8 * WIDE ? 16 * (r >> 2) + 4 * g + (r & 3) : 32 * WIDE + g;
+  }
+  // wide step s holds rows < hi(s) and >= lo(s)
+  __host__ __device__ static constexpr int lo(int s) { return KS * s; }
+  __host__ __device__ static constexpr int hi(int s) { return KS * (s + 1); }
 };
 
 // Column j of the derivative matrix: 0..9 D^0; 10 the damage row of D^1;
 // 11..19 its wave rows; 20 + 9 (i-2) + p: D^i, i >= 2.
-// Stored as matrix-core fragments, [element][fragment][lane]: 16-column tile c
-// keeps steps(c) k-steps from fragment frag0(c) on; lane (g, n) = (lane / 16,
-// lane % 16) holds column 16 c + n at row 4 s + g (rows 16 s + 4 g + 0..3, split
-// into BF16 pairs, in the split-BF16 form).
-template <int N, int P> struct Deriv {
-  static constexpr int KS = Prec<P>::KS;
+// Stored as fragments of four rows, [element][fragment][lane]: 16-column tile c
+// keeps steps(c) of them from fragment frag0(c) on; lane (g, n) = (lane / 16,
+// lane % 16) holds column 16 c + n at row 4 s + g.
+template <int N> struct Deriv {
   static constexpr int NC = 20 + 9 * (N - 1);
   static constexpr int NT = (NC + 15) / 16;
   __host__ __device__ static constexpr int rows(int j) {
     return j <= 10 ? Dims<N>::L : (j < 20 ? modes_upto(N - 1) : modes_upto(N + 1 - (2 + (j - 20) / 9)));
   }
-  __host__ __device__ static constexpr int steps(int c) { return (rows(16 * c) + KS - 1) / KS; }
+  __host__ __device__ static constexpr int steps(int c) { return (rows(16 * c) + 3) / 4; }
   __host__ __device__ static constexpr int frag0(int c) {
     int f = 0;
     for (int k = 0; k < c; ++k) f += steps(k);
@@ -60,32 +82,92 @@ template <int N, int P> struct Deriv {
   __host__ __device__ static constexpr int col(int i, int p) {
     return i == 0 ? p : (i == 1 ? (p == 9 ? 10 : 11 + p) : 20 + 9 * (i - 2) + p);
   }
+  // first fragment of the tile of column j (j not a compile-time constant)
+  __device__ static int tile0(int j) {
+    const int c = j >> 4;
+    return c == 0 ? 0 : (c == 1 ? frag0(1) : frag0(NT > 2 ? 2 : 1));
+  }
 };
+
+// Launch shapes.  From degree 3 on, k_ck and k_update keep the reference matrices
+// in LDS: one workgroup of wpb_* wavefronts per compute unit copies them once and
+// walks over elements (read from L2 instead, 67 KB per element at degree 4 missed
+// the 32 KB L1 and the wavefronts waited on its pending lines for 60 % of the
+// time).  Below degree 3 they fit the L1 and a wavefront takes one element.
+// pd_*: how many fragments ahead of their use they are requested.
+template <int N, int P> struct StepTune {
+  static constexpr bool stage_ck = N >= 3, stage_update = N >= 3 && P != PREC_F64;
+  static constexpr int wpb_ck = !stage_ck ? 1 : (P == PREC_F64 ? 8 : 16);
+  static constexpr int wpb_update = !stage_update ? 1 : (N >= 4 ? 8 : 16);
+  static constexpr int w_ck = P == PREC_F64 ? 2 : 4, w_face = P == PREC_F64 ? 2 : 4,
+                       w_update = stage_update ? wpb_update / 4 : (P == PREC_F64 && N >= 4 ? 1 : 2);
+  static constexpr int pd_ck = 4, pd_face = 6, pd_update = 4;
+};
+
+// this wavefront's elements: each XCD (block index mod 8) walks a contiguous range.
+// The lane index is made opaque per element: what depends on it alone (table
+// addresses, mixing weights) would else be kept in registers over the whole walk
+// and spill.
+template <int P, class F>
+__device__ inline void for_elements(const StepArgs<P>& a, int wpb, F body) {
+  const long long n = a.elist ? a.nlist : a.E, per = (n + 7) / 8;
+  const long long x = blockIdx.x & 7, b = blockIdx.x >> 3, nb = gridDim.x >> 3;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  for (long long i = b + nb * wave; i < per; i += nb * wpb) {
+    const long long k = x * per + i;
+    if (k >= n) break;
+    int lane = threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));
+    body(a.elist ? (long long)a.elist[k] : k, lane & 63);   // (& 63: offsets fold into the loads)
+  }
+}
+
+// copy of bytes (a multiple of 16) to LDS by the whole workgroup
+__device__ inline void stage(void* dst, const void* src, int bytes) {
+  typedef float V4 __attribute__((ext_vector_type(4)));
+  for (int i = threadIdx.x; i < bytes / 16; i += blockDim.x) ((V4*)dst)[i] = ((const V4*)src)[i];
+}
 
 // Orders in which lanes and accumulator rows stand for quantities and modes.
 // A product's output row r sits in lane group g, register i with r = 4 g + i
 // (FP32 accumulators) or g + 4 i (FP64).  Operand rows fed in the order qperm /
-// mperm come out with quantity 4 i + g, and mode 16 t + 4 i + g (FP64, FP32) or
-// 16 t + 4 g + i (split BF16), in register i of tile t: just the k order of the
-// next product's operand, which then needs no data movement.
+// mperm come out with quantity 4 i + g, and with the modes of Steps::row, in the
+// registers: just the k order of the next product's operand, which then needs no
+// data movement.
 template <class T> __host__ __device__ constexpr int qperm(int n) {
   return sizeof(T) == 8 ? n : (n & 3) * 4 + (n >> 2);
 }
-template <int P> __host__ __device__ constexpr int mperm(int n) {
-  return P == PREC_F32 ? (n & 3) * 4 + (n >> 2) : n;
+// mode of row (or column) n of 16-mode tile t
+template <int N, int M> __host__ __device__ constexpr int mperm(int t, int n) {
+  return 16 * t + (M == PREC_F32 || (M == PREC_X3 && t >= 2 * Steps<M, Dims<N>::L>::WIDE)
+                       ? (n & 3) * 4 + (n >> 2)
+                       : n);
 }
-// mode held by register r (= 4 t + i) of lane group g
-template <int P> __device__ inline int reg_mode(int r, int g) {
-  return P == PREC_BF16 ? 16 * (r >> 2) + 4 * g + (r & 3) : 4 * r + g;
+// mode in register i of tile t of lane group g
+template <int N, int M> __device__ inline int acc_mode(int t, int i, int g) {
+  return M == PREC_X3 && t < 2 * Steps<M, Dims<N>::L>::WIDE ? 16 * t + 4 * g + i : 16 * t + 4 * i + g;
 }
-// operand of k-step s from registers in that order
-template <int P, class T> __device__ inline typename Prec<P>::AF mode_op(const T* m, int s) {
-  if constexpr (P == PREC_BF16)
-    return split4(m[4 * s], m[4 * s + 1], m[4 * s + 2], m[4 * s + 3]);
+// operand of wide step s from registers in the order of Steps::row
+template <int M, class T> __device__ inline typename Prec<M>::AF wide_op(const T* m, int s) {
+  if constexpr (M == PREC_X3)
+    return split8(m + 8 * s);
   else
     return m[s];
 }
-
+// fragment f of a packed matrix: one value per lane, or the three parts of a
+// split fragment one after the other
+template <int M>
+__device__ inline typename Prec<M>::AF load_frag(const void* tab, int f, int lane) {
+  if constexpr (M == PREC_X3) {
+    const bf16x8* p = (const bf16x8*)tab + f * 192 + lane;
+    return {p[0], p[64], p[128]};
+  } else {
+    return ((const typename Prec<M>::AF*)tab)[f * 64 + lane];
+  }
+}
+template <int M> struct FragBytes {
+  static constexpr int value = M == PREC_X3 ? 3072 : 64 * (int)sizeof(typename Prec<M>::AF);
+};
 // LDS written by one lane of the wavefront and read by another: the LDS unit
 // serves a wavefront's accesses in order, so only the compiler must keep them so.
 __device__ inline void wave_sync() {
@@ -171,19 +253,20 @@ template <int M, class T> __device__ inline void reduce_to_lds(const T (&x)[M], 
 }
 
 // Products with K^e (mode l' of the result needs modes of higher degree only)
-// or its transpose (of lower degree only): the (e, tile, k-step) triples that
+// or its transpose (of lower degree only): the (e, tile, wide step) triples that
 // are not zero, in the order they are issued.
 template <int NMAX> struct TripleList {
   int n = 0;
   unsigned char e[NMAX] = {}, t[NMAX] = {}, s[NMAX] = {};
 };
-// K^e: inputs of KIN k-steps, NTO result tiles
-template <int N, int P, int KIN, int NTO> constexpr TripleList<3 * KIN * NTO> k_list() {
-  TripleList<3 * KIN * NTO> r;
-  for (int s = 0; s < KIN; ++s)
-    for (int e = 0; e < 3; ++e)
-      for (int t = 0; t < NTO; ++t)
-        if ((s + 1) * Prec<P>::KS > modes_upto(mode_degree(16 * t))) {
+// K^e: inputs of R modes, NTO result tiles
+template <int N, int M, int R, int NTO> constexpr auto k_list() {
+  using ST = Steps<M, R>;
+  TripleList<3 * (ST::WIDE + 1) * NTO> r;
+  for (int s = 0; s < ST::WIDE; ++s)
+    for (int t = 0; t < NTO; ++t)
+      for (int e = 0; e < 3; ++e)
+        if (ST::hi(s) > modes_upto(mode_degree(16 * t))) {
           r.e[r.n] = (unsigned char)e;
           r.t[r.n] = (unsigned char)t;
           r.s[r.n++] = (unsigned char)s;
@@ -191,19 +274,20 @@ template <int N, int P, int KIN, int NTO> constexpr TripleList<3 * KIN * NTO> k_
   return r;
 }
 // transposed: all MT result tiles, inputs of degree <= (largest of the tile) - 1
-template <int N, int P> constexpr TripleList<3 * 16 * 3> kt_list() {
-  TripleList<3 * 16 * 3> r;
-  constexpr int KS = Prec<P>::KS, L = Dims<N>::L;
-  for (int s = 0; KS * s < modes_upto(N - 1); ++s)
-    for (int e = 0; e < 3; ++e)
-      for (int t = 0; t < Dims<N>::MT; ++t) {
-        const int last = 16 * t + 15 < L ? 16 * t + 15 : L - 1;
-        if (KS * s < modes_upto(mode_degree(last) - 1)) {
+template <int N, int M> constexpr auto kt_list() {
+  using ST = Steps<M, modes_upto(N - 1)>;
+  TripleList<3 * (ST::WIDE + 1) * 3> r;
+  constexpr int L = Dims<N>::L;
+  for (int s = 0; s < ST::WIDE; ++s)
+    for (int t = 0; t < Dims<N>::MT; ++t) {
+      const int last = 16 * t + 15 < L ? 16 * t + 15 : L - 1;
+      for (int e = 0; e < 3; ++e)
+        if (ST::lo(s) < modes_upto(mode_degree(last) - 1)) {
           r.e[r.n] = (unsigned char)e;
           r.t[r.n] = (unsigned char)t;
           r.s[r.n++] = (unsigned char)s;
         }
-      }
+    }
   return r;
 }
 
@@ -224,11 +308,10 @@ __device__ inline void stream(Ld ld, Use use) {
 
 template <int N, int P> struct CkLDS {
   using T = typename Prec<P>::T;
-  static constexpr int W = P == PREC_BF16 ? 4 : 1;      // values per fragment entry
-  alignas(16) T dz[Deriv<N, P>::NF * 64 * W];
+  alignas(16) T dz[Deriv<N>::NF * 64];
   alignas(16) T r[Dims<N>::NCH * 64];                   // damage rate at the points
   T al[64];                                             // its projection, the damage row of D^1
-  T ext[64];                                            // sums of the tangent, then mixing weights
+  T ext[64];                                            // sums of the tangent
   T tg[48];                                             // cell-averaged tangent / rho, 0, 1/2, 1
 };
 
@@ -243,23 +326,23 @@ template <int N, int P> struct CkLDS {
 // accumulators of one product are the operand of the next, and the order of
 // D changes from quantities-in-lanes to quantities-in-registers and back.
 template <int N, int P, class LW>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(StepTune<N, P>::w_ck))) void k_ck(StepArgs<P> a) {
-  using PR = Prec<P>;
-  using T = typename PR::T;
+__device__ inline void ck_element(const StepArgs<P>& a, long long e, CkLDS<N, P>& S,
+                                  const void* Vw, const typename Prec<P>::T* Vt, const void* Kw,
+                                  const typename Prec<P>::T* Kt, int lane) {
+  constexpr int M = MatForm<N, P>::value;
+  using PR = Prec<M>;
+  using PA = Prec<P>;
+  using T = typename PA::T;
   using AF = typename PR::AF;
   using Acc = typename PR::Acc;
-  constexpr int PA_ = Accurate<P>::value;
-  using PA = Prec<PA_>;
   using DM = Dims<N>;
-  using DV = Deriv<N, P>;
+  using DV = Deriv<N>;
   constexpr int L = DM::L, Q = DM::Q, NCH = DM::NCH, MT = DM::MT;
-  constexpr int KS = PR::KS, KSL = round_up(L, KS) / KS, NR = P == PREC_BF16 ? 4 * KSL : KSL;
-  constexpr int W = CkLDS<N, P>::W, PD = StepTune<N, P>::pd_ck;
-  __shared__ CkLDS<N, P> S;
-
-  const int lane = threadIdx.x, n = lane & 15, g = lane >> 4;
-  const long long e = elem_index(a);
-  if (e < 0) return;
+  using SL = Steps<M, L>;
+  constexpr int WL = SL::WIDE, NR = SL::NREG, PD = M == PREC_X3 ? 1 : StepTune<N, P>::pd_ck;
+  constexpr int R1 = modes_upto(N - 1), R3 = modes_upto(N - 2), R4 = modes_upto(N - 3);
+  constexpr int NT1 = (R1 + 15) / 16;
+  const int n = lane & 15, g = lane >> 4;
   const int p = qperm<T>(n);
 
   // D^0 as the row operand: quantity p in lane n, modes in registers
@@ -268,41 +351,41 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(StepTune<N, 
     const T* u = a.U9 + (e * 9 + (p < 9 ? p : 8)) * L;
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
-      const int l = reg_mode<P>(r, g);
+      const int l = SL::row(r, g);
       d0[r] = u[l < L ? l : L - 1];
     }
     if (p == 9) {
       const double* ua = a.Ua + e * L;
 #pragma unroll
       for (int r = 0; r < NR; ++r) {
-        const int l = reg_mode<P>(r, g);
+        const int l = SL::row(r, g);
         d0[r] = (T)ua[l < L ? l : L - 1];
       }
     }
 #pragma unroll
     for (int r = 0; r < NR; ++r)
-      if (p > 9 || reg_mode<P>(r, g) >= L) d0[r] = T(0);
+      if (p > 9 || SL::row(r, g) >= L) d0[r] = T(0);
   }
   const Law<T> law{a.amax, a.smin};
-  const MatP<T> mt = load_mat<T>(a.mat + e * 8);
-  const StepMat<T> m = LW::constants(mt);
-  T J[9];
-#pragma unroll
-  for (int k = 0; k < 9; ++k) J[k] = (T)a.geo[e * 16 + k];
-  for (int i = lane; i < DV::NF * 64 * W; i += 64) S.dz[i] = T(0);
+  const StepMat<T> m = LW::constants(load_mat<T>(a.mat + e * 8));
+  for (int i = lane; i < DV::NF * 16; i += 64) {
+    typedef T T4 __attribute__((ext_vector_type(4), aligned(16)));
+    ((T4*)S.dz)[i] = T4{T(0), T(0), T(0), T(0)};
+  }
   wave_sync();
-  // place of quantities-in-lanes register r of order i: its lane's base + roff(r)
-  auto roff = [](int r) { return P == PREC_BF16 ? (r >> 2) * 256 + (r & 3) : r * 64; };
-  auto lbase = [&](int i) {
-    const int j = DV::col(i, p), c = j >> 4;
-    const int f0 = c == 0 ? 0 : (c == 1 ? DV::frag0(1) : DV::frag0(DV::NT > 2 ? 2 : 1));
-    return (f0 * 64 + g * 16 + (j & 15)) * W;
+  // place of quantities-in-lanes register (t, i) of order o
+  auto lane_place = [&](int o, int t, int i) {
+    const int j = DV::col(o, p), f0 = DV::tile0(j) * 64 + (j & 15);
+    return M == PREC_X3 && t < 2 * WL ? f0 + g * 64 + t * 256 + i * 16 : f0 + g * 16 + t * 256 + i * 64;
   };
   if (p < 10) {
-    const int b = lbase(0);
 #pragma unroll
-    for (int r = 0; r < NR; ++r) S.dz[b + roff(r)] = d0[r];
+    for (int r = 0; r < NR; ++r)
+      if (SL::row(r, g) < 4 * DV::steps(0)) S.dz[lane_place(0, r >> 2, r & 3)] = d0[r];
   }
+  AF d0w[WL > 0 ? WL : 1];
+#pragma unroll
+  for (int s = 0; s < WL; ++s) d0w[s] = wide_op<M>(d0, s);
 
   // nodal values at t_n: the product's rows are quantities, its columns 16
   // points; a transposition over the lane groups gives every lane one point
@@ -312,12 +395,15 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(StepTune<N, 
 #pragma unroll 1
   for (int c = 0; c < NCH; ++c) {
     Acc C[4];
-    zero_C<P, 4>(C);
-    const AF* V = a.Vpk + (size_t)c * 4 * KSL * 64 + lane;
-    stream<PD, 4 * KSL, AF>([&](int k) { return V[((k % 4) * KSL + k / 4) * 64]; },
-                            [&](int k, const AF& b) {
-                              C[k % 4] = PR::mma(mode_op<P>(d0, k / 4), b, C[k % 4]);
-                            });
+    zero_C<M, 4>(C);
+    stream<PD, 4 * WL, AF>(
+        [&](int k) { return load_frag<M>(Vw, (c * 4 + k % 4) * WL + k / 4, lane); },
+        [&](int k, const AF& b) { C[k % 4] = PR::mma(d0w[k / 4], b, C[k % 4]); });
+    if constexpr (SL::TAIL) {
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        C[t] = PA::mma(d0[NR - 1], Vt[(c * 4 + t) * 64 + lane], C[t]);
+    }
     T u[12];
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
@@ -353,9 +439,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(StepTune<N, 
         const T4 x = pw[k * L], y = rr[k];
         s += x[0] * y[0] + x[1] * y[1] + x[2] * y[2] + x[3] * y[3];
       }
-      const int pos = P == PREC_BF16 ? (((lane >> 4) * 64 + ((lane & 15) >> 2) * 16 + 10) << 2) + (lane & 3)
-                                     : (lane >> 2) * 64 + (lane & 3) * 16 + 10;
-      S.dz[pos] = s;
+      S.dz[(lane >> 2) * 64 + (lane & 3) * 16 + 10] = s;
     }
     S.al[lane] = s;
   }
@@ -369,98 +453,115 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(StepTune<N, 
     for (int d = 0; d < 3; ++d) w[d] = S.tg[a.mixP[(i * 3 + d) * 64 + lane]];
 #pragma unroll
     for (int ee = 0; ee < 3; ++ee)
-      As[ee][i] = J[ee * 3] * w[0] + J[ee * 3 + 1] * w[1] + J[ee * 3 + 2] * w[2];
+      As[ee][i] = (T)a.geo[e * 16 + ee * 3] * w[0] + (T)a.geo[e * 16 + ee * 3 + 1] * w[1] +
+                  (T)a.geo[e * 16 + ee * 3 + 2] * w[2];
   }
 
-  const AF* K = a.Kck + lane;
-  auto kfrag = [&](int ee, int t, int s) { return K[((ee * MT + t) * KSL + s) * 64]; };
-  // contract, then mix: NTO tiles of 16 modes, quantities in rows
-  auto contract_mix = [&](const T* in, auto kin, auto nto, Acc* R) {
-    constexpr int KIN = decltype(kin)::value, NTO = decltype(nto)::value;
-    constexpr auto list = k_list<N, P, KIN, NTO>();
+  auto kfrag = [&](int ee, int t, int s) { return load_frag<M>(Kw, (ee * NT1 + t) * WL + s, lane); };
+  auto ktail = [&](int ee, int t) { return Kt[(ee * NT1 + t) * 64 + lane]; };
+  // contract R modes, then mix: NTO tiles of 16 modes, quantities in rows
+  auto contract_mix = [&](const T* in, const AF* inw, auto rows, auto nto, Acc* out) {
+    constexpr int R = decltype(rows)::value, NTO = decltype(nto)::value;
+    using ST = Steps<M, R>;
+    constexpr auto list = k_list<N, M, R, NTO>();
     Acc Z[3][NTO];
 #pragma unroll
-    for (int ee = 0; ee < 3; ++ee) zero_C<P, NTO>(Z[ee]);
+    for (int ee = 0; ee < 3; ++ee) zero_C<M, NTO>(Z[ee]);
     stream<PD, list.n, AF>([&](int k) { return kfrag(list.e[k], list.t[k], list.s[k]); },
                            [&](int k, const AF& b) {
                              Acc& z = Z[list.e[k]][list.t[k]];
-                             z = PR::mma(mode_op<P>(in, list.s[k]), b, z);
+                             z = PR::mma(inw[list.s[k]], b, z);
                            });
+    if constexpr (ST::TAIL) {
+#pragma unroll
+      for (int ee = 0; ee < 3; ++ee)
+#pragma unroll
+        for (int t = 0; t < NTO; ++t) Z[ee][t] = PA::mma(in[ST::NREG - 1], ktail(ee, t), Z[ee][t]);
+    }
 #pragma unroll
     for (int t = 0; t < NTO; ++t) {
 #pragma unroll
-      for (int k = 0; k < 4; ++k) R[t][k] = 0;
+      for (int k = 0; k < 4; ++k) out[t][k] = 0;
     }
 #pragma unroll
     for (int ee = 0; ee < 3; ++ee)
 #pragma unroll
       for (int i = 0; i < 3; ++i)
 #pragma unroll
-        for (int t = 0; t < NTO; ++t) R[t] = PA::mma(As[ee][i], Z[ee][t][i], R[t]);
+        for (int t = 0; t < NTO; ++t) out[t] = PA::mma(As[ee][i], Z[ee][t][i], out[t]);
   };
-  // mix, then contract: NTI tiles of 16 modes in, NTO out, modes in rows
-  auto mix_contract = [&](const Acc* R, auto kin, auto nto, Acc* C) {
-    constexpr int KIN = decltype(kin)::value, NTO = decltype(nto)::value;
-    constexpr int NTI = (KIN * KS + 15) / 16;
-    constexpr auto list = k_list<N, P, KIN, NTO>();
-    T Y[3][NTI * 4];
+  // mix, then contract R modes: NTO tiles out, modes in rows
+  auto mix_contract = [&](const Acc* in, auto rows, auto nto, Acc* out) {
+    constexpr int R = decltype(rows)::value, NTO = decltype(nto)::value;
+    constexpr int NTI = (R + 15) / 16;
+    using ST = Steps<M, R>;
+    constexpr auto list = k_list<N, M, R, NTO>();
+    constexpr int NY = ST::NREG > 4 * NTI ? ST::NREG : 4 * NTI;
 #pragma unroll
-    for (int t = 0; t < NTI; ++t)
+    for (int t = 0; t < NTO; ++t) {
 #pragma unroll
-      for (int ee = 0; ee < 3; ++ee) {
+      for (int k = 0; k < 4; ++k) out[t][k] = 0;
+    }
+    T Y[3][NY];
+    AF Yw[3][ST::WIDE > 0 ? ST::WIDE : 1];
+#pragma unroll
+    for (int ee = 0; ee < 3; ++ee) {
+#pragma unroll
+      for (int k = 0; k < NY; ++k) Y[ee][k] = T(0);
+#pragma unroll
+      for (int t = 0; t < NTI; ++t) {
         Acc y;
 #pragma unroll
         for (int k = 0; k < 4; ++k) y[k] = 0;
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
           // tiles past the wave rows of order 1 hold the damage row (i = 2) only
-          if (16 * t >= modes_upto(N - 1) && i < 2) continue;
-          y = PA::mma(R[t][i], As[ee][i], y);
+          if (16 * t >= R1 && i < 2) continue;
+          y = PA::mma(in[t][i], As[ee][i], y);
         }
 #pragma unroll
         for (int k = 0; k < 4; ++k) Y[ee][4 * t + k] = y[k];
       }
 #pragma unroll
-    for (int t = 0; t < NTO; ++t) {
-#pragma unroll
-      for (int k = 0; k < 4; ++k) C[t][k] = 0;
+      for (int s = 0; s < ST::WIDE; ++s) Yw[ee][s] = wide_op<M>(Y[ee], s);
     }
     stream<PD, list.n, AF>([&](int k) { return kfrag(list.e[k], list.t[k], list.s[k]); },
                            [&](int k, const AF& aa) {
-                             Acc& z = C[list.t[k]];
-                             z = PR::mma(aa, mode_op<P>(Y[list.e[k]], list.s[k]), z);
+                             Acc& z = out[list.t[k]];
+                             z = PR::mma(aa, Yw[list.e[k]][list.s[k]], z);
                            });
+    if constexpr (ST::TAIL) {
+#pragma unroll
+      for (int ee = 0; ee < 3; ++ee)
+#pragma unroll
+        for (int t = 0; t < NTO; ++t) out[t] = PA::mma(ktail(ee, t), Y[ee][ST::NREG - 1], out[t]);
+    }
   };
-  // quantities-in-registers result of order i to the derivative matrix
-  auto put_regs = [&](const Acc* R, int i, int rows, int nt) {
-    const int mp = mperm<P>(n);
+  // quantities-in-registers result of order o to the derivative matrix
+  auto put_regs = [&](const Acc* R, int o, int rows, int nt) {
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
       const int pq = 4 * k + g;
       if (pq >= 9) continue;
-      const int j = DV::col(i, pq), c = j >> 4;
-      const int f0 = c == 0 ? 0 : (c == 1 ? DV::frag0(1) : DV::frag0(DV::NT > 2 ? 2 : 1));
+      const int j = DV::col(o, pq), f0 = DV::tile0(j) * 64 + (j & 15);
 #pragma unroll
       for (int t = 0; t < MT; ++t) {
-        if (t >= nt || 16 * t + mp >= rows) continue;
-        const int pos = P == PREC_BF16
-                            ? (((f0 + t) * 64 + (mp >> 2) * 16 + (j & 15)) << 2) + (mp & 3)
-                            : (f0 + 4 * t + (mp >> 2)) * 64 + (mp & 3) * 16 + (j & 15);
-        S.dz[pos] = R[t][k];
+        if (t >= nt) continue;
+        const int l = mperm<N, M>(t, n);
+        if (l < rows) S.dz[f0 + (l >> 2) * 64 + (l & 3) * 16] = R[t][k];
       }
     }
   };
-  // quantities-in-lanes result of order i
-  auto put_lanes = [&](const Acc* C, int i, int nsteps) {
+  // quantities-in-lanes result of order o
+  auto put_lanes = [&](const Acc* C, int o, int rows) {
     if (p >= 9) return;
-    const int b = lbase(i);
 #pragma unroll
-    for (int r = 0; r < 4 * MT; ++r)
-      if (r < (P == PREC_BF16 ? 4 * nsteps : nsteps)) S.dz[b + roff(r)] = C[r >> 2][r & 3];
+    for (int t = 0; t < MT; ++t)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (16 * t < rows && acc_mode<N, M>(t, i, g) < ((rows + 3) & ~3))
+          S.dz[lane_place(o, t, i)] = C[t][i];
   };
-  constexpr int R1 = modes_upto(N - 1), R3 = modes_upto(N - 2), R4 = modes_upto(N - 3);
-  constexpr int NT1 = (R1 + 15) / 16;
-  auto ksteps = [](int rows) constexpr { return (rows + KS - 1) / KS; };
 
   // order 1: all modes in, degree <= N - 1 out; then the damage row
   Acc D1[MT];
@@ -468,48 +569,88 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(StepTune<N, 
   for (int t = 0; t < MT; ++t)
 #pragma unroll
     for (int k = 0; k < 4; ++k) D1[t][k] = 0;
-  contract_mix(d0, std::integral_constant<int, KSL>{}, std::integral_constant<int, NT1>{}, D1);
+  contract_mix(d0, d0w, std::integral_constant<int, L>{}, std::integral_constant<int, NT1>{}, D1);
   put_regs(D1, 1, R1, NT1);
   if constexpr (N >= 2) {
 #pragma unroll
     for (int t = 0; t < MT; ++t) {
-      const T v = S.al[16 * t + mperm<P>(n)];
+      const T v = S.al[mperm<N, M>(t, n)];
       if (g == 1) D1[t][2] = v;
     }
     // order 2: the damage row brings all modes, degree <= N - 1 out
     Acc D2[NT1];
-    mix_contract(D1, std::integral_constant<int, KSL>{}, std::integral_constant<int, NT1>{}, D2);
-    put_lanes(D2, 2, ksteps(R1));
+    mix_contract(D1, std::integral_constant<int, L>{}, std::integral_constant<int, NT1>{}, D2);
+    put_lanes(D2, 2, R1);
     if constexpr (N >= 3) {
-      T d2[4 * NT1];
+      using S2 = Steps<M, R1>;
+      constexpr int N2 = S2::NREG > 4 * NT1 ? S2::NREG : 4 * NT1;
+      T d2[N2];
 #pragma unroll
-      for (int r = 0; r < 4 * NT1; ++r) d2[r] = D2[r >> 2][r & 3];
+      for (int r = 0; r < N2; ++r) d2[r] = r < 4 * NT1 ? D2[r >> 2][r & 3] : T(0);
+      AF d2w[S2::WIDE];
+#pragma unroll
+      for (int s = 0; s < S2::WIDE; ++s) d2w[s] = wide_op<M>(d2, s);
       Acc D3[1];
-      contract_mix(d2, std::integral_constant<int, ksteps(R1)>{}, std::integral_constant<int, 1>{}, D3);
+      contract_mix(d2, d2w, std::integral_constant<int, R1>{}, std::integral_constant<int, 1>{}, D3);
       put_regs(D3, 3, R3, 1);
       if constexpr (N >= 4) {
         Acc D4[1];
-        mix_contract(D3, std::integral_constant<int, ksteps(R3)>{}, std::integral_constant<int, 1>{}, D4);
-        put_lanes(D4, 4, ksteps(R4));
+        mix_contract(D3, std::integral_constant<int, R3>{}, std::integral_constant<int, 1>{}, D4);
+        put_lanes(D4, 4, R4);
       }
     }
   }
   wave_sync();
-  AF* out = a.Dz + (size_t)e * DV::NF * 64;
-  if constexpr (P == PREC_BF16) {
+  T* out = a.Dz + (size_t)e * DV::NF * 64;
+  constexpr int VW = 16 / sizeof(T), NV = DV::NF * 64 / VW;
+  typedef T TV __attribute__((ext_vector_type(VW)));
 #pragma unroll
-    for (int f = 0; f < DV::NF; ++f) {
-      const T* v = S.dz + (f * 64 + lane) * 4;
-      out[f * 64 + lane] = split4(v[0], v[1], v[2], v[3]);
-    }
+  for (int k = 0; k < (NV + 63) / 64; ++k) {
+    const int idx = lane + 64 * k;
+    if (idx < NV) ((TV*)out)[idx] = ((const TV*)S.dz)[idx];
+  }
+}
+
+template <int N, int P> struct CkTabs {     // bytes of the matrices in LDS
+  static constexpr int M = MatForm<N, P>::value;
+  using T = typename Prec<P>::T;
+  using SL = Steps<M, Dims<N>::L>;
+  static constexpr int NT1 = (modes_upto(N - 1) + 15) / 16;
+  static constexpr int vw = Dims<N>::NCH * 4 * SL::WIDE * FragBytes<M>::value;
+  static constexpr int vt = SL::TAIL ? Dims<N>::NCH * 4 * 64 * (int)sizeof(T) : 0;
+  static constexpr int kw = 3 * NT1 * SL::WIDE * FragBytes<M>::value;
+  static constexpr int kt = SL::TAIL ? 3 * NT1 * 64 * (int)sizeof(T) : 0;
+  static constexpr int all = StepTune<N, P>::stage_ck ? vw + vt + kw + kt : 0;
+  static constexpr int wpb = StepTune<N, P>::wpb_ck;
+  static constexpr int bytes = all + wpb * (int)sizeof(CkLDS<N, P>);
+  static_assert(bytes <= 163840, "the workgroup's LDS");
+};
+
+template <int N, int P, class LW>
+__global__ __launch_bounds__((64 * CkTabs<N, P>::wpb))
+__attribute__((amdgpu_waves_per_eu(StepTune<N, P>::w_ck))) void k_ck(StepArgs<P> a) {
+  using T = typename Prec<P>::T;
+  using TB = CkTabs<N, P>;
+  __shared__ __attribute__((aligned(64))) char smem[TB::bytes];
+  if constexpr (StepTune<N, P>::stage_ck) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    char* tab = smem;
+    stage(tab, a.Vw, TB::vw);
+    stage(tab + TB::vw, a.Vt, TB::vt);
+    stage(tab + TB::vw + TB::vt, a.Kw, TB::kw);
+    stage(tab + TB::vw + TB::vt + TB::kw, a.Kt, TB::kt);
+    __syncthreads();
+    CkLDS<N, P>& S = ((CkLDS<N, P>*)(smem + TB::all))[wave];
+    for_elements(a, TB::wpb, [&](long long e, int lane) {
+      ck_element<N, P, LW>(a, e, S, tab, (const T*)(tab + TB::vw), tab + TB::vw + TB::vt,
+                           (const T*)(tab + TB::vw + TB::vt + TB::kw), lane);
+      wave_sync();
+    });
   } else {
-    constexpr int VW = 16 / sizeof(T), NV = DV::NF * 64 / VW;
-    typedef T TV __attribute__((ext_vector_type(VW)));
-#pragma unroll
-    for (int k = 0; k < (NV + 63) / 64; ++k) {
-      const int idx = lane + 64 * k;
-      if (idx < NV) ((TV*)out)[idx] = ((const TV*)S.dz)[idx];
-    }
+    CkLDS<N, P>& S = *(CkLDS<N, P>*)smem;
+    for_elements(a, 1, [&](long long e, int lane) {
+      ck_element<N, P, LW>(a, e, S, a.Vw, a.Vt, a.Kw, a.Kt, lane);
+    });
   }
 }
 
@@ -527,6 +668,21 @@ template <int N, int P> struct UpdLDS {
   T al[2][64];                    // damage row: projected source, lifted flux
 };
 
+// Modes of a face flux on its face: orthonormal polynomials of degree <= N in the
+// plane.  The basis restricted to a face is such a polynomial, so the lift of
+// the (N + 1)^2 point values is the lift of their NM2 projections.
+template <int N> struct FaceModes {
+  static constexpr int value = (N + 1) * (N + 2) / 2;
+};
+// Modes projected one per 16-row tile by matrix products; the few left over
+// (3 at degree 4, 4 at degree 3), which only the damage source needs, by a sum
+// over the lanes.
+template <int N> struct ProjTiles {
+  static constexpr int L = Dims<N>::L;
+  static constexpr int MTP = L > 16 && L % 16 <= 4 ? L / 16 : Dims<N>::MT;
+  static constexpr int LEFT = L > 16 * MTP ? L - 16 * MTP : 0;
+};
+
 // Corrector (Appendix A.2, Eqs. 2nd term, 3rd term, rhs term, time-integrated):
 // lift of the four face fluxes, volume and source terms, update.
 //
@@ -537,39 +693,57 @@ template <int N, int P> struct UpdLDS {
 // followed by the modal stiffness is the quadrature with S^e, so the ten time
 // integrals are projected once (one contraction over the points in place of
 // three) and the stiffness, of L x modes of degree < N, and the element's
-// Jacobian act on modes.  (Few modes carry what many points did, so the rounding
-// of split-BF16 operands would no longer average out there: these two
-// contractions take FP32 operands in that form.)
+// Jacobian act on modes.
 template <int N, int P, class LW>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(StepTune<N, P>::w_update))) void k_update(StepArgs<P> a, const int* fmap,
-                                               const typename Prec<P>::T* fflux) {
-  using PR = Prec<P>;
-  using T = typename PR::T;
+__device__ inline void update_element(const StepArgs<P>& a, long long e, const int* fmap,
+                                      const typename Prec<P>::T* fflux, UpdLDS<N, P>& S,
+                                      const void* Vw, const typename Prec<P>::T* Vt,
+                                      const void* Pw, const void* Ktw, int lane) {
+  constexpr int M = MatForm<N, P>::value;
+  using PR = Prec<M>;
+  using PA = Prec<P>;
+  using T = typename PA::T;
   using AF = typename PR::AF;
   using Acc = typename PR::Acc;
-  constexpr int PA_ = Accurate<P>::value;
-  using PA = Prec<PA_>;
   using DM = Dims<N>;
-  using DV = Deriv<N, P>;
-  constexpr int L = DM::L, Q = DM::Q, Ns = DM::Ns, Nt = DM::Nt, NCH = DM::NCH, MT = DM::MT;
-  constexpr int KS = PR::KS, KSL = round_up(L, KS) / KS, KSN = round_up(Ns, KS) / KS;
-  constexpr int NRN = P == PREC_BF16 ? 4 * KSN : KSN, NT = DV::NT, PD = StepTune<N, P>::pd_update;
+  using DV = Deriv<N>;
+  constexpr int L = DM::L, Q = DM::Q, Nt = DM::Nt, NCH = DM::NCH, MT = DM::MT;
+  constexpr int WL = Steps<M, L>::WIDE, NT = DV::NT;
+  constexpr int NM2 = FaceModes<N>::value, MTP = ProjTiles<N>::MTP, LEFT = ProjTiles<N>::LEFT;
+  constexpr int PD = M == PREC_X3 ? 1 : StepTune<N, P>::pd_update, PDL = N >= 4 ? 4 : 1;
   using SL = UpdLDS<N, P>;
-  __shared__ SL S;
-
-  const int lane = threadIdx.x, n = lane & 15, g = lane >> 4;
-  const long long e = elem_index(a);
-  if (e < 0) return;
+  const int n = lane & 15, g = lane >> 4;
   const int p = qperm<T>(n);
 
-  // lift of the face fluxes (negated where the element is the face's second
-  // side; integrals of the finer cluster, cleared, under local time stepping):
-  // quantities in rows, modes in columns
-  AF dz[DV::NF];
-  const AF* dze = a.Dz + (size_t)e * DV::NF * 64 + lane;
+  // the derivative matrix as row operand: tile ct in dzw[ct], dzt[ct]
+  T dzr[NT][Steps<M, L>::NREG];
+  const T* dze = a.Dz + (size_t)e * DV::NF * 64;
 #pragma unroll
-  for (int f = 0; f < DV::NF; ++f) dz[f] = dze[f * 64];
-  T fv[4][NRN], sc[4];
+  for (int ct = 0; ct < NT; ++ct) {
+    if constexpr (M == PREC_X3) {
+#pragma unroll
+      for (int r = 0; r < 9; ++r) {
+        const int W = DV::rows(16 * ct) % 32 <= 4 ? DV::rows(16 * ct) / 32 : 1;
+        const bool tail = DV::rows(16 * ct) % 32 <= 4;
+        if (r < 8 * W) {
+          const int f = 4 * (r >> 2) + g;
+          const T v = dze[(DV::frag0(ct) + (f < DV::steps(ct) ? f : 0)) * 64 + (r & 3) * 16 + n];
+          dzr[ct][r] = f < DV::steps(ct) ? v : T(0);
+        } else if (r == 8 * W && tail) {
+          dzr[ct][r] = dze[(DV::frag0(ct) + 8 * W) * 64 + lane];
+        }
+      }
+    } else {
+#pragma unroll
+      for (int r = 0; r < WL; ++r)
+        if (r < DV::steps(ct)) dzr[ct][r] = dze[(DV::frag0(ct) + r) * 64 + lane];
+    }
+  }
+  // the four face fluxes (integrals of the finer cluster, cleared, under local
+  // time stepping), quantity p in lane n, scaled; negated where the element is
+  // the face's first side
+  constexpr int NF2 = M == PREC_X3 ? 4 : (NM2 + 3) / 4;
+  T fv[4][NF2];
   int sp[4];
 #pragma unroll
   for (int f = 0; f < 4; ++f) {
@@ -577,41 +751,77 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(StepTune<N, 
     sp[f] = conn_perm(a.conn[(e * 4 + f) * 2 + 1]);
     const int nb = a.conn[(e * 4 + f) * 2];
     const bool fine = a.lts_c > 0 && nb >= 0 && a.ecl[nb] == a.lts_c - 1;
-    sc[f] = (T)((fm & 1 ? 1.0 : -1.0) * a.fgeo[(e * 4 + f) * 4 + 3] * (fine ? 1.0 : a.dt));
-    T* fl = (fine ? a.facc : (T*)fflux) + (size_t)(fm >> 1) * Ns * 10 + (p < 10 ? p : 9);
+    const T sc = (T)((fm & 1 ? 1.0 : -1.0) * a.fgeo[(e * 4 + f) * 4 + 3] * (fine ? 1.0 : a.dt));
+    T* fl = (fine ? a.facc : (T*)fflux) + (size_t)(fm >> 1) * NM2 * 10 + (p < 10 ? p : 9);
 #pragma unroll
-    for (int r = 0; r < NRN; ++r) {
-      const int i = reg_mode<P>(r, g);     // face point
-      fv[f][r] = fl[(i < Ns ? i : Ns - 1) * 10];
+    for (int r = 0; r < NF2; ++r) {
+      const int i = M == PREC_X3 ? 4 * g + r : 4 * r + g;     // face mode
+      fv[f][r] = fl[(i < NM2 ? i : NM2 - 1) * 10];
     }
     if (fine) {
       wave_sync();
 #pragma unroll
-      for (int r = 0; r < NRN; ++r) {
-        const int i = reg_mode<P>(r, g);
-        if (i < Ns && p < 10) fl[i * 10] = T(0);
+      for (int r = 0; r < NF2; ++r) {
+        const int i = M == PREC_X3 ? 4 * g + r : 4 * r + g;
+        if (i < NM2 && p < 10) fl[i * 10] = T(0);
       }
+    }
+#pragma unroll
+    for (int r = 0; r < NF2; ++r) {
+      const int i = M == PREC_X3 ? 4 * g + r : 4 * r + g;
+      fv[f][r] = (i < NM2 && p < 10) ? sc * fv[f][r] : T(0);
     }
   }
   const Law<T> law{a.amax, a.smin};
   const StepMat<T> m = LW::constants(load_mat<T>(a.mat + e * 8));
   Acc U[MT];
-  zero_C<P, MT>(U);
+  zero_C<M, MT>(U);
+  if constexpr (M == PREC_X3) {
+    // two faces per 32-term step: modes of one, then modes of the other
+    typedef __bf16 bf16q __attribute__((ext_vector_type(4)));
+    const bf16q* Lf[4];
+    AF b[2];
 #pragma unroll
-  for (int f = 0; f < 4; ++f) {
-    T v[NRN];
+    for (int f = 0; f < 4; ++f) Lf[f] = (const bf16q*)a.Rw + (size_t)(f * 6 + sp[f]) * MT * 192 + lane;
 #pragma unroll
-    for (int r = 0; r < NRN; ++r)
-      v[r] = (reg_mode<P>(r, g) < Ns && p < 10) ? sc[f] * fv[f][r] : T(0);
-    const AF* Lf = a.Lpk + (size_t)(f * 6 + sp[f]) * MT * KSN * 64 + lane;
-    stream<PD, MT * KSN, AF>([&](int k) { return Lf[((k % MT) * KSN + k / MT) * 64]; },
-                             [&](int k, const AF& b) {
-                               U[k % MT] = PR::mma(mode_op<P>(v, k / MT), b, U[k % MT]);
-                             });
+    for (int h = 0; h < 2; ++h) {
+      T v[8];
+#pragma unroll
+      for (int r = 0; r < 8; ++r) v[r] = fv[2 * h + (r >> 2)][r & 3];
+      b[h] = split8(v);
+    }
+    stream<PDL, 2 * MT, AF>(
+        [&](int k) {
+          const bf16q *La = Lf[k / MT * 2] + k % MT * 192, *Lb = Lf[k / MT * 2 + 1] + k % MT * 192;
+          AF f;
+          f.h = __builtin_shufflevector(La[0], Lb[0], 0, 1, 2, 3, 4, 5, 6, 7);
+          f.m = __builtin_shufflevector(La[64], Lb[64], 0, 1, 2, 3, 4, 5, 6, 7);
+          f.l = __builtin_shufflevector(La[128], Lb[128], 0, 1, 2, 3, 4, 5, 6, 7);
+          return f;
+        },
+        [&](int k, const AF& f) { U[k % MT] = PR::mma(b[k / MT], f, U[k % MT]); });
+  } else {
+#pragma unroll
+    for (int f = 0; f < 4; ++f) {
+      const AF* Lf = (const AF*)a.Rw + (size_t)(f * 6 + sp[f]) * MT * NF2 * 64 + lane;
+      stream<PD, MT * NF2, AF>([&](int k) { return Lf[((k % MT) * NF2 + k / MT) * 64]; },
+                               [&](int k, const AF& b) {
+                                 U[k % MT] = PR::mma(fv[f][k / MT], b, U[k % MT]);
+                               });
+    }
   }
+  AF dzw[NT][WL];
+#pragma unroll
+  for (int ct = 0; ct < NT; ++ct)
+#pragma unroll
+    for (int s = 0; s < WL; ++s)
+      if (M != PREC_X3 || DV::rows(16 * ct) > 4) dzw[ct][s] = wide_op<M>(dzr[ct], s);
 
-  typename PA::Acc X[MT];
-  zero_C<PA_, MT>(X);
+  typename PA::Acc X[MTP];
+  zero_C<P, MTP>(X);
+  T left[LEFT > 0 ? LEFT : 1];
+#pragma unroll
+  for (int k = 0; k < (LEFT > 0 ? LEFT : 1); ++k) left[k] = T(0);
 #pragma unroll 1
   for (int c = 0; c < NCH; ++c) {
     T x[10];
@@ -620,16 +830,37 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(StepTune<N, 
     {
       Acc C[NT][4];
 #pragma unroll
-      for (int ct = 0; ct < NT; ++ct) zero_C<P, 4>(C[ct]);
-      const AF* V = a.Vpk + (size_t)c * 4 * KSL * 64 + lane;
-      stream<PD, 4 * KSL, AF>([&](int k) { return V[((k % 4) * KSL + k / 4) * 64]; },
-                              [&](int k, const AF& b) {
-                                const int s = k / 4, t = k % 4;
+      for (int ct = 0; ct < NT; ++ct) zero_C<M, 4>(C[ct]);
+      stream<PD, 4 * WL, AF>(
+          [&](int k) { return load_frag<M>(Vw, (c * 4 + k % 4) * WL + k / 4, lane); },
+          [&](int k, const AF& b) {
+            const int s = k / 4, t = k % 4;
+            if constexpr (M == PREC_X3) {
 #pragma unroll
-                                for (int ct = 0; ct < NT; ++ct)
-                                  if (s < DV::steps(ct))
-                                    C[ct][t] = PR::mma(dz[DV::frag0(ct) + s], b, C[ct][t]);
-                              });
+              for (int q = 0; q < 6; ++q)
+#pragma unroll
+                for (int ct = 0; ct < NT; ++ct)
+                  if (DV::rows(16 * ct) > 4) C[ct][t] = PR::product(q, dzw[ct][s], b, C[ct][t]);
+            } else {
+#pragma unroll
+              for (int ct = 0; ct < NT; ++ct)
+                if (s < DV::steps(ct)) C[ct][t] = PR::mma(dzw[ct][s], b, C[ct][t]);
+            }
+          });
+      if constexpr (M == PREC_X3) {
+        // FP32 steps: rows 32..35 of tile 0 at degree 4, the four rows of the
+        // last tile at degree 3 (its own first four rows of the matrix)
+#pragma unroll
+        for (int ct = 0; ct < NT; ++ct) {
+          const int rows = DV::rows(16 * ct);
+          if (rows % 32 > 4) continue;
+#pragma unroll
+          for (int t = 0; t < 4; ++t)
+            C[ct][t] = PA::mma(dzr[ct][rows / 32 * 8],
+                               Vt[((rows > 32 ? 0 : NCH * 4 * Steps<M, L>::TAIL) + c * 4 + t) * 64 + lane],
+                               C[ct][t]);
+        }
+      }
 #pragma unroll
       for (int ct = 0; ct < NT; ++ct)
 #pragma unroll
@@ -643,16 +874,16 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(StepTune<N, 
         }
 #pragma unroll
       for (int z = 0; z < Nt; ++z) {
-        const T h = a.hz[z], gz = a.gamma[z];
+        const T gz = a.gamma[z];
         T u[10];   // (the velocity is not needed per time point)
 #pragma unroll
         for (int k = 0; k < 6; ++k) {
           T v = column<T>(C, DV::col(N, k));
 #pragma unroll
-          for (int i = N - 1; i >= 0; --i) v = column<T>(C, DV::col(i, k)) + (h * T(1.0 / (i + 1))) * v;
+          for (int i = N - 1; i >= 0; --i) v = column<T>(C, DV::col(i, k)) + a.hzi[z][i] * v;
           u[k] = v;
         }
-        u[9] = column<T>(C, 9) + h * column<T>(C, 10);
+        u[9] = column<T>(C, 9) + a.hzi[z][0] * column<T>(C, 10);
         T sig[6];
         const auto v = LW::invariants(u, law);
         LW::stress(v, u, m, sig);
@@ -668,29 +899,48 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(StepTune<N, 
         for (int i = 1; i <= N; ++i) x[k] += a.wint[i] * column<T>(C, DV::col(i, 6 + k));
       }
     }
+    if constexpr (LEFT > 0) {
+#pragma unroll
+      for (int k = 0; k < LEFT; ++k) left[k] += x[9] * a.PXleft[(c * LEFT + k) * 64 + lane];
+    }
     wave_sync();
 #pragma unroll
     for (int k = 0; k < 10; ++k) S.X[k * SL::RS + lane] = x[k];
     wave_sync();
     // projection: X += P_c x, modes in rows, quantities in columns
     typedef T T4 __attribute__((ext_vector_type(4), aligned(16)));
-    using PAF = typename PA::AF;
-    const T* xs = S.X + (p < 10 ? p : 9) * SL::RS + 4 * g;
-    T4 xv[4];
+    const T* xs = S.X + (p < 10 ? p : 9) * SL::RS;
+    if constexpr (M == PREC_X3) {
+      AF xw[2];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) xv[k] = *(const T4*)(xs + 16 * k);
-    const PAF* Pk = a.PXpk + (size_t)c * MT * 16 * 64 + lane;
-    stream<PD, 16 * MT, PAF>([&](int k) { return Pk[((k % MT) * 16 + k / MT) * 64]; },
-                             [&](int k, const PAF& aa) {
-                               const int s = k / MT;
-                               X[k % MT] = PA::mma(aa, xv[s >> 2][s & 3], X[k % MT]);
-                             });
+      for (int s = 0; s < 2; ++s) {
+        const T4 lo = *(const T4*)(xs + 32 * s + 8 * g), hi = *(const T4*)(xs + 32 * s + 8 * g + 4);
+        const T v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+        xw[s] = split8(v);
+      }
+      stream<1, 2 * MTP, AF>(
+          [&](int k) { return load_frag<M>(Pw, c * 2 * MTP + k, lane); },
+          [&](int k, const AF& aa) { X[k % MTP] = PR::mma(aa, xw[k / MTP], X[k % MTP]); });
+    } else {
+      T4 xv[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) xv[k] = *(const T4*)(xs + 16 * k + 4 * g);
+      stream<PD, 16 * MTP, AF>(
+          [&](int k) { return load_frag<M>(Pw, c * 16 * MTP + k, lane); },
+          [&](int k, const AF& aa) {
+            const int s = k / MTP;
+            X[k % MTP] = PR::mma(aa, xv[s >> 2][s & 3], X[k % MTP]);
+          });
+    }
   }
   // the projected source (times dt) leaves through LDS, one mode per lane
   if (p == 9) {
 #pragma unroll
-    for (int r = 0; r < 4 * MT; ++r) S.al[0][reg_mode<PA_>(r, g)] = X[r >> 2][r & 3];
+    for (int t = 0; t < MTP; ++t)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) S.al[0][acc_mode<N, M>(t, i, g)] = X[t][i];
   }
+  if constexpr (LEFT > 0) reduce_to_lds(left, S.al[0] + 16 * MTP, lane);
   T u9[3][MT];
   const T* U9 = a.U9 + e * 9 * L;
 #pragma unroll
@@ -703,22 +953,23 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(StepTune<N, 
   const double ua = a.Ua[e * L + (lane < L ? lane : L - 1)];
   // stiffness on modes, then the Jacobian and the material on quantities
   {
-    T xm[4 * MT];
+    using S1 = Steps<M, modes_upto(N - 1)>;
+    constexpr int NX = S1::NREG > 4 * MTP ? S1::NREG : 4 * MTP;
+    T xm[NX];
 #pragma unroll
-    for (int r = 0; r < 4 * MT; ++r) xm[r] = X[r >> 2][r & 3];
-    constexpr auto list = kt_list<N, PA_>();
-    using PAF = typename PA::AF;
-    constexpr int KSA = round_up(L, PA::KS) / PA::KS;
-    typename PA::Acc Z[3][MT];
+    for (int r = 0; r < NX; ++r) xm[r] = r < 4 * MTP ? X[r >> 2][r & 3] : T(0);
+    AF xw[S1::WIDE];
 #pragma unroll
-    for (int ee = 0; ee < 3; ++ee) zero_C<PA_, MT>(Z[ee]);
-    const PAF* Kt = a.Ktl + lane;
-    stream<PD, list.n, PAF>(
-        [&](int k) { return Kt[((list.e[k] * MT + list.t[k]) * KSA + list.s[k]) * 64]; },
-        [&](int k, const PAF& b) {
-          auto& z = Z[list.e[k]][list.t[k]];
-          z = PA::mma(mode_op<PA_>(xm, list.s[k]), b, z);
-        });
+    for (int s = 0; s < S1::WIDE; ++s) xw[s] = wide_op<M>(xm, s);
+    constexpr auto list = kt_list<N, M>();
+    Acc Z[3][MT];
+#pragma unroll
+    for (int ee = 0; ee < 3; ++ee) zero_C<M, MT>(Z[ee]);
+    stream<PD, list.n, AF>([&](int k) { return load_frag<M>(Ktw, k, lane); },
+                           [&](int k, const AF& b) {
+                             Acc& z = Z[list.e[k]][list.t[k]];
+                             z = PR::mma(xw[list.s[k]], b, z);
+                           });
     const T rs = (T)a.dt * (p >= 6 ? m.ir : T(1));
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
@@ -762,20 +1013,67 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(StepTune<N, 
   if (bad) a.flag[0] = 1;
 }
 
+template <int N, int P> struct UpdTabs {    // bytes of the matrices in LDS
+  static constexpr int M = MatForm<N, P>::value;
+  using T = typename Prec<P>::T;
+  using SL = Steps<M, Dims<N>::L>;
+  // FP32 steps of the evaluation: the leftover rows of tile 0, then the last tile
+  static constexpr int ntail =
+      M == PREC_X3 ? SL::TAIL + (Deriv<N>::rows(16 * (Deriv<N>::NT - 1)) <= 4) : 0;
+  static constexpr int vw = Dims<N>::NCH * 4 * SL::WIDE * FragBytes<M>::value;
+  static constexpr int vt = ntail * Dims<N>::NCH * 4 * 64 * (int)sizeof(T);
+  static constexpr int pw =
+      Dims<N>::NCH * (M == PREC_X3 ? 2 : 16) * ProjTiles<N>::MTP * FragBytes<M>::value;
+  static constexpr int kw = kt_list<N, M>().n * FragBytes<M>::value;
+  static constexpr int all = StepTune<N, P>::stage_update ? vw + vt + pw + kw : 0;
+  static constexpr int wpb = StepTune<N, P>::wpb_update;
+  static constexpr int bytes = all + wpb * (int)sizeof(UpdLDS<N, P>);
+  static_assert(bytes <= 163840, "the workgroup's LDS");
+};
+
+template <int N, int P, class LW>
+__global__ __launch_bounds__((64 * UpdTabs<N, P>::wpb))
+__attribute__((amdgpu_waves_per_eu(StepTune<N, P>::w_update))) void k_update(
+    StepArgs<P> a, const int* fmap, const typename Prec<P>::T* fflux) {
+  using T = typename Prec<P>::T;
+  using TB = UpdTabs<N, P>;
+  __shared__ __attribute__((aligned(64))) char smem[TB::bytes];
+  if constexpr (StepTune<N, P>::stage_update) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    char* tab = smem;
+    stage(tab, a.Vw, TB::vw);
+    stage(tab + TB::vw, a.Vt, TB::vt);
+    stage(tab + TB::vw + TB::vt, a.PXw, TB::pw);
+    stage(tab + TB::vw + TB::vt + TB::pw, a.Ktw, TB::kw);
+    __syncthreads();
+    UpdLDS<N, P>& S = ((UpdLDS<N, P>*)(smem + TB::all))[wave];
+    for_elements(a, TB::wpb, [&](long long e, int lane) {
+      update_element<N, P, LW>(a, e, fmap, fflux, S, tab, (const T*)(tab + TB::vw),
+                               tab + TB::vw + TB::vt, tab + TB::vw + TB::vt + TB::pw, lane);
+      wave_sync();
+    });
+  } else {
+    UpdLDS<N, P>& S = *(UpdLDS<N, P>*)smem;
+    for_elements(a, 1, [&](long long e, int lane) {
+      update_element<N, P, LW>(a, e, fmap, fflux, S, a.Vw, a.Vt, a.PXw, a.Ktw, lane);
+    });
+  }
+}
+
 // Time since each cluster's prediction at the start of the step being corrected
 // (all zero in the global step).
 struct ClusterOffsets { double v[8]; };
 
 template <int N, int P> struct FaceLDS {
   using T = typename Prec<P>::T;
-  static constexpr int JS = 16 * Deriv<N, P>::NT + 16 / sizeof(T);
+  static constexpr int JS = 16 * Deriv<N>::NT + 16 / sizeof(T);
   alignas(16) T tr[2][Dims<N>::Ns * JS];   // derivative traces of both sides, [point][column]
 };
 
 // Face fluxes (Appendix A.2 Eq. 2nd term, A.3), interior faces once: traces of
 // both sides' derivative matrices at the shared face points, Taylor sums per
 // (time point, face point), local Lax-Friedrichs or boundary flux, time
-// quadrature; sum_z gamma_z F* at the face points, [face][Ns][10].
+// quadrature; sum_z gamma_z F* projected on the face modes, [face][NM2][10].
 template <int N, int P, class LW>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(StepTune<N, P>::w_face))) void k_face(StepArgs<P> a, const int* faces, long long nfaces,
                                              typename Prec<P>::T* fflux, const int* flist,
@@ -785,12 +1083,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(StepTune<N, 
   using AF = typename PR::AF;
   using Acc = typename PR::Acc;
   using DM = Dims<N>;
-  using DV = Deriv<N, P>;
+  using DV = Deriv<N>;
   using SL = FaceLDS<N, P>;
   constexpr int L = DM::L, Ns = DM::Ns, Nt = DM::Nt, NST = DM::NST, NT = DV::NT;
-  constexpr int KS = PR::KS, KSL = round_up(L, KS) / KS, JS = SL::JS, PD = StepTune<N, P>::pd_face;
-  constexpr int NRD = (Ns * Nt + 63) / 64, FR = 11;
-  static_assert(Ns * Nt * FR <= 2 * Ns * JS, "fluxes fit the spent traces");
+  constexpr int KSL = (L + 3) / 4, JS = SL::JS, PD = StepTune<N, P>::pd_face;
+  constexpr int NRD = (Ns * Nt + 63) / 64, FR = 11, NM2 = FaceModes<N>::value;
+  static_assert(Ns * Nt * FR + Ns * 10 <= 2 * Ns * JS, "fluxes fit the spent traces");
   __shared__ SL S;
 
   const int lane = threadIdx.x, n = lane & 15, g = lane >> 4;
@@ -815,7 +1113,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(StepTune<N, 
   // (a boundary face evaluates its own side twice and uses the first)
 #pragma unroll
   for (int side = 0; side < 2; ++side) {
-    const AF* F = a.Fpk + (size_t)((side ? nf : f) * 6 + (side ? sq : sp)) * NST * KSL * 64 + lane;
+    const AF* F = a.Fst + (size_t)((side ? nf : f) * 6 + (side ? sq : sp)) * NST * KSL * 64 + lane;
     Acc C[NT][NST];
 #pragma unroll
     for (int ct = 0; ct < NT; ++ct) zero_C<P, NST>(C[ct]);
@@ -893,7 +1191,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(StepTune<N, 
     }
   }
   wave_sync();
-  T* out = fflux + (size_t)fid * Ns * 10;
+  T* sG = sF + Ns * Nt * FR;
 #pragma unroll
   for (int j = 0; j < (Ns * 10 + 63) / 64; ++j) {
     const int idx = lane + 64 * j;
@@ -902,8 +1200,24 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(StepTune<N, 
       T s = T(0);
 #pragma unroll
       for (int z = 0; z < Nt; ++z) s += a.gamma[z] * sF[(z * Ns + i) * FR + k];
-      out[idx] = s;
+      sG[idx] = s;
     }
+  }
+  wave_sync();
+  // projection on the face modes: modes in rows, quantities in columns
+  Acc C;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) C[i] = 0;
+#pragma unroll
+  for (int s = 0; s < (Ns + 3) / 4; ++s) {
+    const int i = 4 * s + g;
+    C = PR::mma(a.Psi[s * 64 + lane], sG[(i < Ns ? i : Ns - 1) * 10 + (n < 10 ? n : 9)], C);
+  }
+  T* out = fflux + (size_t)fid * NM2 * 10;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int r = PR::crow(lane, i);
+    if (r < NM2 && n < 10) out[r * 10 + n] = C[i];
   }
 }
 
@@ -913,20 +1227,13 @@ template <int N, int P>
 __global__ __launch_bounds__(64) void k_time_points(StepArgs<P> a, double* out) {
   using T = typename Prec<P>::T;
   using DM = Dims<N>;
-  using DV = Deriv<N, P>;
+  using DV = Deriv<N>;
   constexpr int L = DM::L, Nt = DM::Nt;
   const long long e = blockIdx.x;
   auto at = [&](int l, int j) -> T {
     const int c = j >> 4, f0 = DV::frag0(c);
     if (l >= DV::rows(j)) return T(0);
-    const typename Prec<P>::AF* d = a.Dz + (size_t)e * DV::NF * 64;
-    if constexpr (P == PREC_BF16) {
-      const bf16s v = d[(f0 + l / 16) * 64 + ((l % 16) / 4) * 16 + (j & 15)];
-      auto f = [](short b) { return __builtin_bit_cast(float, (unsigned)(unsigned short)b << 16); };
-      return f(v.hi[l & 3]) + f(v.lo[l & 3]);
-    } else {
-      return d[(f0 + l / 4) * 64 + (l & 3) * 16 + (j & 15)];
-    }
+    return a.Dz[((size_t)e * DV::NF + f0 + l / 4) * 64 + (l & 3) * 16 + (j & 15)];
   };
   for (int idx = threadIdx.x; idx < 10 * L; idx += 64) {
     const int p = idx / L, l = idx - p * L;
