@@ -76,7 +76,7 @@ struct dgd_handle {
   // reference data on the device
   DevBuf Vpk, Kpk, Spk, Fpk, Lpk, Ppk, Vd, wqd, Pwd, betad, KPpk;
   // Cauchy-Kovalevskaya step (step_kernels.hpp)
-  DevBuf Vw, Vt, Kw, Kt, Ktw, PXw, PXleft, Rw, Fst, Psi, Psrc, mixP, mixV;
+  DevBuf Vw, Vt, Kw, Kt, Ktw, PXw, PXleft, Rw, Fst, Fstt, Psi, Psrc, mixP, mixV;
   size_t dz_elem = 0;     // bytes of one element's time derivatives
   double points_dt = 0.0;      // step of the last step's derivatives
   bool points_in_uz = false;   // the last step left time-point states in Uz, not derivatives in Dz
@@ -142,7 +142,7 @@ struct dgd_handle {
                      &VTpk, &STpk, &PTpk, &KTpk, &lam[0], &lam[1], &gtr, &gmuf, &lzf, &gmu, &gcd, &adjW9,
                      &adjWa, &dlds, &seg9, &sega, &seguz, &segd, &segacc, &save9, &savea, &st9, &sta,
                      &KPpk, &ecl, &facc, &Vw, &Vt, &Kw, &Kt, &Ktw, &PXw,
-                     &PXleft, &Rw, &Fst, &Psi, &Psrc, &mixP, &mixV, &Dz, &Vpk32, &Kpk32, &Spk32, &Fpk32, &Lpk32, &Ppk32,
+                     &PXleft, &Rw, &Fst, &Fstt, &Psi, &Psrc, &mixP, &mixV, &Dz, &Vpk32, &Kpk32, &Spk32, &Fpk32, &Lpk32, &Ppk32,
                      &KPpk32};
     for (DevBuf* b : all) b->release();
     for (DevBuf& b : ck9) b.release();
@@ -397,6 +397,7 @@ dgd_status build_step_packs(dgd_handle* h) {
   constexpr bool X3 = M == PREC_X3;
   constexpr int L = DM::L, Q = DM::Q, Ns = DM::Ns, MT = DM::MT, NCH = DM::NCH, NST = DM::NST;
   constexpr int NT1 = (modes_upto(N - 1) + 15) / 16, Q4 = (Q + 3) / 4, NM2 = FaceModes<N>::value;
+  constexpr int MF = FaceForm<N, P>::value;
   using SL = Steps<M, L>;
   const RefData& r = h->ref;
   // row of entry j of wide step s (contractions over modes) and of a leftover step
@@ -406,8 +407,11 @@ dgd_status build_step_packs(dgd_handle* h) {
     return (k < L && l < L && r.deg[k] < r.deg[l]) ? r.K[((size_t)e * L + k) * L + l] : 0.0;
   };
   auto Pw = [&](int l, int q) { return (l < L && q < Q) ? r.Pw[(size_t)l * Q + q] : 0.0; };
-  std::vector<char> vw, kw, ktw, pw, rw;
-  std::vector<T> vt, kt, pl, fs, psi, ps((size_t)Q4 * L * 4, T(0));
+  auto Ft = [&](int ff, int i, int l) {
+    return (i < Ns && l < L) ? r.F[((size_t)ff * Ns + i) * L + l] : 0.0;
+  };
+  std::vector<char> vw, kw, ktw, pw, rw, fs;
+  std::vector<T> vt, kt, pl, ft, psi, ps((size_t)Q4 * L * 4, T(0));
   auto tail = [](std::vector<T>& out, auto val) {
     for (int lane = 0; lane < 64; ++lane) out.push_back((T)val(lane & 15, lane >> 4));
   };
@@ -469,15 +473,20 @@ dgd_status build_step_packs(dgd_handle* h) {
       }
     }
     for (int t = 0; t < NST; ++t)
-      for (int s = 0; s < (L + 3) / 4; ++s)
-        tail(fs, [&](int n, int g) {
-          const int i = 16 * t + n, l = 4 * s + g;
-          return (i < Ns && l < L) ? F[i * L + l] : 0.0;
+      for (int s = 0; s < Steps<MF, L>::WIDE; ++s)
+        append_frag<MF>(fs, [&](int n, int g, int j) {
+          return Ft(ff, 16 * t + n, MF == PREC_X3 ? mode(s, g, j) : 4 * s + g);
         });
   }
   for (int s = 0; s < (Ns + 3) / 4; ++s)
     tail(psi, [&](int n, int g) {
       const int i = 4 * s + g;
+  if constexpr (Steps<MF, L>::TAIL)
+    for (int t = 0; t < 24 * NST; ++t)
+      tail(ft, [&](int n, int g) { return Ft(t / NST, 16 * (t % NST) + n, 32 * Steps<MF, L>::WIDE + g); });
+  if constexpr (MF == PREC_X3 && Deriv<N>::rows(16 * (Deriv<N>::NT - 1)) <= 4)
+    for (int t = 0; t < 24 * NST; ++t)
+      tail(ft, [&](int n, int g) { return Ft(t / NST, 16 * (t % NST) + n, g); });
       return (n < NM2 && i < Ns) ? r.beta[i] * fm[n][i] : 0.0;
     });
   for (int q = 0; q < Q; ++q)
@@ -509,6 +518,7 @@ dgd_status build_step_packs(dgd_handle* h) {
       (st = upload(h, h->Psi, psi)) || (st = upload(h, h->Psrc, ps)) || (st = upload(h, h->mixP, mp)) ||
       (st = upload(h, h->mixV, mv)))
     return st;
+      (st = upload(h, h->Fstt, ft)) ||
   h->dz_elem = (size_t)Deriv<N>::NF * 64 * sizeof(T);
   return DGD_OK;
 }
@@ -612,7 +622,8 @@ StepArgs<P> make_args(dgd_handle* h) {
   a.PXw = h->PXw.p;
   a.PXleft = (const T*)h->PXleft.p;
   a.Rw = h->Rw.p;
-  a.Fst = (const T*)h->Fst.p;
+  a.Fst = h->Fst.p;
+  a.Fstt = (const T*)h->Fstt.p;
   a.Psi = (const T*)h->Psi.p;
   a.Psrc = (const T*)h->Psrc.p;
   a.mixP = (const int*)h->mixP.p;

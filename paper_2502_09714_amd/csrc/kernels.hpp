@@ -98,7 +98,8 @@ template <int P> struct StepArgs {
   const void* PXw;      // projection of the point integrals
   const T* PXleft;      // its last modes [chunk][mode][64]
   const void* Rw;       // lift of the face modes [face][permutation][tile]
-  const T* Fst;         // face traces [face][permutation][tile][step]
+  const void* Fst;      // face traces [face][permutation][tile][wide step]
+  const T* Fstt;        // their FP32 steps (three-way form)
   const T* Psi;         // projection of point fluxes on the face modes [step]
   const T* Psrc;        // Pw as [point / 4][mode][4]
   const int* mixP;      // [3][3][64] which averaged-tangent entry a lane's A*_e entry takes

@@ -41,6 +41,11 @@ __host__ __device__ constexpr int mode_degree(int l) {
 template <int N, int P> struct MatForm {
   static constexpr int value = P == PREC_F32 && N >= 3 ? PREC_X3 : P;
 };
+// The face traces read their matrices (24 of them) from L2, where the split ones
+// are half as large again: only from degree 4 on is that the smaller cost.
+template <int N, int P> struct FaceForm {
+  static constexpr int value = P == PREC_F32 && N >= 4 ? PREC_X3 : P;
+};
 
 // Steps of a contraction over R rows: WIDE fragments of Prec<M>::KS rows each,
 // and in the three-way form, where 1..4 rows are left over, one FP32 step (TAIL).
@@ -98,7 +103,7 @@ template <int N> struct Deriv {
 template <int N, int P> struct StepTune {
   static constexpr bool stage_ck = N >= 3, stage_update = N >= 3 && P != PREC_F64;
   static constexpr int wpb_ck = !stage_ck ? 1 : (P == PREC_F64 ? 8 : 16);
-  static constexpr int wpb_update = !stage_update ? 1 : (N >= 4 ? 8 : 16);
+  static constexpr int wpb_update = !stage_update ? 1 : (N >= 4 ? 12 : 16);
   static constexpr int w_ck = P == PREC_F64 ? 2 : 4, w_face = P == PREC_F64 ? 2 : 4,
                        w_update = stage_update ? wpb_update / 4 : (P == PREC_F64 && N >= 4 ? 1 : 2);
   static constexpr int pd_ck = 4, pd_face = 6, pd_update = 4;
@@ -308,7 +313,10 @@ __device__ inline void stream(Ld ld, Use use) {
 
 template <int N, int P> struct CkLDS {
   using T = typename Prec<P>::T;
-  alignas(16) T dz[Deriv<N>::NF * 64];
+  // fragments of the derivative matrix, padded by 16 bytes each: a column's
+  // fragments then start on different banks
+  static constexpr int FS = 64 + 16 / sizeof(T);
+  alignas(16) T dz[Deriv<N>::NF * FS];
   alignas(16) T r[Dims<N>::NCH * 64];                   // damage rate at the points
   T al[64];                                             // its projection, the damage row of D^1
   T ext[64];                                            // sums of the tangent
@@ -368,20 +376,33 @@ __device__ inline void ck_element(const StepArgs<P>& a, long long e, CkLDS<N, P>
   }
   const Law<T> law{a.amax, a.smin};
   const StepMat<T> m = LW::constants(load_mat<T>(a.mat + e * 8));
-  for (int i = lane; i < DV::NF * 16; i += 64) {
-    typedef T T4 __attribute__((ext_vector_type(4), aligned(16)));
-    ((T4*)S.dz)[i] = T4{T(0), T(0), T(0), T(0)};
-  }
+  constexpr int FS = CkLDS<N, P>::FS, VW = 16 / sizeof(T);
+  typedef T TV __attribute__((ext_vector_type(VW)));
+  for (int i = lane; i < DV::NF * FS / VW; i += 64) ((TV*)S.dz)[i] = TV(T(0));
   wave_sync();
-  // place of quantities-in-lanes register (t, i) of order o
-  auto lane_place = [&](int o, int t, int i) {
-    const int j = DV::col(o, p), f0 = DV::tile0(j) * 64 + (j & 15);
-    return M == PREC_X3 && t < 2 * WL ? f0 + g * 64 + t * 256 + i * 16 : f0 + g * 16 + t * 256 + i * 64;
+  // tile t of a quantities-in-lanes result of order o, c[0..3] in registers
+  typedef T T4 __attribute__((ext_vector_type(4), aligned(16)));
+  auto put_tile = [&](int o, int t, const T4& c, int rows) {
+    const int j = DV::col(o, p);
+    T* d = S.dz + DV::tile0(j) * FS + (j & 15);
+    if (M == PREC_X3 && t < 2 * WL) {
+      if (16 * t + 4 * g >= rows) return;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) d[(4 * t + g) * FS + 16 * i] = c[i];
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (16 * t + 4 * i < rows) d[(4 * t + i) * FS + 16 * g] = c[i];
+    }
   };
   if (p < 10) {
 #pragma unroll
-    for (int r = 0; r < NR; ++r)
-      if (SL::row(r, g) < 4 * DV::steps(0)) S.dz[lane_place(0, r >> 2, r & 3)] = d0[r];
+    for (int t = 0; t < MT; ++t) {
+      T4 c;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) c[i] = 4 * t + i < NR ? d0[4 * t + i < NR ? 4 * t + i : 0] : T(0);
+      put_tile(0, t, c, L);
+    }
   }
   AF d0w[WL > 0 ? WL : 1];
 #pragma unroll
@@ -431,7 +452,6 @@ __device__ inline void ck_element(const StepArgs<P>& a, long long e, CkLDS<N, P>
   {
     T s = T(0);
     if (lane < L) {
-      typedef T T4 __attribute__((ext_vector_type(4), aligned(16)));
       const T4* pw = (const T4*)a.Psrc + lane;
       const T4* rr = (const T4*)S.r;
 #pragma unroll 8
@@ -439,7 +459,7 @@ __device__ inline void ck_element(const StepArgs<P>& a, long long e, CkLDS<N, P>
         const T4 x = pw[k * L], y = rr[k];
         s += x[0] * y[0] + x[1] * y[1] + x[2] * y[2] + x[3] * y[3];
       }
-      S.dz[(lane >> 2) * 64 + (lane & 3) * 16 + 10] = s;
+      S.dz[(lane >> 2) * FS + 16 * (lane & 3) + 10] = s;          // column 10
     }
     S.al[lane] = s;
   }
@@ -543,12 +563,12 @@ __device__ inline void ck_element(const StepArgs<P>& a, long long e, CkLDS<N, P>
     for (int k = 0; k < 3; ++k) {
       const int pq = 4 * k + g;
       if (pq >= 9) continue;
-      const int j = DV::col(o, pq), f0 = DV::tile0(j) * 64 + (j & 15);
+      const int j = DV::col(o, pq), f0 = DV::tile0(j) * FS + (j & 15);
 #pragma unroll
       for (int t = 0; t < MT; ++t) {
         if (t >= nt) continue;
         const int l = mperm<N, M>(t, n);
-        if (l < rows) S.dz[f0 + (l >> 2) * 64 + (l & 3) * 16] = R[t][k];
+        if (l < rows) S.dz[f0 + (l >> 2) * FS + 16 * (l & 3)] = R[t][k];
       }
     }
   };
@@ -557,10 +577,7 @@ __device__ inline void ck_element(const StepArgs<P>& a, long long e, CkLDS<N, P>
     if (p >= 9) return;
 #pragma unroll
     for (int t = 0; t < MT; ++t)
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        if (16 * t < rows && acc_mode<N, M>(t, i, g) < ((rows + 3) & ~3))
-          S.dz[lane_place(o, t, i)] = C[t][i];
+      if (16 * t < rows) put_tile(o, t, T4{C[t][0], C[t][1], C[t][2], C[t][3]}, (rows + 3) & ~3);
   };
 
   // order 1: all modes in, degree <= N - 1 out; then the damage row
@@ -602,12 +619,11 @@ __device__ inline void ck_element(const StepArgs<P>& a, long long e, CkLDS<N, P>
   }
   wave_sync();
   T* out = a.Dz + (size_t)e * DV::NF * 64;
-  constexpr int VW = 16 / sizeof(T), NV = DV::NF * 64 / VW;
-  typedef T TV __attribute__((ext_vector_type(VW)));
+  constexpr int NV = DV::NF * 64 / VW;
 #pragma unroll
   for (int k = 0; k < (NV + 63) / 64; ++k) {
     const int idx = lane + 64 * k;
-    if (idx < NV) ((TV*)out)[idx] = ((const TV*)S.dz)[idx];
+    if (idx < NV) ((TV*)out)[idx] = ((const TV*)S.dz)[idx + idx / (64 / VW)];   // (padding skipped)
   }
 }
 
@@ -661,11 +677,43 @@ template <class T, class Acc> __device__ inline T column(const Acc (*C)[4], int 
   return sizeof(T) == 8 ? C[j >> 4][m & 3][m >> 2] : C[j >> 4][m >> 2][m & 3];
 }
 
+// the derivative matrix of an element as row operand, tile by tile (columns in
+// lanes, rows in the order of Steps::row)
+template <int N, int M, class T, int NT, int NR>
+__device__ inline void load_deriv(const T* dze, T (&d)[NT][NR], int lane) {
+  using DV = Deriv<N>;
+  const int n = lane & 15, g = lane >> 4;
+#pragma unroll
+  for (int ct = 0; ct < NT; ++ct) {
+    const int rows = DV::rows(16 * ct), steps = DV::steps(ct);
+    const T* t = dze + DV::frag0(ct) * 64 + n;
+    if constexpr (M == PREC_X3) {
+      const bool tail = rows % 32 <= 4;                // one FP32 step more
+      const int W = tail ? rows / 32 : 1;
+#pragma unroll
+      for (int r = 0; r < 8 * W; ++r) {
+        const int f = 4 * (r >> 2) + g;
+        const T v = t[(f < steps ? f : 0) * 64 + (r & 3) * 16];
+        d[ct][r] = f < steps ? v : T(0);
+      }
+      if (tail) d[ct][8 * W] = t[8 * W * 64 + 16 * g];
+    } else {
+#pragma unroll
+      for (int r = 0; r < NR; ++r)
+        if (r < steps) d[ct][r] = t[r * 64 + 16 * g];
+    }
+  }
+}
+
 template <int N, int P> struct UpdLDS {
   using T = typename Prec<P>::T;
   static constexpr int RS = 64 + 16 / sizeof(T);
+  // degree 4: 12 registers fewer in the point loop, so that three wavefronts fit a
+  // SIMD without spills
+  static constexpr bool KEEP = MatForm<N, P>::value == PREC_X3 && N >= 4;
   alignas(16) T X[10 * RS];       // time integrals at the points of one chunk, [quantity][point]
   T al[2][64];                    // damage row: projected source, lifted flux
+  alignas(16) T U[KEEP ? Dims<N>::MT * 256 : 4];        // lifted fluxes, during the point loop
 };
 
 // Modes of a face flux on its face: orthonormal polynomials of degree <= N in the
@@ -717,28 +765,7 @@ __device__ inline void update_element(const StepArgs<P>& a, long long e, const i
 
   // the derivative matrix as row operand: tile ct in dzw[ct], dzt[ct]
   T dzr[NT][Steps<M, L>::NREG];
-  const T* dze = a.Dz + (size_t)e * DV::NF * 64;
-#pragma unroll
-  for (int ct = 0; ct < NT; ++ct) {
-    if constexpr (M == PREC_X3) {
-#pragma unroll
-      for (int r = 0; r < 9; ++r) {
-        const int W = DV::rows(16 * ct) % 32 <= 4 ? DV::rows(16 * ct) / 32 : 1;
-        const bool tail = DV::rows(16 * ct) % 32 <= 4;
-        if (r < 8 * W) {
-          const int f = 4 * (r >> 2) + g;
-          const T v = dze[(DV::frag0(ct) + (f < DV::steps(ct) ? f : 0)) * 64 + (r & 3) * 16 + n];
-          dzr[ct][r] = f < DV::steps(ct) ? v : T(0);
-        } else if (r == 8 * W && tail) {
-          dzr[ct][r] = dze[(DV::frag0(ct) + 8 * W) * 64 + lane];
-        }
-      }
-    } else {
-#pragma unroll
-      for (int r = 0; r < WL; ++r)
-        if (r < DV::steps(ct)) dzr[ct][r] = dze[(DV::frag0(ct) + r) * 64 + lane];
-    }
-  }
+  load_deriv<N, M>(a.Dz + (size_t)e * DV::NF * 64, dzr, lane);
   // the four face fluxes (integrals of the finer cluster, cleared, under local
   // time stepping), quantity p in lane n, scaled; negated where the element is
   // the face's first side
@@ -809,6 +836,10 @@ __device__ inline void update_element(const StepArgs<P>& a, long long e, const i
                                  U[k % MT] = PR::mma(fv[f][k / MT], b, U[k % MT]);
                                });
     }
+  }
+  if constexpr (SL::KEEP) {
+#pragma unroll
+    for (int t = 0; t < MT; ++t) ((Acc*)S.U)[64 * t + lane] = U[t];
   }
   AF dzw[NT][WL];
 #pragma unroll
@@ -971,6 +1002,10 @@ __device__ inline void update_element(const StepArgs<P>& a, long long e, const i
                              z = PR::mma(xw[list.s[k]], b, z);
                            });
     const T rs = (T)a.dt * (p >= 6 ? m.ir : T(1));
+    if constexpr (SL::KEEP) {
+#pragma unroll
+      for (int t = 0; t < MT; ++t) U[t] = ((const Acc*)S.U)[64 * t + lane];
+    }
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
       T w[3];
@@ -1078,15 +1113,18 @@ template <int N, int P, class LW>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(StepTune<N, P>::w_face))) void k_face(StepArgs<P> a, const int* faces, long long nfaces,
                                              typename Prec<P>::T* fflux, const int* flist,
                                              ClusterOffsets offs) {
-  using PR = Prec<P>;
-  using T = typename PR::T;
+  constexpr int M = FaceForm<N, P>::value;
+  using PR = Prec<M>;
+  using PA = Prec<P>;
+  using T = typename PA::T;
   using AF = typename PR::AF;
   using Acc = typename PR::Acc;
   using DM = Dims<N>;
   using DV = Deriv<N>;
   using SL = FaceLDS<N, P>;
-  constexpr int L = DM::L, Ns = DM::Ns, Nt = DM::Nt, NST = DM::NST, NT = DV::NT;
-  constexpr int KSL = (L + 3) / 4, JS = SL::JS, PD = StepTune<N, P>::pd_face;
+  using SD = Steps<M, DM::L>;
+  constexpr int Ns = DM::Ns, Nt = DM::Nt, NST = DM::NST, NT = DV::NT, WL = SD::WIDE;
+  constexpr int JS = SL::JS, PD = M == PREC_X3 ? 2 : StepTune<N, P>::pd_face;
   constexpr int NRD = (Ns * Nt + 63) / 64, FR = 11, NM2 = FaceModes<N>::value;
   static_assert(Ns * Nt * FR + Ns * 10 <= 2 * Ns * JS, "fluxes fit the spent traces");
   __shared__ SL S;
@@ -1103,28 +1141,52 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(StepTune<N, 
   const bool inner = kind == 0;
   const long long nb = inner ? (long long)(of >> 2) : e;
   const int nf = inner ? (of & 3) : f, sq = inner ? conn_nperm(w) : sp;
-  AF dz[2][DV::NF];
+  T dzr[2][NT][SD::NREG];
 #pragma unroll
-  for (int side = 0; side < 2; ++side) {
-    const AF* d = a.Dz + (size_t)(side ? nb : e) * DV::NF * 64 + lane;
-#pragma unroll
-    for (int k = 0; k < DV::NF; ++k) dz[side][k] = d[k * 64];
-  }
+  for (int side = 0; side < 2; ++side)
+    load_deriv<N, M>(a.Dz + (size_t)(side ? nb : e) * DV::NF * 64, dzr[side], lane);
   // (a boundary face evaluates its own side twice and uses the first)
 #pragma unroll
   for (int side = 0; side < 2; ++side) {
-    const AF* F = a.Fst + (size_t)((side ? nf : f) * 6 + (side ? sq : sp)) * NST * KSL * 64 + lane;
+    const int fo = (side ? nf : f) * 6 + (side ? sq : sp);
     Acc C[NT][NST];
 #pragma unroll
     for (int ct = 0; ct < NT; ++ct) zero_C<P, NST>(C[ct]);
-    stream<PD, NST * KSL, AF>([&](int k) { return F[((k % NST) * KSL + k / NST) * 64]; },
-                              [&](int k, const AF& b) {
-                                const int s = k / NST, t = k % NST;
+    AF dzw[NT][WL];
 #pragma unroll
-                                for (int ct = 0; ct < NT; ++ct)
-                                  if (s < DV::steps(ct))
-                                    C[ct][t] = PR::mma(dz[side][DV::frag0(ct) + s], b, C[ct][t]);
-                              });
+    for (int ct = 0; ct < NT; ++ct)
+#pragma unroll
+      for (int s = 0; s < WL; ++s)
+        if (M != PREC_X3 || DV::rows(16 * ct) > 4) dzw[ct][s] = wide_op<M>(dzr[side][ct], s);
+    stream<PD, NST * WL, AF>(
+        [&](int k) { return load_frag<M>(a.Fst, (fo * NST + k % NST) * WL + k / NST, lane); },
+        [&](int k, const AF& b) {
+          const int s = k / NST, t = k % NST;
+          if constexpr (M == PREC_X3) {
+#pragma unroll
+            for (int q = 0; q < 6; ++q)
+#pragma unroll
+              for (int ct = 0; ct < NT; ++ct)
+                if (DV::rows(16 * ct) > 4) C[ct][t] = PR::product(q, dzw[ct][s], b, C[ct][t]);
+          } else {
+#pragma unroll
+            for (int ct = 0; ct < NT; ++ct)
+              if (s < DV::steps(ct)) C[ct][t] = PR::mma(dzw[ct][s], b, C[ct][t]);
+          }
+        });
+    if constexpr (M == PREC_X3) {
+      // FP32 steps, as in the corrector
+#pragma unroll
+      for (int ct = 0; ct < NT; ++ct) {
+        const int rows = DV::rows(16 * ct);
+        if (rows % 32 > 4) continue;
+#pragma unroll
+        for (int t = 0; t < NST; ++t)
+          C[ct][t] = PA::mma(dzr[side][ct][rows / 32 * 8],
+                             a.Fstt[((rows > 32 ? 0 : 24 * NST * SD::TAIL) + fo * NST + t) * 64 + lane],
+                             C[ct][t]);
+      }
+    }
 #pragma unroll
     for (int ct = 0; ct < NT; ++ct)
 #pragma unroll
@@ -1211,12 +1273,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(StepTune<N, 
 #pragma unroll
   for (int s = 0; s < (Ns + 3) / 4; ++s) {
     const int i = 4 * s + g;
-    C = PR::mma(a.Psi[s * 64 + lane], sG[(i < Ns ? i : Ns - 1) * 10 + (n < 10 ? n : 9)], C);
+    C = PA::mma(a.Psi[s * 64 + lane], sG[(i < Ns ? i : Ns - 1) * 10 + (n < 10 ? n : 9)], C);
   }
   T* out = fflux + (size_t)fid * NM2 * 10;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const int r = PR::crow(lane, i);
+    const int r = PA::crow(lane, i);
     if (r < NM2 && n < 10) out[r * 10 + n] = C[i];
   }
 }
@@ -1233,7 +1295,7 @@ __global__ __launch_bounds__(64) void k_time_points(StepArgs<P> a, double* out) 
   auto at = [&](int l, int j) -> T {
     const int c = j >> 4, f0 = DV::frag0(c);
     if (l >= DV::rows(j)) return T(0);
-    return a.Dz[((size_t)e * DV::NF + f0 + l / 4) * 64 + (l & 3) * 16 + (j & 15)];
+    return a.Dz[((size_t)e * DV::NF + f0 + l / 4) * 64 + 16 * (l & 3) + (j & 15)];
   };
   for (int idx = threadIdx.x; idx < 10 * L; idx += 64) {
     const int p = idx / L, l = idx - p * L;
