@@ -111,7 +111,10 @@ struct dgd_handle {
   long long steps_since_check = 0, check_every = 64;
   // sources and receivers
   int nsrc = 0, srckind = 0;
-  DevBuf s_elem, s_M6, s_dphi, s_onset, s_param, s_rhoJ;
+  std::vector<long long> src_elem, rec_elem;   // their elements
+  int npt = 0, npt_src = 0;                    // elements with either; the first npt_src have sources
+  DevBuf p_elem, p_range, p_order;             // (PointArgs)
+  DevBuf s_M6, s_dphi, s_onset, s_param, s_rhoJ;
   int nrec = 0;
   DevBuf r_elem, r_phi, seis;
   long long nrec_steps = 0, seis_cap = 0;
@@ -138,7 +141,7 @@ struct dgd_handle {
   ~dgd_handle() {
     DevBuf* all[] = {&Vpk, &Kpk, &Spk, &Fpk, &Lpk, &Ppk, &Vd, &wqd, &Pwd, &betad, &geo, &fgeo,
                      &conn, &mat, &faces, &fmap, &fflux, &U9[0], &U9[1], &Ua[0], &Ua[1], &Uz, &flag, &tmp,
-                     &s_elem, &s_M6, &s_dphi, &s_onset, &s_param, &s_rhoJ, &r_elem, &r_phi, &seis,
+                     &p_elem, &p_range, &p_order, &s_M6, &s_dphi, &s_onset, &s_param, &s_rhoJ, &r_elem, &r_phi, &seis,
                      &VTpk, &STpk, &PTpk, &KTpk, &lam[0], &lam[1], &gtr, &gmuf, &lzf, &gmu, &gcd, &adjW9,
                      &adjWa, &dlds, &seg9, &sega, &seguz, &segd, &segacc, &save9, &savea, &st9, &sta,
                      &KPpk, &ecl, &facc, &Vw, &Vt, &Kw, &Kt, &Ktw, &PXw,
@@ -394,10 +397,10 @@ dgd_status build_step_packs(dgd_handle* h) {
   using DM = Dims<N>;
   using T = typename Prec<P>::T;
   constexpr int M = MatForm<N, P>::value;
+  constexpr int MF = FaceForm<N, P>::value;
   constexpr bool X3 = M == PREC_X3;
   constexpr int L = DM::L, Q = DM::Q, Ns = DM::Ns, MT = DM::MT, NCH = DM::NCH, NST = DM::NST;
   constexpr int NT1 = (modes_upto(N - 1) + 15) / 16, Q4 = (Q + 3) / 4, NM2 = FaceModes<N>::value;
-  constexpr int MF = FaceForm<N, P>::value;
   using SL = Steps<M, L>;
   const RefData& r = h->ref;
   // row of entry j of wide step s (contractions over modes) and of a leftover step
@@ -478,15 +481,15 @@ dgd_status build_step_packs(dgd_handle* h) {
           return Ft(ff, 16 * t + n, MF == PREC_X3 ? mode(s, g, j) : 4 * s + g);
         });
   }
-  for (int s = 0; s < (Ns + 3) / 4; ++s)
-    tail(psi, [&](int n, int g) {
-      const int i = 4 * s + g;
   if constexpr (Steps<MF, L>::TAIL)
     for (int t = 0; t < 24 * NST; ++t)
       tail(ft, [&](int n, int g) { return Ft(t / NST, 16 * (t % NST) + n, 32 * Steps<MF, L>::WIDE + g); });
   if constexpr (MF == PREC_X3 && Deriv<N>::rows(16 * (Deriv<N>::NT - 1)) <= 4)
     for (int t = 0; t < 24 * NST; ++t)
       tail(ft, [&](int n, int g) { return Ft(t / NST, 16 * (t % NST) + n, g); });
+  for (int s = 0; s < (Ns + 3) / 4; ++s)
+    tail(psi, [&](int n, int g) {
+      const int i = 4 * s + g;
       return (n < NM2 && i < Ns) ? r.beta[i] * fm[n][i] : 0.0;
     });
   for (int q = 0; q < Q; ++q)
@@ -515,10 +518,10 @@ dgd_status build_step_packs(dgd_handle* h) {
   if ((st = upload(h, h->Vw, vw)) || (st = upload(h, h->Vt, vt)) || (st = upload(h, h->Kw, kw)) ||
       (st = upload(h, h->Kt, kt)) || (st = upload(h, h->Ktw, ktw)) || (st = upload(h, h->PXw, pw)) ||
       (st = upload(h, h->PXleft, pl)) || (st = upload(h, h->Rw, rw)) || (st = upload(h, h->Fst, fs)) ||
+      (st = upload(h, h->Fstt, ft)) ||
       (st = upload(h, h->Psi, psi)) || (st = upload(h, h->Psrc, ps)) || (st = upload(h, h->mixP, mp)) ||
       (st = upload(h, h->mixV, mv)))
     return st;
-      (st = upload(h, h->Fstt, ft)) ||
   h->dz_elem = (size_t)Deriv<N>::NF * 64 * sizeof(T);
   return DGD_OK;
 }
@@ -650,6 +653,36 @@ void launch_ck(dgd_handle* h, const StepArgs<P>& a) {
   });
 }
 
+// sources over [t0, t1] of the elements of one cluster (-1: all) on state buffer
+// buf, then the receivers (out != nullptr)
+template <class T>
+void launch_points(dgd_handle* h, int nsrc, double t0, double t1, int cluster, int buf, double* out) {
+  const int n = out ? h->npt : (nsrc > 0 ? h->npt_src : 0);
+  if (n == 0) return;
+  PointArgs s;
+  s.L = h->ref.L;
+  s.nsrc = nsrc;
+  s.nrec = out ? h->nrec : 0;
+  s.elem = (const long long*)h->p_elem.p;
+  s.range = (const int*)h->p_range.p;
+  s.order = (const int*)h->p_order.p;
+  s.M6 = (const double*)h->s_M6.p;
+  s.dphi = (const double*)h->s_dphi.p;
+  s.onset = (const double*)h->s_onset.p;
+  s.param = (const double*)h->s_param.p;
+  s.rhoJ = (const double*)h->s_rhoJ.p;
+  s.kind = h->srckind;
+  s.t0 = t0;
+  s.t1 = t1;
+  s.ecl = cluster >= 0 ? (const signed char*)h->ecl.p : nullptr;
+  s.only_cluster = cluster;
+  s.phi = (const double*)h->r_phi.p;
+  s.out = out;
+  timed(h, nsrc > 0 ? 2 : 3, [&] {
+    hipLaunchKernelGGL((k_points<T>), dim3(n), dim3(128), 0, h->stream, s, (T*)h->U9[buf].p);
+  });
+}
+
 template <int N, int P, class LW>
 void launch_face(dgd_handle* h, const StepArgs<P>& a, long long n, const int* list,
                  const ClusterOffsets& offs) {
@@ -725,36 +758,12 @@ dgd_status step_impl(dgd_handle* h, long long nsteps) {
       else
         ck_step<N, SP, CdmStep>(h, a);
     }
-    if (h->nsrc > 0) {
-      SrcArgs s;
-      s.nsrc = h->nsrc;
-      s.L = h->ref.L;
-      s.elem = (const long long*)h->s_elem.p;
-      s.M6 = (const double*)h->s_M6.p;
-      s.dphi = (const double*)h->s_dphi.p;
-      s.onset = (const double*)h->s_onset.p;
-      s.param = (const double*)h->s_param.p;
-      s.rhoJ = (const double*)h->s_rhoJ.p;
-      s.kind = h->srckind;
-      s.t0 = h->t;
-      s.t1 = h->t + h->dt;
-      s.ecl = nullptr;
-      s.only_cluster = -1;
-      timed(h, 2, [&] {
-        hipLaunchKernelGGL((k_sources<T>), dim3(1), dim3(3 * h->ref.L), 0, h->stream, s,
-                           (T*)h->U9[1 - h->cur].p);
-      });
-    }
+    double* rec = nullptr;
     if (h->nrec > 0) {
-      double* out = (double*)h->seis.p + (size_t)h->nrec_steps * h->nrec * 3;
-      const int nth = h->nrec * 3;
-      timed(h, 3, [&] {
-        hipLaunchKernelGGL((k_receivers<T>), dim3((nth + 63) / 64), dim3(64), 0, h->stream,
-                           h->nrec, h->ref.L, (const long long*)h->r_elem.p,
-                           (const double*)h->r_phi.p, (const T*)h->U9[1 - h->cur].p, out);
-      });
+      rec = (double*)h->seis.p + (size_t)h->nrec_steps * h->nrec * 3;
       h->nrec_steps += 1;
     }
+    launch_points<T>(h, h->nsrc, h->t, h->t + h->dt, -1, 1 - h->cur, rec);
     HIPCHK(h, hipGetLastError());
     h->cur = 1 - h->cur;
     h->t += h->dt;
@@ -804,27 +813,8 @@ dgd_status lts_advance(dgd_handle* h, int c, double t) {
   a.W9 = (T*)h->U9[h->cur].p;
   a.Wa = (double*)h->Ua[h->cur].p;
   launch_update<N, P, LW>(h, a);
-  if (h->nsrc > 0) {
-    // the point sources of this cluster's elements, over its step
-    SrcArgs sa;
-    sa.nsrc = h->nsrc;
-    sa.L = h->ref.L;
-    sa.elem = (const long long*)h->s_elem.p;
-    sa.M6 = (const double*)h->s_M6.p;
-    sa.dphi = (const double*)h->s_dphi.p;
-    sa.onset = (const double*)h->s_onset.p;
-    sa.param = (const double*)h->s_param.p;
-    sa.rhoJ = (const double*)h->s_rhoJ.p;
-    sa.kind = h->srckind;
-    sa.t0 = t;
-    sa.t1 = t + dtc;
-    sa.ecl = (const signed char*)h->ecl.p;
-    sa.only_cluster = c;
-    timed(h, 2, [&] {
-      hipLaunchKernelGGL((k_sources<T>), dim3(1), dim3(3 * h->ref.L), 0, h->stream, sa,
-                         (T*)h->U9[h->cur].p);
-    });
-  }
+  // the point sources of this cluster's elements, over its step
+  launch_points<T>(h, h->nsrc, t, t + dtc, c, h->cur, nullptr);
   HIPCHK(h, hipGetLastError());
   return DGD_OK;
 }
@@ -842,10 +832,7 @@ template <int N, int P> struct LtsFn {
       h->t += mdt;
       if (h->nrec > 0) {
         double* out = (double*)h->seis.p + (size_t)h->nrec_steps * h->nrec * 3;
-        const int nth = h->nrec * 3;
-        hipLaunchKernelGGL((k_receivers<T>), dim3((nth + 63) / 64), dim3(64), 0, h->stream, h->nrec,
-                           h->ref.L, (const long long*)h->r_elem.p, (const double*)h->r_phi.p,
-                           (const T*)h->U9[h->cur].p, out);
+        launch_points<T>(h, 0, 0.0, 0.0, -1, h->cur, out);
         h->nrec_steps += 1;
       }
       HIPCHK(h, hipGetLastError());
@@ -1438,6 +1425,9 @@ dgd_status dgd_set_mesh(dgd_handle* h, int64_t nv, const double* xyz, int64_t ne
   h->have_mat = false;
   h->nsrc = 0;
   h->nrec = 0;
+  h->src_elem.clear();
+  h->rec_elem.clear();
+  h->npt = h->npt_src = 0;
   h->nrec_steps = 0;
   return DGD_OK;
 }
@@ -1779,6 +1769,37 @@ dgd_status dgd_step_lts(dgd_handle* h, int64_t nmacro) {
   return dgd_synchronize(h);
 }
 
+// groups of point sources and receivers by element, those with sources first
+static dgd_status group_points(dgd_handle* h) {
+  h->npt = h->npt_src = 0;
+  std::map<long long, std::vector<int>> src, rec;
+  for (size_t k = 0; k < h->src_elem.size(); ++k) src[h->src_elem[k]].push_back((int)k);
+  for (size_t r = 0; r < h->rec_elem.size(); ++r) rec[h->rec_elem[r]].push_back((int)r);
+  std::vector<long long> elem;
+  std::vector<int> range, order, rorder;
+  const int ns = (int)h->src_elem.size();
+  auto add = [&](long long e, const std::vector<int>& s, const std::vector<int>& r) {
+    elem.push_back(e);
+    range.push_back((int)order.size());
+    order.insert(order.end(), s.begin(), s.end());
+    range.push_back((int)order.size());
+    range.push_back(ns + (int)rorder.size());
+    rorder.insert(rorder.end(), r.begin(), r.end());
+    range.push_back(ns + (int)rorder.size());
+  };
+  for (const auto& s : src) add(s.first, s.second, rec[s.first]);
+  for (const auto& r : rec)
+    if (!src.count(r.first)) add(r.first, {}, r.second);
+  order.insert(order.end(), rorder.begin(), rorder.end());
+  dgd_status s;
+  if ((s = upload(h, h->p_elem, elem)) || (s = upload(h, h->p_range, range)) ||
+      (s = upload(h, h->p_order, order)))
+    return s;
+  h->npt = (int)elem.size();
+  h->npt_src = (int)src.size();
+  return DGD_OK;
+}
+
 dgd_status dgd_set_point_sources(dgd_handle* h, int n, const double* xyz, const double* M6,
                                  const double* t_onset, const double* stf_param, int stf_kind) {
   if (!h) return DGD_EINVAL;
@@ -1810,10 +1831,12 @@ dgd_status dgd_set_point_sources(dgd_handle* h, int n, const double* xyz, const 
     rhoJ[k] = h->rho_h[e] * h->detJ[e];
   }
   dgd_status s;
-  if ((s = upload(h, h->s_elem, elem)) || (s = upload(h, h->s_M6, m6)) ||
+  if ((s = upload(h, h->s_M6, m6)) ||
       (s = upload(h, h->s_dphi, dphi)) || (s = upload(h, h->s_onset, on)) ||
       (s = upload(h, h->s_param, par)) || (s = upload(h, h->s_rhoJ, rhoJ)))
     return s;
+  h->src_elem = std::move(elem);
+  if ((s = group_points(h))) return s;
   h->nsrc = n;
   h->srckind = stf_kind;
   return DGD_OK;
@@ -1836,6 +1859,8 @@ dgd_status dgd_set_receivers(dgd_handle* h, int nrec, const double* xyz) {
   }
   dgd_status s;
   if ((s = upload(h, h->r_elem, elem)) || (s = upload(h, h->r_phi, phi))) return s;
+  h->rec_elem = std::move(elem);
+  if ((s = group_points(h))) return s;
   h->nrec = nrec;
   h->nrec_steps = 0;
   h->seis.release();

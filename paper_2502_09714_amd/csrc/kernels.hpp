@@ -1034,9 +1034,12 @@ __device__ inline double stf_G(int kind, double tau, double p) {
   return 0.5 * (tau * (1.0 + erf(tau / p)) + p * exp(-tau * tau / (p * p)) / sqrt(M_PI));
 }
 
-struct SrcArgs {
-  int nsrc, L;
-  const long long* elem;   // [nsrc]
+// Point sources and receivers, grouped by the element they lie in.
+struct PointArgs {
+  int L, nsrc, nrec;       // nsrc = 0, nrec = 0: not applied, not recorded
+  const long long* elem;   // [group]
+  const int* range;        // [group][4]  its sources' and its receivers' range in order
+  const int* order;        // sources of all groups, then receivers of all groups
   const double* M6;        // [nsrc][6]
   const double* dphi;      // [nsrc][3][L]  dphi_l/dx_d at the source
   const double* onset;     // [nsrc]
@@ -1046,35 +1049,46 @@ struct SrcArgs {
   double t0, t1;
   const signed char* ecl;  // cluster of every element, with only_cluster >= 0
   int only_cluster;        // -1: every source; else those in elements of this cluster
+  const double* phi;       // [nrec][L]  basis at the receivers
+  double* out;             // [nrec][3]
 };
 
+// Sources of an element, in the order they were given, then its receivers: one
+// workgroup per element.  (Two launches with all sources in one workgroup, one
+// after the other, took 65 + 16 us for 64 sources and 64 receivers, of a step of
+// 5.9 ms at 311040 elements of degree 4, and 6 + 7 us of one of 56 us at 3780 elements
+// of degree 3.)
 template <class T>
-__global__ void k_sources(SrcArgs s, T* U9) {
-  const int idx = threadIdx.x;   // (i, l)
-  if (idx >= 3 * s.L) return;
-  const int i = idx / s.L, l = idx % s.L;
-  for (int k = 0; k < s.nsrc; ++k) {
-    if (s.only_cluster >= 0 && s.ecl[s.elem[k]] != s.only_cluster) continue;
-    const double dG = stf_G(s.kind, s.t1 - s.onset[k], s.param[k]) -
-                      stf_G(s.kind, s.t0 - s.onset[k], s.param[k]);
-    const double fac = dG / s.rhoJ[k];
-    double v = 0.0;
-    for (int j = 0; j < 3; ++j) v += s.M6[k * 6 + sym_idx(i, j)] * s.dphi[(k * 3 + j) * s.L + l];
-    T* dst = U9 + (s.elem[k] * 9 + 6 + i) * s.L + l;
-    *dst = (T)((double)*dst + fac * v);
+__global__ __launch_bounds__(128) void k_points(PointArgs s, T* U9) {
+  const long long e = s.elem[blockIdx.x];
+  const int* rg = s.range + blockIdx.x * 4;
+  if (s.nsrc > 0 && (s.only_cluster < 0 || s.ecl[e] == s.only_cluster)) {
+    const int idx = threadIdx.x;   // (i, l)
+    if (idx < 3 * s.L && rg[0] < rg[1]) {
+      const int i = idx / s.L, l = idx % s.L;
+      T* dst = U9 + (e * 9 + 6 + i) * s.L + l;
+      T u = *dst;
+      for (int n = rg[0]; n < rg[1]; ++n) {
+        const int k = s.order[n];
+        const double dG = stf_G(s.kind, s.t1 - s.onset[k], s.param[k]) -
+                          stf_G(s.kind, s.t0 - s.onset[k], s.param[k]);
+        const double fac = dG / s.rhoJ[k];
+        double v = 0.0;
+        for (int j = 0; j < 3; ++j) v += s.M6[k * 6 + sym_idx(i, j)] * s.dphi[(k * 3 + j) * s.L + l];
+        u = (T)((double)u + fac * v);
+      }
+      *dst = u;
+    }
   }
-}
-
-template <class T>
-__global__ void k_receivers(int nrec, int L, const long long* elem, const double* phi,
-                            const T* U9, double* out) {
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= nrec * 3) return;
-  const int r = idx / 3, c = idx % 3;
-  const T* u = U9 + (elem[r] * 9 + 6 + c) * L;
-  double s = 0.0;
-  for (int l = 0; l < L; ++l) s += phi[r * L + l] * (double)u[l];
-  out[idx] = s;
+  if (s.nrec == 0) return;
+  __syncthreads();
+  for (int idx = threadIdx.x; idx < 3 * (rg[3] - rg[2]); idx += blockDim.x) {
+    const int r = s.order[rg[2] + idx / 3], c = idx % 3;
+    const T* u = U9 + (e * 9 + 6 + c) * s.L;
+    double v = 0.0;
+    for (int l = 0; l < s.L; ++l) v += s.phi[r * s.L + l] * (double)u[l];
+    s.out[r * 3 + c] = v;
+  }
 }
 
 // L2 projection of point values [E][Q][10] onto the modes (FP64)
