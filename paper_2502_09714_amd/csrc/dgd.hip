@@ -74,9 +74,9 @@ struct dgd_handle {
   RefData ref;
   size_t tsize = 8;  // bytes of the working type
   // reference data on the device
-  DevBuf Vpk, Kpk, Spk, Fpk, Lpk, Ppk, Vd, wqd, Pwd, betad, KPpk;
+  DevBuf Vpk, Kpk, Spk, Fpk, Lpk, Ppk, Vd, wqd, Pwd, betad;
   // Cauchy-Kovalevskaya step (step_kernels.hpp)
-  DevBuf Vw, Vt, Kw, Kt, Ktw, PXw, PXleft, Rw, Fst, Fstt, Psi, Psrc, mixP, mixV;
+  DevBuf Vw, Vt, Kw, Kt, Ktw, PXw, PXa, PXleft, Rw, Fst, Fstt, Psi, Psrc, mixP, mixV;
   size_t dz_elem = 0;     // bytes of one element's time derivatives
   double points_dt = 0.0;      // step of the last step's derivatives
   bool points_in_uz = false;   // the last step left time-point states in Uz, not derivatives in Dz
@@ -122,7 +122,7 @@ struct dgd_handle {
   // discrete adjoint: transposed reference data, adjoint state, checkpoints
   DevBuf VTpk, STpk, PTpk, KTpk;
   // FP32 forward operators of a split-BF16 handle, for its FP32 adjoint
-  DevBuf Vpk32, Kpk32, Spk32, Fpk32, Lpk32, Ppk32, KPpk32;
+  DevBuf Vpk32, Kpk32, Spk32, Fpk32, Lpk32, Ppk32;
   DevBuf lam[2], gtr, gmuf, lzf, gmu, gcd, adjW9, adjWa, dlds, seg9, sega, seguz, segd, segacc, save9, savea;
   DevBuf st9, sta;               // the state U^n handed to dgd_adjoint_step, working precision
   void* uz_override = nullptr;   // time-point states of the step being replayed
@@ -144,9 +144,8 @@ struct dgd_handle {
                      &p_elem, &p_range, &p_order, &s_M6, &s_dphi, &s_onset, &s_param, &s_rhoJ, &r_elem, &r_phi, &seis,
                      &VTpk, &STpk, &PTpk, &KTpk, &lam[0], &lam[1], &gtr, &gmuf, &lzf, &gmu, &gcd, &adjW9,
                      &adjWa, &dlds, &seg9, &sega, &seguz, &segd, &segacc, &save9, &savea, &st9, &sta,
-                     &KPpk, &ecl, &facc, &Vw, &Vt, &Kw, &Kt, &Ktw, &PXw,
-                     &PXleft, &Rw, &Fst, &Fstt, &Psi, &Psrc, &mixP, &mixV, &Dz, &Vpk32, &Kpk32, &Spk32, &Fpk32, &Lpk32, &Ppk32,
-                     &KPpk32};
+                     &ecl, &facc, &Vw, &Vt, &Kw, &Kt, &Ktw, &PXw, &PXa,
+                     &PXleft, &Rw, &Fst, &Fstt, &Psi, &Psrc, &mixP, &mixV, &Dz, &Vpk32, &Kpk32, &Spk32, &Fpk32, &Lpk32, &Ppk32};
     for (DevBuf* b : all) b->release();
     for (DevBuf& b : ck9) b.release();
     for (DevBuf& b : cka) b.release();
@@ -248,7 +247,7 @@ dgd_status build_packed(dgd_handle* h) {
   const RefData& r = h->ref;
   constexpr int KS = Prec<P>::KS, L = DM::L, Q = DM::Q, Ns = DM::Ns;
   constexpr int KPL = round_up(L, KS), KSL = KPL / KS, KPN = round_up(Ns, KS), KSN = KPN / KS;
-  std::vector<AF> v, k, s, f, lf, kp;
+  std::vector<AF> v, k, s, f, lf;
   for (int c = 0; c < DM::NCH; ++c)
     append(v, pack_A<P>(
                   [&](int m, int kk) {
@@ -270,12 +269,6 @@ dgd_status build_packed(dgd_handle* h) {
                       return (m < L && q < Q) ? r.Sw[((size_t)e * L + m) * Q + q] : 0.0;
                     },
                     DM::MT, 64 / KS));
-      append(kp, pack_A<P>(
-                     [&](int m, int kk) {
-                       int q = 64 * c + kk;
-                       return (m < L && q < Q) ? r.KP[((size_t)e * L + m) * Q + q] : 0.0;
-                     },
-                     DM::MT, 64 / KS));
     }
   for (int ff = 0; ff < 4; ++ff)
     for (int sp = 0; sp < 6; ++sp) {
@@ -301,8 +294,7 @@ dgd_status build_packed(dgd_handle* h) {
                    DM::MT, KSQA));
   dgd_status st;
   if ((st = upload(h, h->Vpk, v)) || (st = upload(h, h->Kpk, k)) || (st = upload(h, h->Spk, s)) ||
-      (st = upload(h, h->Fpk, f)) || (st = upload(h, h->Lpk, lf)) || (st = upload(h, h->Ppk, pp)) ||
-      (st = upload(h, h->KPpk, kp)))
+      (st = upload(h, h->Fpk, f)) || (st = upload(h, h->Lpk, lf)) || (st = upload(h, h->Ppk, pp)))
     return st;
   if constexpr (P != PREC_BF16) {
     // transposed operators of the discrete adjoint
@@ -413,7 +405,7 @@ dgd_status build_step_packs(dgd_handle* h) {
   auto Ft = [&](int ff, int i, int l) {
     return (i < Ns && l < L) ? r.F[((size_t)ff * Ns + i) * L + l] : 0.0;
   };
-  std::vector<char> vw, kw, ktw, pw, rw, fs;
+  std::vector<char> vw, kw, ktw, pw, pa, rw, fs;
   std::vector<T> vt, kt, pl, ft, psi, ps((size_t)Q4 * L * 4, T(0));
   auto tail = [](std::vector<T>& out, auto val) {
     for (int lane = 0; lane < 64; ++lane) out.push_back((T)val(lane & 15, lane >> 4));
@@ -440,11 +432,14 @@ dgd_status build_step_packs(dgd_handle* h) {
     });
   for (int c = 0; c < NCH; ++c)
     for (int s = 0; s < (X3 ? 2 : 16); ++s)
-      for (int t = 0; t < ProjTiles<N>::MTP; ++t)
-        append_frag<M>(pw, [&](int n, int g, int j) {
+      for (int t = 0; t < MT; ++t) {
+        auto val = [&](int n, int g, int j) {
           const int q = 64 * c + (X3 ? 32 * s + 8 * g + j : 16 * (s / 4) + 4 * g + s % 4);
           return Pw(mperm<N, M>(t, n), q);
-        });
+        };
+        append_frag<M>(pa, val);
+        if (t < ProjTiles<N>::MTP) append_frag<M>(pw, val);
+      }
   for (int c = 0; c < NCH; ++c)
     for (int k = 0; k < ProjTiles<N>::LEFT; ++k)
       for (int q = 0; q < 64; ++q) pl.push_back((T)Pw(16 * ProjTiles<N>::MTP + k, 64 * c + q));
@@ -517,6 +512,7 @@ dgd_status build_step_packs(dgd_handle* h) {
   dgd_status st;
   if ((st = upload(h, h->Vw, vw)) || (st = upload(h, h->Vt, vt)) || (st = upload(h, h->Kw, kw)) ||
       (st = upload(h, h->Kt, kt)) || (st = upload(h, h->Ktw, ktw)) || (st = upload(h, h->PXw, pw)) ||
+      (st = upload(h, h->PXa, pa)) ||
       (st = upload(h, h->PXleft, pl)) || (st = upload(h, h->Rw, rw)) || (st = upload(h, h->Fst, fs)) ||
       (st = upload(h, h->Fstt, ft)) ||
       (st = upload(h, h->Psi, psi)) || (st = upload(h, h->Psrc, ps)) || (st = upload(h, h->mixP, mp)) ||
@@ -625,6 +621,7 @@ StepArgs<P> make_args(dgd_handle* h) {
   a.PXw = h->PXw.p;
   a.PXleft = (const T*)h->PXleft.p;
   a.Rw = h->Rw.p;
+  a.PXa = h->PXa.p;
   a.Fst = h->Fst.p;
   a.Fstt = (const T*)h->Fstt.p;
   a.Psi = (const T*)h->Psi.p;
@@ -705,19 +702,22 @@ void launch_update(dgd_handle* h, const StepArgs<P>& a) {
 }
 
 // one step with the Picard predictor: time-point states through HBM
-template <int N, int P, class LW>
+template <int N, int P, class LW, class LS>
 void picard_step(dgd_handle* h, const StepArgs<P>& a) {
   using T = typename Prec<P>::T;
   const dim3 grid((unsigned)(8 * ((h->ne + 7) / 8))), block(64);
   const dim3 fgrid((unsigned)(8 * ((h->nfaces + 7) / 8)));
-  PicardArgs<P> pa;
-  pa.KPpk = (const typename Prec<P>::AF*)h->KPpk.p;
+  constexpr int SP = StepPrec<P>::value;
+  using TB = PicardTabs<N, SP>;
+  const StepArgs<SP> sa = make_args<N, SP>(h);
+  PicardArgs<SP> pa;
   pa.iters = h->picard_iters > 0 ? h->picard_iters : N + 1;
   for (int z = 0; z < 8; ++z)
     for (int j = 0; j < 8; ++j)
       pa.om[z][j] = (z < h->ref.Nt && j < h->ref.Nt) ? (T)h->ref.Om[z * h->ref.Nt + j] : T(0);
   timed(h, 0, [&] {
-    hipLaunchKernelGGL((k_predict_picard<N, P, LW>), grid, block, 0, h->stream, a, pa);
+    hipLaunchKernelGGL((k_picard<N, SP, LS>), element_grid(h, h->ne, TB::wpb), dim3(64 * TB::wpb), 0,
+                       h->stream, sa, pa);
   });
   timed(h, 9, [&] { hipLaunchKernelGGL((k_volume<N, P, LW>), grid, block, 0, h->stream, a); });
   timed(h, 1, [&] {
@@ -747,9 +747,9 @@ dgd_status step_impl(dgd_handle* h, long long nsteps) {
     if (h->predictor == 1) {
       const StepArgs<P> a = make_args<N, P>(h);
       if (ivm)
-        picard_step<N, P, IvmLaw>(h, a);
+        picard_step<N, P, IvmLaw, IvmStep>(h, a);
       else
-        picard_step<N, P, CdmLaw>(h, a);
+        picard_step<N, P, CdmLaw, CdmStep>(h, a);
     } else {
       constexpr int SP = StepPrec<P>::value;
       const StepArgs<SP> a = make_args<N, SP>(h);
@@ -900,9 +900,9 @@ size_t lam_elems(const dgd_handle* h) { return (size_t)h->ne * adj_kpl(h) * 16; 
 // come with them.
 dgd_status ensure_adjoint_packs(dgd_handle* h) {
   if (h->prec != DGD_BF16 || h->Vpk32.p) return DGD_OK;
-  DevBuf* fw[] = {&h->Vpk, &h->Kpk, &h->Spk, &h->Fpk, &h->Lpk, &h->Ppk, &h->KPpk};
-  DevBuf* f32[] = {&h->Vpk32, &h->Kpk32, &h->Spk32, &h->Fpk32, &h->Lpk32, &h->Ppk32, &h->KPpk32};
-  for (int i = 0; i < 7; ++i) std::swap(*fw[i], *f32[i]);
+  DevBuf* fw[] = {&h->Vpk, &h->Kpk, &h->Spk, &h->Fpk, &h->Lpk, &h->Ppk};
+  DevBuf* f32[] = {&h->Vpk32, &h->Kpk32, &h->Spk32, &h->Fpk32, &h->Lpk32, &h->Ppk32};
+  for (int i = 0; i < 6; ++i) std::swap(*fw[i], *f32[i]);
   const int kpl = h->kpl;
   dgd_status s = DGD_EINVAL;
   switch (h->N) {
@@ -913,7 +913,7 @@ dgd_status ensure_adjoint_packs(dgd_handle* h) {
     default: break;
   }
   h->kpl = kpl;
-  for (int i = 0; i < 7; ++i) std::swap(*fw[i], *f32[i]);
+  for (int i = 0; i < 6; ++i) std::swap(*fw[i], *f32[i]);
   if (s) h->Vpk32.release();
   return s;
 }

@@ -182,14 +182,6 @@ RefData build_reference(int N) {
         basis_eval(N, xi, phi.data(), nullptr);
         for (int l = 0; l < L; ++l) r.F[(((size_t)f * 6 + s) * Ns + i) * L + l] = phi[l];
       }
-  // strong-form derivative of a projected field: KP[e] = K[e] Pw
-  r.KP.assign((size_t)3 * L * Q, 0.0);
-  for (int e = 0; e < 3; ++e)
-    for (int k = 0; k < L; ++k)
-      for (int l = 0; l < L; ++l) {
-        const double kk = r.K[((size_t)e * L + k) * L + l];
-        for (int q = 0; q < Q; ++q) r.KP[((size_t)e * L + k) * Q + q] += kk * r.Pw[(size_t)l * Q + q];
-      }
   // Om[z][j] = int_0^{tau_z} l_j(s) ds for the Lagrange polynomials l_j of the
   // time points (monomial coefficients built factor by factor)
   r.Om.assign((size_t)n * n, 0.0);

@@ -311,6 +311,118 @@ __device__ inline void stream(Ld ld, Use use) {
   }
 }
 
+// state of an element as row operand: quantity p in lane n, modes in registers
+template <int N, int P, class T, int NR>
+__device__ inline void load_state(const StepArgs<P>& a, long long e, T (&d)[NR], int lane) {
+  using SL = Steps<MatForm<N, P>::value, Dims<N>::L>;
+  constexpr int L = Dims<N>::L;
+  const int g = lane >> 4, p = qperm<T>(lane & 15);
+  const T* u = a.U9 + (e * 9 + (p < 9 ? p : 8)) * L;
+#pragma unroll
+  for (int r = 0; r < NR; ++r) {
+    const int l = SL::row(r, g);
+    d[r] = u[l < L ? l : L - 1];
+  }
+  if (p == 9) {
+    const double* ua = a.Ua + e * L;
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      const int l = SL::row(r, g);
+      d[r] = (T)ua[l < L ? l : L - 1];
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < NR; ++r)
+    if (p > 9 || SL::row(r, g) >= L) d[r] = T(0);
+}
+
+// values at the 64 points of chunk c: the product's rows are quantities, its
+// columns 16 points; a transposition over the lane groups gives every lane one
+// point
+template <int N, int P, int PD, class T, int NR, class AF>
+__device__ inline void nodal(const T (&d)[NR], const AF* dw, const void* Vw, const T* Vt, int c,
+                             T (&u)[12], int lane) {
+  constexpr int M = MatForm<N, P>::value;
+  using PR = Prec<M>;
+  using SL = Steps<M, Dims<N>::L>;
+  constexpr int WL = SL::WIDE;
+  typename PR::Acc C[4];
+  zero_C<M, 4>(C);
+  stream<PD, 4 * WL, AF>(
+      [&](int k) { return load_frag<M>(Vw, (c * 4 + k % 4) * WL + k / 4, lane); },
+      [&](int k, const AF& b) { C[k % 4] = PR::mma(dw[k / 4], b, C[k % 4]); });
+  if constexpr (SL::TAIL) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t) C[t] = Prec<P>::mma(d[NR - 1], Vt[(c * 4 + t) * 64 + lane], C[t]);
+  }
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    T x0 = C[0][i], x1 = C[1][i], x2 = C[2][i], x3 = C[3][i];
+    transpose4(x0, x1, x2, x3);
+    u[4 * i] = x0;
+    u[4 * i + 1] = x1;
+    u[4 * i + 2] = x2;
+    u[4 * i + 3] = x3;
+  }
+}
+
+// mix the quantities of R modes (quantities in registers; As: the matrices of the
+// three directions), then contract with K^e: NTO tiles out, modes in rows.  DAM:
+// tiles past the modes of degree < N hold the damage row (register 2) only.
+template <int N, int P, int R, int NTO, bool DAM, int PD, class Acc, class T>
+__device__ inline void mix_contract(const Acc* in, const T (&As)[3][3], const void* Kw, const T* Kt,
+                                    Acc* out, int lane) {
+  constexpr int M = MatForm<N, P>::value;
+  using PR = Prec<M>;
+  using PA = Prec<P>;
+  using AF = typename PR::AF;
+  using ST = Steps<M, R>;
+  constexpr int NTI = (R + 15) / 16, R1 = modes_upto(N - 1), NT1 = (R1 + 15) / 16;
+  constexpr int WL = Steps<M, Dims<N>::L>::WIDE;
+  constexpr auto list = k_list<N, M, R, NTO>();
+  constexpr int NY = ST::NREG > 4 * NTI ? ST::NREG : 4 * NTI;
+#pragma unroll
+  for (int t = 0; t < NTO; ++t) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) out[t][k] = 0;
+  }
+  T Y[3][NY];
+  AF Yw[3][ST::WIDE > 0 ? ST::WIDE : 1];
+#pragma unroll
+  for (int ee = 0; ee < 3; ++ee) {
+#pragma unroll
+    for (int k = 0; k < NY; ++k) Y[ee][k] = T(0);
+#pragma unroll
+    for (int t = 0; t < NTI; ++t) {
+      Acc y;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) y[k] = 0;
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        if (DAM && 16 * t >= R1 && i < 2) continue;
+        y = PA::mma(in[t][i], As[ee][i], y);
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k) Y[ee][4 * t + k] = y[k];
+    }
+#pragma unroll
+    for (int s = 0; s < ST::WIDE; ++s) Yw[ee][s] = wide_op<M>(Y[ee], s);
+  }
+  stream<PD, list.n, AF>(
+      [&](int k) { return load_frag<M>(Kw, (list.e[k] * NT1 + list.t[k]) * WL + list.s[k], lane); },
+      [&](int k, const AF& aa) {
+        Acc& z = out[list.t[k]];
+        z = PR::mma(aa, Yw[list.e[k]][list.s[k]], z);
+      });
+  if constexpr (ST::TAIL) {
+#pragma unroll
+    for (int ee = 0; ee < 3; ++ee)
+#pragma unroll
+      for (int t = 0; t < NTO; ++t)
+        out[t] = PA::mma(Kt[(ee * NT1 + t) * 64 + lane], Y[ee][ST::NREG - 1], out[t]);
+  }
+}
+
 template <int N, int P> struct CkLDS {
   using T = typename Prec<P>::T;
   // fragments of the derivative matrix, padded by 16 bytes each: a column's
@@ -353,27 +465,8 @@ __device__ inline void ck_element(const StepArgs<P>& a, long long e, CkLDS<N, P>
   const int n = lane & 15, g = lane >> 4;
   const int p = qperm<T>(n);
 
-  // D^0 as the row operand: quantity p in lane n, modes in registers
   T d0[NR];
-  {
-    const T* u = a.U9 + (e * 9 + (p < 9 ? p : 8)) * L;
-#pragma unroll
-    for (int r = 0; r < NR; ++r) {
-      const int l = SL::row(r, g);
-      d0[r] = u[l < L ? l : L - 1];
-    }
-    if (p == 9) {
-      const double* ua = a.Ua + e * L;
-#pragma unroll
-      for (int r = 0; r < NR; ++r) {
-        const int l = SL::row(r, g);
-        d0[r] = (T)ua[l < L ? l : L - 1];
-      }
-    }
-#pragma unroll
-    for (int r = 0; r < NR; ++r)
-      if (p > 9 || SL::row(r, g) >= L) d0[r] = T(0);
-  }
+  load_state<N, P>(a, e, d0, lane);
   const Law<T> law{a.amax, a.smin};
   const StepMat<T> m = LW::constants(load_mat<T>(a.mat + e * 8));
   constexpr int FS = CkLDS<N, P>::FS, VW = 16 / sizeof(T);
@@ -415,26 +508,8 @@ __device__ inline void ck_element(const StepArgs<P>& a, long long e, CkLDS<N, P>
   for (int k = 0; k < LW::NACC; ++k) acc[k] = T(0);
 #pragma unroll 1
   for (int c = 0; c < NCH; ++c) {
-    Acc C[4];
-    zero_C<M, 4>(C);
-    stream<PD, 4 * WL, AF>(
-        [&](int k) { return load_frag<M>(Vw, (c * 4 + k % 4) * WL + k / 4, lane); },
-        [&](int k, const AF& b) { C[k % 4] = PR::mma(d0w[k / 4], b, C[k % 4]); });
-    if constexpr (SL::TAIL) {
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-        C[t] = PA::mma(d0[NR - 1], Vt[(c * 4 + t) * 64 + lane], C[t]);
-    }
     T u[12];
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      T x0 = C[0][i], x1 = C[1][i], x2 = C[2][i], x3 = C[3][i];
-      transpose4(x0, x1, x2, x3);
-      u[4 * i] = x0;
-      u[4 * i + 1] = x1;
-      u[4 * i + 2] = x2;
-      u[4 * i + 3] = x3;
-    }
+    nodal<N, P, PD>(d0, d0w, Vw, Vt, c, u, lane);
     const int q = 64 * c + lane;
     const T w = q < Q ? (T)a.wq[q < Q ? q : 0] * a.inv_wsum : T(0);
     const auto v = LW::invariants(u, law);
@@ -510,53 +585,6 @@ __device__ inline void ck_element(const StepArgs<P>& a, long long e, CkLDS<N, P>
 #pragma unroll
         for (int t = 0; t < NTO; ++t) out[t] = PA::mma(As[ee][i], Z[ee][t][i], out[t]);
   };
-  // mix, then contract R modes: NTO tiles out, modes in rows
-  auto mix_contract = [&](const Acc* in, auto rows, auto nto, Acc* out) {
-    constexpr int R = decltype(rows)::value, NTO = decltype(nto)::value;
-    constexpr int NTI = (R + 15) / 16;
-    using ST = Steps<M, R>;
-    constexpr auto list = k_list<N, M, R, NTO>();
-    constexpr int NY = ST::NREG > 4 * NTI ? ST::NREG : 4 * NTI;
-#pragma unroll
-    for (int t = 0; t < NTO; ++t) {
-#pragma unroll
-      for (int k = 0; k < 4; ++k) out[t][k] = 0;
-    }
-    T Y[3][NY];
-    AF Yw[3][ST::WIDE > 0 ? ST::WIDE : 1];
-#pragma unroll
-    for (int ee = 0; ee < 3; ++ee) {
-#pragma unroll
-      for (int k = 0; k < NY; ++k) Y[ee][k] = T(0);
-#pragma unroll
-      for (int t = 0; t < NTI; ++t) {
-        Acc y;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) y[k] = 0;
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-          // tiles past the wave rows of order 1 hold the damage row (i = 2) only
-          if (16 * t >= R1 && i < 2) continue;
-          y = PA::mma(in[t][i], As[ee][i], y);
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) Y[ee][4 * t + k] = y[k];
-      }
-#pragma unroll
-      for (int s = 0; s < ST::WIDE; ++s) Yw[ee][s] = wide_op<M>(Y[ee], s);
-    }
-    stream<PD, list.n, AF>([&](int k) { return kfrag(list.e[k], list.t[k], list.s[k]); },
-                           [&](int k, const AF& aa) {
-                             Acc& z = out[list.t[k]];
-                             z = PR::mma(aa, Yw[list.e[k]][list.s[k]], z);
-                           });
-    if constexpr (ST::TAIL) {
-#pragma unroll
-      for (int ee = 0; ee < 3; ++ee)
-#pragma unroll
-        for (int t = 0; t < NTO; ++t) out[t] = PA::mma(ktail(ee, t), Y[ee][ST::NREG - 1], out[t]);
-    }
-  };
   // quantities-in-registers result of order o to the derivative matrix
   auto put_regs = [&](const Acc* R, int o, int rows, int nt) {
 #pragma unroll
@@ -596,7 +624,7 @@ __device__ inline void ck_element(const StepArgs<P>& a, long long e, CkLDS<N, P>
     }
     // order 2: the damage row brings all modes, degree <= N - 1 out
     Acc D2[NT1];
-    mix_contract(D1, std::integral_constant<int, L>{}, std::integral_constant<int, NT1>{}, D2);
+    mix_contract<N, P, L, NT1, true, PD>(D1, As, Kw, Kt, D2, lane);
     put_lanes(D2, 2, R1);
     if constexpr (N >= 3) {
       using S2 = Steps<M, R1>;
@@ -612,7 +640,7 @@ __device__ inline void ck_element(const StepArgs<P>& a, long long e, CkLDS<N, P>
       put_regs(D3, 3, R3, 1);
       if constexpr (N >= 4) {
         Acc D4[1];
-        mix_contract(D3, std::integral_constant<int, R3>{}, std::integral_constant<int, 1>{}, D4);
+        mix_contract<N, P, R3, 1, true, PD>(D3, As, Kw, Kt, D4, lane);
         put_lanes(D4, 4, R4);
       }
     }
@@ -1091,6 +1119,219 @@ __attribute__((amdgpu_waves_per_eu(StepTune<N, P>::w_update))) void k_update(
     UpdLDS<N, P>& S = *(UpdLDS<N, P>*)smem;
     for_elements(a, 1, [&](long long e, int lane) {
       update_element<N, P, LW>(a, e, fmap, fflux, S, a.Vw, a.Vt, a.PXw, a.Ktw, lane);
+    });
+  }
+}
+
+// ---- Picard-iteration predictor --------------------------------------------------
+// The alternative to the linearised Cauchy-Kovalevskaya prediction named in the
+// paper's Discussion (Section 5.1).  The element-local evolution that the
+// recursion differentiates, taken in strong form without linearisation,
+//   dU/dt = R(U) = - sum_e K^e P G^e(U) + P r(U),
+//   G^e = sum_d Theta^-1_ed F^d(V U) at the volume points, P the projection,
+// is solved on the Gauss-Legendre time points by Picard iteration of the
+// collocation equations U_z = U^n + dt sum_j Om_zj R(U_j), from U_z = U^n.
+template <int P> struct PicardArgs {
+  using T = typename Prec<P>::T;
+  int iters;
+  T om[8][8];
+};
+
+template <int N, int P> struct PicardLDS {
+  using T = typename Prec<P>::T;
+  static constexpr int RS = 64 + 16 / sizeof(T);
+  alignas(16) T X[10 * RS];       // velocity, stress and damage rate at the points of one chunk
+  T al[64];                       // projected damage rate
+};
+
+template <int N, int P> struct PicardTabs {     // bytes of the matrices in LDS, launch shape
+  static constexpr int M = MatForm<N, P>::value;
+  static constexpr bool staged = M == PREC_X3;
+  static constexpr int vw = CkTabs<N, P>::vw, vt = CkTabs<N, P>::vt, kw = CkTabs<N, P>::kw,
+                       kt = CkTabs<N, P>::kt;
+  static constexpr int pw = Dims<N>::NCH * (M == PREC_X3 ? 2 : 16) * Dims<N>::MT * FragBytes<M>::value;
+  static constexpr int all = staged ? vw + vt + kw + kt + pw : 0;
+  static constexpr int wpb = !staged ? 1 : (N >= 4 ? 8 : 12);
+  static constexpr int waves = staged ? wpb / 4 : (P == PREC_F64 && N >= 4 ? 1 : 2);
+  static constexpr int bytes = all + wpb * (int)sizeof(PicardLDS<N, P>);
+  static_assert(bytes <= 163840, "the workgroup's LDS");
+};
+
+// The iterate and the next one stay in registers as row operands.  The flux is
+// linear in velocity and stress, so they and the damage rate are projected once
+// per evaluation, mixed as in the corrector and contracted with K^e on modes (as
+// even orders of the recursion).  A contraction of the 9 fluxes of each reference
+// direction with K^e P over the points, the states in LDS, took 730 us for 10368
+// elements of degree 3, against 265 us.
+template <int N, int P, class LW>
+__device__ inline void picard_element(const StepArgs<P>& a, const PicardArgs<P>& pa, long long e,
+                                      PicardLDS<N, P>& S, const void* Vw,
+                                      const typename Prec<P>::T* Vt, const void* Kw,
+                                      const typename Prec<P>::T* Kt, const void* Pw, int lane) {
+  constexpr int M = MatForm<N, P>::value;
+  using PR = Prec<M>;
+  using PA = Prec<P>;
+  using T = typename PA::T;
+  using AF = typename PR::AF;
+  using Acc = typename PR::Acc;
+  using DM = Dims<N>;
+  constexpr int L = DM::L, Nt = DM::Nt, NCH = DM::NCH, MT = DM::MT;
+  using SL = Steps<M, L>;
+  constexpr int WL = SL::WIDE, NR = SL::NREG, PD = M == PREC_X3 ? 1 : 4;
+  constexpr int NT1 = (modes_upto(N - 1) + 15) / 16, RS = PicardLDS<N, P>::RS;
+  const int n = lane & 15, g = lane >> 4;
+  const int p = qperm<T>(n);
+  const Law<T> law{a.amax, a.smin};
+  const StepMat<T> m = LW::constants(load_mat<T>(a.mat + e * 8));
+  T u0[NR], U[Nt][NR], W[Nt][NR];
+  load_state<N, P>(a, e, u0, lane);
+#pragma unroll
+  for (int z = 0; z < Nt; ++z)
+#pragma unroll
+    for (int r = 0; r < NR; ++r) U[z][r] = u0[r];
+  // -sum_d Theta^-1_ed W_d: rows p (lanes), columns 4 i + g of (v, sigma, rate)
+  T As[3][3];
+  {
+    const T rs = p >= 6 ? -m.ir : T(-1);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      T w[3];
+#pragma unroll
+      for (int d = 0; d < 3; ++d) w[d] = rs * a.mixV[(i * 3 + d) * 64 + lane];
+#pragma unroll
+      for (int ee = 0; ee < 3; ++ee)
+        As[ee][i] = (T)a.geo[e * 16 + ee * 3] * w[0] + (T)a.geo[e * 16 + ee * 3 + 1] * w[1] +
+                    (T)a.geo[e * 16 + ee * 3 + 2] * w[2];
+    }
+  }
+  const T dt = (T)a.dt;
+#pragma unroll 1
+  for (int it = 0; it < pa.iters; ++it) {
+#pragma unroll
+    for (int z = 0; z < Nt; ++z)
+#pragma unroll
+      for (int r = 0; r < NR; ++r) W[z][r] = u0[r];
+#pragma unroll 1
+    for (int jt = 0; jt < Nt; ++jt) {
+      // (U[0] is the state at time point jt: the iterate rotates)
+      Acc X[MT];
+      zero_C<M, MT>(X);
+      {
+        AF uw[WL > 0 ? WL : 1];
+#pragma unroll
+        for (int s = 0; s < WL; ++s) uw[s] = wide_op<M>(U[0], s);
+#pragma unroll 1
+        for (int c = 0; c < NCH; ++c) {
+          T u[12], sig[6];
+          nodal<N, P, PD>(U[0], uw, Vw, Vt, c, u, lane);
+          const auto v = LW::invariants(u, law);
+          LW::stress(v, u, m, sig);
+          wave_sync();
+#pragma unroll
+          for (int k = 0; k < 3; ++k) S.X[k * RS + lane] = u[6 + k];
+#pragma unroll
+          for (int k = 0; k < 6; ++k) S.X[(3 + k) * RS + lane] = sig[k];
+          S.X[9 * RS + lane] = LW::rate(v, m);
+          wave_sync();
+          // projection: quantities in rows, modes in columns
+          typedef T T4 __attribute__((ext_vector_type(4), aligned(16)));
+          const T* xs = S.X + (p < 10 ? p : 9) * RS;
+          if constexpr (M == PREC_X3) {
+            AF xw[2];
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+              const T4 lo = *(const T4*)(xs + 32 * s + 8 * g), hi = *(const T4*)(xs + 32 * s + 8 * g + 4);
+              const T v8[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+              xw[s] = split8(v8);
+            }
+            stream<1, 2 * MT, AF>(
+                [&](int k) { return load_frag<M>(Pw, c * 2 * MT + k, lane); },
+                [&](int k, const AF& b) { X[k % MT] = PR::mma(xw[k / MT], b, X[k % MT]); });
+          } else {
+            T4 xv[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) xv[k] = *(const T4*)(xs + 16 * k + 4 * g);
+            stream<PD, 16 * MT, AF>(
+                [&](int k) { return load_frag<M>(Pw, c * 16 * MT + k, lane); },
+                [&](int k, const AF& b) {
+                  const int s = k / MT;
+                  X[k % MT] = PR::mma(xv[s >> 2][s & 3], b, X[k % MT]);
+                });
+          }
+        }
+      }
+      // the damage row changes from modes in lanes to modes in registers in LDS
+      if (g == 1) {
+#pragma unroll
+        for (int t = 0; t < MT; ++t) S.al[mperm<N, M>(t, n)] = X[t][2];
+      }
+      wave_sync();
+      Acc R[NT1];
+      mix_contract<N, P, L, NT1, false, PD>(X, As, Kw, Kt, R, lane);
+      T k[NR];
+#pragma unroll
+      for (int r = 0; r < NR; ++r) {
+        k[r] = r < 4 * NT1 ? R[r < 4 * NT1 ? r >> 2 : 0][r & 3] : T(0);
+        if (p == 9) k[r] = S.al[SL::row(r, g)];
+        if (p > 9) k[r] = T(0);
+      }
+      // the next iterate: U_z += dt Om_z,jt R(U_jt) for every z
+#pragma unroll
+      for (int z = 0; z < Nt; ++z) {
+        const T w = dt * pa.om[z][jt];
+#pragma unroll
+        for (int r = 0; r < NR; ++r) W[z][r] += w * k[r];
+      }
+#pragma unroll
+      for (int r = 0; r < NR; ++r) {
+        const T first = U[0][r];
+#pragma unroll
+        for (int z = 0; z + 1 < Nt; ++z) U[z][r] = U[z + 1][r];
+        U[Nt - 1][r] = first;
+      }
+    }
+#pragma unroll
+    for (int z = 0; z < Nt; ++z)
+#pragma unroll
+      for (int r = 0; r < NR; ++r) U[z][r] = W[z][r];
+  }
+  T* out = a.Uz + (size_t)e * DM::UZE;
+  if (p < 10) {
+#pragma unroll
+    for (int z = 0; z < Nt; ++z)
+#pragma unroll
+      for (int r = 0; r < NR; ++r) {
+        const int l = SL::row(r, g);
+        if (l < L) out[z * DM::UZT + l * 10 + p] = U[z][r];
+      }
+  }
+}
+
+template <int N, int P, class LW>
+__global__ __launch_bounds__((64 * PicardTabs<N, P>::wpb))
+__attribute__((amdgpu_waves_per_eu(PicardTabs<N, P>::waves))) void k_picard(StepArgs<P> a,
+                                                                            PicardArgs<P> pa) {
+  using T = typename Prec<P>::T;
+  using TB = PicardTabs<N, P>;
+  __shared__ __attribute__((aligned(64))) char smem[TB::bytes];
+  if constexpr (TB::staged) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    char *vw = smem, *vt = vw + TB::vw, *kw = vt + TB::vt, *kt = kw + TB::kw, *pw = kt + TB::kt;
+    stage(vw, a.Vw, TB::vw);
+    stage(vt, a.Vt, TB::vt);
+    stage(kw, a.Kw, TB::kw);
+    stage(kt, a.Kt, TB::kt);
+    stage(pw, a.PXa, TB::pw);
+    __syncthreads();
+    PicardLDS<N, P>& S = ((PicardLDS<N, P>*)(smem + TB::all))[wave];
+    for_elements(a, TB::wpb, [&](long long e, int lane) {
+      picard_element<N, P, LW>(a, pa, e, S, vw, (const T*)vt, kw, (const T*)kt, pw, lane);
+      wave_sync();
+    });
+  } else {
+    PicardLDS<N, P>& S = *(PicardLDS<N, P>*)smem;
+    for_elements(a, 1, [&](long long e, int lane) {
+      picard_element<N, P, LW>(a, pa, e, S, a.Vw, a.Vt, a.Kw, a.Kt, a.PXa, lane);
     });
   }
 }
