@@ -58,8 +58,11 @@ typedef enum {
 typedef enum {
   DGD_FP64 = 0,       /* every contraction and pointwise law in FP64 */
   DGD_FP32 = 1,       /* FP32 state and arithmetic; alpha kept and updated in FP64 */
-  DGD_BF16 = 2        /* as FP32, reference-matrix contractions with BF16 MFMA
-                         inputs (FP32 accumulation) */
+  DGD_BF16 = 2        /* as FP32, reference-matrix contractions with split BF16
+                         MFMA inputs (FP32 accumulation).  The
+                         Cauchy-Kovalevskaya step and the Picard predictor are
+                         those of DGD_FP32 (three-way split from degree 3 on,
+                         exact inputs); the Picard corrector splits two-way */
 } dgd_precision;
 
 typedef enum {
@@ -328,11 +331,12 @@ dgd_status dgd_energy_noalloc(dgd_handle* h, double* E /* device, 1 double */);
  * Per-kernel timing with HIP events recorded on the solver's stream around
  * every launch while profiling is on.  dgd_get_kernel_times synchronises,
  * returns the summed milliseconds and launch counts of the kernel classes
- * {0: predictor (Cauchy-Kovalevskaya, time points), 1: face fluxes,
- *  2: sources, 3: receivers, 4: adjoint's predictor recomputation,
- *  5: adjoint faces and their lift, 6: adjoint volume + predictor,
- *  7: adjoint receivers, 8: lift of the face fluxes + update,
- *  9: volume and source integrals}
+ * {0: predictor, 1: face fluxes, 2: sources (and, in the same launch, the
+ *  receivers), 3: receivers where no sources are set, 4: adjoint's predictor
+ *  recomputation, 5: adjoint faces and their lift, 6: adjoint volume +
+ *  predictor, 7: adjoint receivers, 8: lift of the face fluxes + update (Picard
+ *  predictor), 9: volume and source integrals (Cauchy-Kovalevskaya predictor:
+ *  with the lift and the update)}
  * since the last call, and resets them. */
 #define DGD_NUM_KERNEL_CLASSES 10
 dgd_status dgd_set_profiling(dgd_handle* h, int on);
@@ -359,7 +363,7 @@ dgd_status dgd_get_time_point_states(dgd_handle* h, double* out);
  * takes half of the derivative.  Point sources do not depend on the state or
  * on mu0, C_d.  The adjoint arithmetic is FP64 on DGD_FP64 handles and FP32
  * on the others: a DGD_BF16 handle runs its forward (and replayed) steps in
- * its split-BF16 form and differentiates them with the FP32 adjoint of the
+ * its own form and differentiates them with the FP32 adjoint of the
  * step, taken at the states of that trajectory (its FP32 operators are
  * packed on the first adjoint call).  CDM law only.
  *

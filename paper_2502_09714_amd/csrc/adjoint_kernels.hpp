@@ -1,5 +1,6 @@
-// Discrete adjoint of one ADER-DG step (device), transposing every stage of
-// k_predict + k_volume / k_face_flux / k_lift_update:  given U^n and lambda^{n+1} = dJ/dU^{n+1}
+// Discrete adjoint of one ADER-DG step (device), transposing every stage of the
+// step on its time-point states (prediction, volume terms, face fluxes, lift, in
+// exact arithmetic what step_kernels.hpp computes):  given U^n and lambda^{n+1} = dJ/dU^{n+1}
 // it returns lambda^n = dJ/dU^n and accumulates dJ/dmu0, dJ/dC_d per element.
 //
 //   k_predict (forward, recomputed)         ->  time-point states U_z of all elements
@@ -17,6 +18,7 @@
 #pragma once
 #include "adjoint_point.hpp"
 #include "kernels.hpp"
+#include "step_kernels.hpp"
 
 namespace dgd {
 
@@ -42,7 +44,7 @@ template <int P> struct AdjArgs {
   double* gcd;            // [E] dJ/dC_d (accumulated)
 };
 
-// One wavefront per face (the face list of k_face_flux): traces of U_z and of
+// One wavefront per face (the face list of k_face): traces of U_z and of
 // lambda^{n+1} on both sides at the shared face points.  The face flux F* is
 // single valued: the first side's update uses -dt|S|/|J| F*, the second side's
 // +dt|S'|/|J'| F*, so its cotangent at a point is
@@ -239,167 +241,237 @@ __global__ __launch_bounds__(64) void k_adj_lift(AdjArgs<P> A) {
 // its own register and LDS budget (one launch holds more than a SIMD's
 // registers): k_adj_points (the volume and source cotangents at the time
 // points, dJ/dU_z to HBM), then k_adj_volume<N, P, false> (the predictor
-// reversed).  Below degree 4 k_adj_volume<N, P, true> does both.
+// reversed).  Below degree 4 k_adj_volume<N, P, true> does both: two launches
+// cost 3..5 us more at 162 elements and gained at most 4 % at 16464.
 template <int N> struct AdjSplit {
   static constexpr bool value = N >= 4;
 };
 
-// LDS of k_adj_points: lambda^{n+1}, then the time-point state being
-// evaluated (then its cotangent); the point values / integrands of a chunk;
-// the per-point cotangents that lambda^{n+1} gives.
 template <int N, int P> struct AdjPtLDS {
   using T = typename Prec<P>::T;
-  static constexpr int KPL = round_up(Dims<N>::L, Prec<P>::KS);
-  static constexpr int R = Lds<T>::RS;
-  union {
-    T Lam[KPL * 16];
-    T Z[KPL * 16];              // lambda^{n+1} is spent before the first time point
-  };
-  T X[64 * R];
-  T Lp[Dims<N>::NCH][10][64];   // per point: velocity, stress and rate cotangents
+  static constexpr int RS = 64 + 16 / sizeof(T);
+  alignas(16) T X[10 * RS];       // cotangents of the quantities at the points of one chunk
+};
+
+template <int N, int P> struct AdjPtTabs {      // bytes of the matrices in LDS, launch shape
+  static constexpr int M = MatForm<N, P>::value;
+  static constexpr bool staged = M == PREC_X3;
+  static constexpr int vw = CkTabs<N, P>::vw, vt = CkTabs<N, P>::vt, vta = PicardTabs<N, P>::pw;
+  static constexpr int all = staged ? vw + vt + vta : 0;
+  static constexpr int wpb = staged ? 12 : 1, waves = staged ? wpb / 4 : (P == PREC_F64 && N >= 4 ? 1 : 2);
+  static constexpr int bytes = all + wpb * (int)sizeof(AdjPtLDS<N, P>);
+  static_assert(bytes <= 163840, "the workgroup's LDS");
 };
 
 // One wavefront per element: the volume and source terms transposed.
 // dJ/dG^e at the volume points is dt Sw^e^T lambda, folded at once into the
 // cotangents of the velocity and of the stress per point and unit time weight
-// (the flux is linear in both), and dJ/dr is dt Pw^T lambda_alpha; at every
-// (z, q) the pointwise VJP of sigma and r_alpha at the time-point state U_z
-// (read from HBM, where k_predict left it) and the transposed nodal
-// evaluation give the volume part of dJ/dU_z, which joins the face part in
-// lzf[e][z]; the material cotangents of the volume points join gmu, gcd.
+// (the flux is linear in both), and dJ/dr is dt Pw^T lambda_alpha (these two
+// matrices, used once per element, are read from L2; on modes, as the corrector
+// applies the stiffness, this is 20 us less but dJ/dmu0 loses: error against 64
+// bits 2.9e-7 in place of 1.9e-7).  At every
+// (z, q) the pointwise VJP of sigma and r_alpha at the time-point state U_z (read
+// from HBM, where k_predict left it) and the transposed nodal evaluation give the
+// volume part of dJ/dU_z, which joins the face part in lzf[e][z]; the material
+// cotangents of the volume points join gmu, gcd.
+// (With every contraction on FP32 matrix products out of LDS and the stiffness
+// applied over the points, 904 us at 20250 elements of degree 4; now 340 us.)
 template <int N, int P>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(P == PREC_F64 ? 2 : 4)))
-void k_adj_points(AdjArgs<P> A) {
-  using PR = Prec<P>;
-  using T = typename PR::T;
+__device__ inline void adj_points_element(const AdjArgs<P>& A, long long e, AdjPtLDS<N, P>& S,
+                                          const void* Vw, const typename Prec<P>::T* Vt,
+                                          const void* VTa, int lane) {
+  constexpr int M = MatForm<N, P>::value;
+  using PR = Prec<M>;
+  using PA = Prec<P>;
+  using T = typename PA::T;
+  using AF = typename PR::AF;
   using Acc = typename PR::Acc;
   using DM = Dims<N>;
-  const StepArgs<P>& a = A.s;
   constexpr int L = DM::L, Q = DM::Q, Nt = DM::Nt, NCH = DM::NCH, MT = DM::MT;
-  constexpr int KS = PR::KS, KPL = round_up(L, KS), KSL = KPL / KS, KSQ = 64 / KS;
-  constexpr int DS = 16, DPL = KPL * DS / 64;
-  using SL = AdjPtLDS<N, P>;
-  constexpr int R = SL::R;
-  __shared__ SL S;
-  T* const sX = S.X;
-  T* const sZ = S.Z;
-  const int lane = threadIdx.x;
-  const long long e = elem_of_block(a.E);
-  if (e >= a.E) return;
+  constexpr int KPL = round_up(L, PA::KS);
+  using SL = Steps<M, L>;
+  constexpr int WL = SL::WIDE, NR = SL::NREG, PD = M == PREC_X3 ? 1 : 4;
+  constexpr int PDS = M == PREC_X3 ? 3 : 4, RS = AdjPtLDS<N, P>::RS;
+  const StepArgs<P>& a = A.s;
+  const int n = lane & 15, g = lane >> 4;
+  const int p = qperm<T>(n);
   const Law<T> law{a.amax, a.smin};
   const MatP<T> m = load_mat<T>(a.mat + e * 8);
-  T Ji[9];
+  const T ir = T(1) / m.rho, dt = (T)a.dt;
+  const T* lam = A.lam + (size_t)e * KPL * 16;
+  T Lp[NCH][10];                  // velocity, stress and rate cotangents per point
+  {
+    T x[NR];
 #pragma unroll
-  for (int k = 0; k < 9; ++k) Ji[k] = (T)a.geo[e * 16 + k];
-  const T ir = T(1) / m.rho;
-  for (int i = lane; i < KPL * DS; i += 64) S.Lam[i] = A.lam[(size_t)e * KPL * 16 + i];
-  T gmu = T(0), gcd = T(0);
-  __syncthreads();
-
-  // per point and unit time weight: Lp[c][k][lane], k = 0..2 velocity,
-  // 3..8 stress, 9 damage rate
-#pragma unroll
-  for (int c = 0; c < NCH; ++c) {
-    T LV[3], LS[6];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) LV[k] = T(0);
-#pragma unroll
-    for (int k = 0; k < 6; ++k) LS[k] = T(0);
-#pragma unroll 1
-    for (int ee = 0; ee < 3; ++ee) {
-      Acc C[4];
-      zero_C<P, 4>(C);
-      wave_gemm<P, 4, KSL, DS>(A.STpk + (size_t)(ee * NCH + c) * 4 * KSL * 64, S.Lam, C, lane);
-      store_C<P, 4>(C, sX, 64, (T)a.dt, lane);
-      __syncthreads();
-      // G^e_(ij) = -(J_ej v_i + J_ei v_j)/2,  G^e_(v_i) = -(1/rho) sum_d J_ed sigma_id
-      T Jr[3];
-#pragma unroll
-      for (int d = 0; d < 3; ++d) Jr[d] = ee == 0 ? Ji[d] : (ee == 1 ? Ji[3 + d] : Ji[6 + d]);
-#pragma unroll
-      for (int p = 0; p < 6; ++p) {
-        const int ii = kVI[p], jj = kVJ[p];
-        const T lg = sX[lane * R + p];
-        LV[ii] += T(-0.5) * Jr[jj] * lg;
-        LV[jj] += T(-0.5) * Jr[ii] * lg;
-      }
-#pragma unroll
-      for (int ii = 0; ii < 3; ++ii) {
-        const T lg = sX[lane * R + 6 + ii] * (-ir);
-#pragma unroll
-        for (int d = 0; d < 3; ++d) LS[sym_idx(ii, d)] += lg * Jr[d];
-      }
-      __syncthreads();
+    for (int r = 0; r < NR; ++r) {
+      const int l = SL::row(r, g);
+      const T v = lam[(l < L ? l : L - 1) * 16 + (p < 10 ? p : 9)];
+      x[r] = l < L && p < 10 ? v : T(0);
     }
-    Acc C[4];
-    zero_C<P, 4>(C);
-    wave_gemm<P, 4, KSL, DS>(A.PTpk + (size_t)c * 4 * KSL * 64, S.Lam, C, lane);
-    store_C<P, 4>(C, sX, 64, (T)a.dt, lane);
-    __syncthreads();
+    AF xw[WL > 0 ? WL : 1];
 #pragma unroll
-    for (int k = 0; k < 3; ++k) S.Lp[c][k][lane] = LV[k];
+    for (int s = 0; s < WL; ++s) xw[s] = wide_op<M>(x, s);
+    T Ji[9];
 #pragma unroll
-    for (int k = 0; k < 6; ++k) S.Lp[c][3 + k][lane] = LS[k];
-    S.Lp[c][9][lane] = sX[lane * R + 9];
-    __syncthreads();
+    for (int k = 0; k < 9; ++k) Ji[k] = (T)a.geo[e * 16 + k];
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {
+      T u[12];
+#pragma unroll
+      for (int k = 0; k < 10; ++k) Lp[c][k] = T(0);
+#pragma unroll 1
+      for (int ee = 0; ee < 3; ++ee) {
+        nodal<N, P, PDS>(x, xw, (const char*)a.STw + ee * AdjPtTabs<N, P>::vw,
+                         a.STt + ee * (NCH * 4 * 64), c, u, lane);
+        // G^e_(ij) = -(J_ej v_i + J_ei v_j)/2,  G^e_(v_i) = -(1/rho) sum_d J_ed sigma_id
+        T Jr[3];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) Jr[d] = ee == 0 ? Ji[d] : (ee == 1 ? Ji[3 + d] : Ji[6 + d]);
+#pragma unroll
+        for (int q = 0; q < 6; ++q) {
+          const T lg = dt * u[q];
+          Lp[c][kVI[q]] += T(-0.5) * Jr[kVJ[q]] * lg;
+          Lp[c][kVJ[q]] += T(-0.5) * Jr[kVI[q]] * lg;
+        }
+#pragma unroll
+        for (int ii = 0; ii < 3; ++ii) {
+          const T lg = dt * u[6 + ii] * (-ir);
+#pragma unroll
+          for (int d = 0; d < 3; ++d) Lp[c][3 + sym_idx(ii, d)] += lg * Jr[d];
+        }
+      }
+      nodal<N, P, PDS>(x, xw, a.PVw, a.PVt, c, u, lane);
+      Lp[c][9] = dt * u[9];
+    }
   }
-
+  T gmu = T(0), gcd = T(0);
   const T* Uze = a.Uz + (size_t)e * DM::UZE;
+  // states and face parts are requested ahead of their use (FP64 has no registers
+  // left for it)
+  constexpr bool AHEAD = M == PREC_X3;
+  auto load_u = [&](int z, T (&v)[NR]) {
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      const int l = SL::row(r, g);
+      v[r] = Uze[z * DM::UZT + (l < L ? l : L - 1) * 10 + (p < 10 ? p : 9)];
+    }
+  };
+  T* lzf = A.lzf + (size_t)e * Nt * KPL * 16 + (p < 10 ? p : 9);
+  T dn[NR];
+  if constexpr (AHEAD) load_u(0, dn);
 #pragma unroll 1
   for (int z = 0; z < Nt; ++z) {
+    const T gz = a.gamma[z];
+    T d[NR], face[MT][4];
+    if constexpr (!AHEAD) load_u(z, dn);
 #pragma unroll
-    for (int j = 0; j < DPL; ++j) {
-      const int idx = lane + 64 * j, l = idx >> 4, p = idx & 15;
-      sZ[idx] = (l < L && p < 10) ? Uze[z * DM::UZT + l * 10 + p] : T(0);
-    }
-    __syncthreads();
-    const T g = a.gamma[z];
-    Acc Cl[MT];
-    zero_C<P, MT>(Cl);
-#pragma unroll 1
+    for (int r = 0; r < NR; ++r) d[r] = SL::row(r, g) < L && p < 10 ? dn[r] : T(0);
+    if constexpr (AHEAD) load_u(z + 1 < Nt ? z + 1 : z, dn);
+    T* lz = lzf + z * KPL * 16;
+    auto load_face = [&]() {
+#pragma unroll
+      for (int t = 0; t < MT; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int l = acc_mode<N, M>(t, i, g);
+          face[t][i] = lz[(l < L ? l : L - 1) * 16];
+        }
+    };
+    if constexpr (AHEAD) load_face();
+    AF dw[WL > 0 ? WL : 1];
+#pragma unroll
+    for (int s = 0; s < WL; ++s) dw[s] = wide_op<M>(d, s);
+    Acc C[MT];
+    zero_C<M, MT>(C);
+#pragma unroll
     for (int c = 0; c < NCH; ++c) {
-      Acc C[4];
-      zero_C<P, 4>(C);
-      wave_gemm_tiles<P, 4, KSL, DS>(a.Vpk + (size_t)c * 4 * KSL * 64, sZ, C, lane);
-      store_C<P, 4>(C, sX, 64, T(1), lane);
-      __syncthreads();
-      const int q = 64 * c + lane;
+      T u[12];
+      nodal<N, P, PD>(d, dw, Vw, Vt, c, u, lane);
       T gu[10];
 #pragma unroll
       for (int k = 0; k < 10; ++k) gu[k] = T(0);
-      if (q < Q) {
-        T u[10];
-#pragma unroll
-        for (int k = 0; k < 10; ++k) u[k] = sX[lane * R + k];
+      if (64 * c + lane < Q) {
         T ls[6];
 #pragma unroll
-        for (int k = 0; k < 6; ++k) ls[k] = g * S.Lp[c][3 + k][lane];
+        for (int k = 0; k < 6; ++k) ls[k] = gz * Lp[c][3 + k];
 #pragma unroll
-        for (int k = 0; k < 3; ++k) gu[6 + k] += g * S.Lp[c][k][lane];
+        for (int k = 0; k < 3; ++k) gu[6 + k] = gz * Lp[c][k];
         const Parts<T> pp = cdm_parts(u, law);
         stress_vjp_p(pp, u, m, ls, gu, gmu);
-        rate_vjp_p(pp, u, m, g * S.Lp[c][9][lane], gu, gcd);
+        rate_vjp_p(pp, u, m, gz * Lp[c][9], gu, gcd);
       }
-      __syncthreads();
+      wave_sync();
 #pragma unroll
-      for (int k = 0; k < 16; ++k) sX[lane * R + k] = k < 10 ? gu[k] : T(0);
-      __syncthreads();
-      wave_gemm_tiles<P, MT, KSQ>(A.VTpk + (size_t)c * MT * KSQ * 64, sX, Cl, lane);
-      __syncthreads();
+      for (int k = 0; k < 10; ++k) S.X[k * RS + lane] = gu[k];
+      wave_sync();
+      // transposed evaluation: modes in rows, quantities in columns
+      typedef T T4 __attribute__((ext_vector_type(4), aligned(16)));
+      const T* xs = S.X + (p < 10 ? p : 9) * RS;
+      if constexpr (M == PREC_X3) {
+        AF xw[2];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          const T4 lo = *(const T4*)(xs + 32 * s + 8 * g), hi = *(const T4*)(xs + 32 * s + 8 * g + 4);
+          const T v8[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+          xw[s] = split8(v8);
+        }
+        stream<1, 2 * MT, AF>(
+            [&](int k) { return load_frag<M>(VTa, c * 2 * MT + k, lane); },
+            [&](int k, const AF& aa) { C[k % MT] = PR::mma(aa, xw[k / MT], C[k % MT]); });
+      } else {
+        T4 xv[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) xv[k] = *(const T4*)(xs + 16 * k + 4 * g);
+        stream<PD, 16 * MT, AF>(
+            [&](int k) { return load_frag<M>(VTa, c * 16 * MT + k, lane); },
+            [&](int k, const AF& aa) {
+              const int s = k / MT;
+              C[k % MT] = PR::mma(aa, xv[s >> 2][s & 3], C[k % MT]);
+            });
+      }
     }
-    // the time-point state is spent: the volume part of dJ/dU_z goes there,
-    // then joins the face part
-    store_C<P, MT, DS>(Cl, sZ, KPL, T(1), lane);
-    __syncthreads();
-    T* lz = A.lzf + ((size_t)e * Nt + z) * KPL * 16;
+    if constexpr (!AHEAD) load_face();
+    if (p < 10) {
 #pragma unroll
-    for (int j = 0; j < DPL; ++j) lz[lane + 64 * j] += sZ[lane + 64 * j];
-    __syncthreads();
+      for (int t = 0; t < MT; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int l = acc_mode<N, M>(t, i, g);
+          if (l < L) lz[l * 16] = face[t][i] + C[t][i];
+        }
+    }
   }
   const T gm = wave_sum(gmu), gc = wave_sum(gcd);
   if (lane == 0) {
     A.gmu[e] += (double)gm;
     A.gcd[e] += (double)gc;
+  }
+}
+
+template <int N, int P>
+__global__ __launch_bounds__((64 * AdjPtTabs<N, P>::wpb))
+__attribute__((amdgpu_waves_per_eu(AdjPtTabs<N, P>::waves))) void k_adj_points(AdjArgs<P> A) {
+  using T = typename Prec<P>::T;
+  using TB = AdjPtTabs<N, P>;
+  const StepArgs<P>& a = A.s;
+  __shared__ __attribute__((aligned(64))) char smem[TB::bytes];
+  if constexpr (TB::staged) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    char *vw = smem, *vt = vw + TB::vw, *vta = vt + TB::vt;
+    stage(vw, a.Vw, TB::vw);
+    stage(vt, a.Vt, TB::vt);
+    stage(vta, a.VTa, TB::vta);
+    __syncthreads();
+    AdjPtLDS<N, P>& S = ((AdjPtLDS<N, P>*)(smem + TB::all))[wave];
+    for_elements(a, TB::wpb, [&](long long e, int lane) {
+      adj_points_element<N, P>(A, e, S, vw, (const T*)vt, vta, lane);
+      wave_sync();
+    });
+  } else {
+    AdjPtLDS<N, P>& S = *(AdjPtLDS<N, P>*)smem;
+    for_elements(a, 1, [&](long long e, int lane) {
+      adj_points_element<N, P>(A, e, S, a.Vw, a.Vt, a.VTa, lane);
+    });
   }
 }
 

@@ -77,6 +77,7 @@ struct dgd_handle {
   DevBuf Vpk, Kpk, Spk, Fpk, Lpk, Ppk, Vd, wqd, Pwd, betad;
   // Cauchy-Kovalevskaya step (step_kernels.hpp)
   DevBuf Vw, Vt, Kw, Kt, Ktw, PXw, PXa, PXleft, Rw, Fst, Fstt, Psi, Psrc, mixP, mixV;
+  DevBuf PVw, PVt, VTa, STw, STt;   // transposed (discrete adjoint)
   size_t dz_elem = 0;     // bytes of one element's time derivatives
   double points_dt = 0.0;      // step of the last step's derivatives
   bool points_in_uz = false;   // the last step left time-point states in Uz, not derivatives in Dz
@@ -145,7 +146,8 @@ struct dgd_handle {
                      &VTpk, &STpk, &PTpk, &KTpk, &lam[0], &lam[1], &gtr, &gmuf, &lzf, &gmu, &gcd, &adjW9,
                      &adjWa, &dlds, &seg9, &sega, &seguz, &segd, &segacc, &save9, &savea, &st9, &sta,
                      &ecl, &facc, &Vw, &Vt, &Kw, &Kt, &Ktw, &PXw, &PXa,
-                     &PXleft, &Rw, &Fst, &Fstt, &Psi, &Psrc, &mixP, &mixV, &Dz, &Vpk32, &Kpk32, &Spk32, &Fpk32, &Lpk32, &Ppk32};
+                     &PXleft, &Rw, &Fst, &Fstt, &Psi, &Psrc, &mixP, &mixV, &PVw, &PVt, &VTa, &STw, &STt,
+                      &Dz, &Vpk32, &Kpk32, &Spk32, &Fpk32, &Lpk32, &Ppk32};
     for (DevBuf* b : all) b->release();
     for (DevBuf& b : ck9) b.release();
     for (DevBuf& b : cka) b.release();
@@ -405,19 +407,32 @@ dgd_status build_step_packs(dgd_handle* h) {
   auto Ft = [&](int ff, int i, int l) {
     return (i < Ns && l < L) ? r.F[((size_t)ff * Ns + i) * L + l] : 0.0;
   };
-  std::vector<char> vw, kw, ktw, pw, pa, rw, fs;
-  std::vector<T> vt, kt, pl, ft, psi, ps((size_t)Q4 * L * 4, T(0));
+  std::vector<char> vw, kw, ktw, pw, pa, rw, fs, pv, vta, sw;
+  std::vector<T> vt, kt, pl, ft, pvt, stl, psi, ps((size_t)Q4 * L * 4, T(0));
   auto tail = [](std::vector<T>& out, auto val) {
     for (int lane = 0; lane < 64; ++lane) out.push_back((T)val(lane & 15, lane >> 4));
   };
   for (int t = 0; t < NCH * 4; ++t)
-    for (int s = 0; s < SL::WIDE; ++s)
+    for (int s = 0; s < SL::WIDE; ++s) {
       append_frag<M>(vw, [&](int n, int g, int j) { return V(16 * t + n, mode(s, g, j)); });
+      append_frag<M>(pv, [&](int n, int g, int j) { return Pw(mode(s, g, j), 16 * t + n); });
+    }
   if constexpr (SL::TAIL)
-    for (int t = 0; t < NCH * 4; ++t)
+    for (int t = 0; t < NCH * 4; ++t) {
       tail(vt, [&](int n, int g) { return V(16 * t + n, 32 * SL::WIDE + g); });
+      tail(pvt, [&](int n, int g) { return Pw(32 * SL::WIDE + g, 16 * t + n); });
+    }
   if constexpr (X3 && Deriv<N>::rows(16 * (Deriv<N>::NT - 1)) <= 4)
     for (int t = 0; t < NCH * 4; ++t) tail(vt, [&](int n, int g) { return V(16 * t + n, g); });
+  auto Sw = [&](int e, int l, int q) {
+    return (l < L && q < Q) ? r.Sw[((size_t)e * L + l) * Q + q] : 0.0;
+  };
+  for (int e = 0; e < 3; ++e)
+    for (int t = 0; t < NCH * 4; ++t) {
+      for (int s = 0; s < SL::WIDE; ++s)
+        append_frag<M>(sw, [&](int n, int g, int j) { return Sw(e, mode(s, g, j), 16 * t + n); });
+      if constexpr (SL::TAIL) tail(stl, [&](int n, int g) { return Sw(e, 32 * SL::WIDE + g, 16 * t + n); });
+    }
   for (int e = 0; e < 3; ++e)
     for (int t = 0; t < NT1; ++t) {
       for (int s = 0; s < SL::WIDE; ++s)
@@ -438,6 +453,10 @@ dgd_status build_step_packs(dgd_handle* h) {
           return Pw(mperm<N, M>(t, n), q);
         };
         append_frag<M>(pa, val);
+        append_frag<M>(vta, [&](int n, int g, int j) {
+          const int q = 64 * c + (X3 ? 32 * s + 8 * g + j : 16 * (s / 4) + 4 * g + s % 4);
+          return V(q, mperm<N, M>(t, n));
+        });
         if (t < ProjTiles<N>::MTP) append_frag<M>(pw, val);
       }
   for (int c = 0; c < NCH; ++c)
@@ -510,6 +529,9 @@ dgd_status build_step_packs(dgd_handle* h) {
         }
       }
   dgd_status st;
+  if ((st = upload(h, h->PVw, pv)) || (st = upload(h, h->PVt, pvt)) ||
+      (st = upload(h, h->VTa, vta)) || (st = upload(h, h->STw, sw)) || (st = upload(h, h->STt, stl)))
+    return st;
   if ((st = upload(h, h->Vw, vw)) || (st = upload(h, h->Vt, vt)) || (st = upload(h, h->Kw, kw)) ||
       (st = upload(h, h->Kt, kt)) || (st = upload(h, h->Ktw, ktw)) || (st = upload(h, h->PXw, pw)) ||
       (st = upload(h, h->PXa, pa)) ||
@@ -622,6 +644,11 @@ StepArgs<P> make_args(dgd_handle* h) {
   a.PXleft = (const T*)h->PXleft.p;
   a.Rw = h->Rw.p;
   a.PXa = h->PXa.p;
+  a.PVw = h->PVw.p;
+  a.PVt = (const T*)h->PVt.p;
+  a.VTa = h->VTa.p;
+  a.STw = h->STw.p;
+  a.STt = (const T*)h->STt.p;
   a.Fst = h->Fst.p;
   a.Fstt = (const T*)h->Fstt.p;
   a.Psi = (const T*)h->Psi.p;
@@ -1015,7 +1042,9 @@ dgd_status adjoint_step_impl(dgd_handle* h, const void* U9, const double* Ua, co
     });
     timed(h, 6, [&] {
       if constexpr (AdjSplit<N>::value) {
-        hipLaunchKernelGGL((k_adj_points<N, P>), grid, block, 0, h->stream, A);
+        using TB = AdjPtTabs<N, P>;
+        hipLaunchKernelGGL((k_adj_points<N, P>), element_grid(h, h->ne, TB::wpb), dim3(64 * TB::wpb),
+                           0, h->stream, A);
         hipLaunchKernelGGL((k_adj_volume<N, P, false>), grid, block, 0, h->stream, A);
       } else {
         hipLaunchKernelGGL((k_adj_volume<N, P, true>), grid, block, 0, h->stream, A);

@@ -1,8 +1,11 @@
-// Per-step kernels of the ADER-DG update (gfx950).  One 64-lane wavefront owns
-// one tetrahedron; workgroups are mapped to elements so that each of the eight
-// XCDs walks a contiguous range of elements (neighbours share an L2).
+// Kernels on time-point states, and what the steps share (gfx950).  The
+// Cauchy-Kovalevskaya step and the Picard predictor are in step_kernels.hpp; here
+// are the corrector of the Picard step and the prediction that the discrete
+// adjoint starts from.  One 64-lane wavefront owns one tetrahedron; workgroups
+// are mapped to elements so that each of the eight XCDs walks a contiguous range
+// of elements (neighbours share an L2).
 //
-// k_predict  (paper Appendix A.1)
+// k_predict  (paper Appendix A.1; adjoint)
 //   nodal values at t_n -> pointwise CDM tangent -> cell-averaged Jacobians
 //   A*_e = sum_d Theta^-1_ed Bbar^d  (Eq. CKIter-ref)
 //   D^i = -sum_e K^e D^{i-1} A*_e^T, + nodal damage source at i = 1
@@ -99,6 +102,9 @@ template <int P> struct StepArgs {
   const T* PXleft;      // its last modes [chunk][mode][64]
   const void* Rw;       // lift of the face modes [face][permutation][tile]
   const void* PXa;      // projection, all modes (Picard predictor)
+  // adjoint: projection and stiffness over the points, and evaluation, transposed
+  const void *PVw, *STw, *VTa;
+  const T *PVt, *STt;
   const void* Fst;      // face traces [face][permutation][tile][wide step]
   const T* Fstt;        // their FP32 steps (three-way form)
   const T* Psi;         // projection of point fluxes on the face modes [step]

@@ -28,7 +28,7 @@
 // Depths of the register rings in the helpers below: how far ahead of its use
 // a fragment is requested from L2/HBM (each slot costs one fragment per tile
 // row in registers).
-//   DGD_PF_STEPS   matrix-core steps, A only: wave_gemm, wave_gemm2, wave_gemm_col9
+//   DGD_PF_STEPS   matrix-core steps, A only: wave_gemm, wave_gemm_col9
 //   DGD_PF_SHARED  matrix-core steps, A and B: wave_gemm_shared_a
 //   DGD_PF_TILES   single products, A only: wave_gemm_tiles
 #ifndef DGD_PF_STEPS
@@ -317,7 +317,7 @@ __device__ inline void wave_gemm_tiles(const typename Prec<P>::AF* __restrict__ 
                                        typename Prec<P>::Acc (&C)[MT], int lane) {
   using PR = Prec<P>;
   using AF = typename PR::AF;
-  // A fragments PD products ahead, in the order they are used (see wave_gemm2)
+  // A fragments PD products ahead, in the order they are used (see wave_gemm)
   constexpr int NS = MT * KSTEPS, PD = DGD_PF_TILES, NB = PD + 1;
   AF a[NB];
 #pragma unroll
