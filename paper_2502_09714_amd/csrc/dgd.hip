@@ -361,30 +361,6 @@ void append_frag(std::vector<char>& out, F val) {
   }
 }
 
-// Orthonormal polynomials of degree <= N on the face, at its points, with respect
-// to the weights beta: psi[m][i] (modified Gram-Schmidt, twice, on monomials)
-std::vector<std::vector<double>> face_modes(const RefData& r) {
-  std::vector<std::vector<double>> psi;
-  for (int d = 0; d <= r.N; ++d)
-    for (int b = 0; b <= d; ++b) {
-      std::vector<double> v(r.Ns);
-      for (int i = 0; i < r.Ns; ++i)
-        v[i] = std::pow(r.eta[2 * i] - 1.0 / 3, d - b) * std::pow(r.eta[2 * i + 1] - 1.0 / 3, b);
-      for (int pass = 0; pass < 2; ++pass) {
-        for (const auto& w : psi) {
-          double s = 0.0;
-          for (int i = 0; i < r.Ns; ++i) s += r.beta[i] * v[i] * w[i];
-          for (int i = 0; i < r.Ns; ++i) v[i] -= s * w[i];
-        }
-        double s = 0.0;
-        for (int i = 0; i < r.Ns; ++i) s += r.beta[i] * v[i] * v[i];
-        for (double& x : v) x /= std::sqrt(s);
-      }
-      psi.push_back(v);
-    }
-  return psi;
-}
-
 // operators of the Cauchy-Kovalevskaya step's kernels (step_kernels.hpp)
 template <int N, int P>
 dgd_status build_step_packs(dgd_handle* h) {
@@ -462,15 +438,9 @@ dgd_status build_step_packs(dgd_handle* h) {
   for (int c = 0; c < NCH; ++c)
     for (int k = 0; k < ProjTiles<N>::LEFT; ++k)
       for (int q = 0; q < 64; ++q) pl.push_back((T)Pw(16 * ProjTiles<N>::MTP + k, 64 * c + q));
-  const std::vector<std::vector<double>> fm = face_modes(r);
   for (int ff = 0; ff < 24; ++ff) {
-    const double* F = &r.F[(size_t)ff * Ns * L];
-    // lift of face mode m: sum_i beta_i psi_m(eta_i) phi_l(x_i)
     auto R = [&](int l, int m) {
-      if (l >= L || m >= NM2) return 0.0;
-      double s = 0.0;
-      for (int i = 0; i < Ns; ++i) s += r.beta[i] * fm[m][i] * F[i * L + l];
-      return s;
+      return (l < L && m < NM2) ? r.R[((size_t)ff * L + l) * NM2 + m] : 0.0;
     };
     for (int t = 0; t < MT; ++t) {
       if constexpr (X3) {
@@ -504,7 +474,7 @@ dgd_status build_step_packs(dgd_handle* h) {
   for (int s = 0; s < (Ns + 3) / 4; ++s)
     tail(psi, [&](int n, int g) {
       const int i = 4 * s + g;
-      return (n < NM2 && i < Ns) ? r.beta[i] * fm[n][i] : 0.0;
+      return (n < NM2 && i < Ns) ? r.Psi[(size_t)n * Ns + i] : 0.0;
     });
   for (int q = 0; q < Q; ++q)
     for (int l = 0; l < L; ++l) ps[((size_t)(q / 4) * L + l) * 4 + q % 4] = (T)r.Pw[(size_t)l * Q + q];

@@ -1,4 +1,5 @@
-// Host-side generator of the reference-element data (FP64).
+// Host-side generator of the reference-element data (computed in extended precision,
+// rounded to FP64).
 //
 // Quadrature: collapsed (Stroud conical product) Gauss-Jacobi rules with N+1
 // points per direction -- nodes by Newton iteration on the three-term Jacobi
@@ -13,6 +14,9 @@
 //   F[f][s][i][l] = phi_l(xi^f(eta_i permuted by s)) face traces, s = permutation of
 //                   the face vertices that puts the rule on the face in global order
 //   beta[i], tau[z], gamma[z]                      face and time weights
+//   Psi[m][i]  = beta_i psi_m(eta_i)               projection on the face modes psi_m,
+//                                                  orthonormal, of degree <= N in the plane
+//   R[f][s][l][m] = sum_i Psi[m][i] F[f][s][i][l]  lift of face mode m
 //   Om[z][j]   = int_0^tau_z l_j(s) ds             time integration of the Lagrange
 //                                                  polynomials of the time points
 #pragma once
@@ -34,6 +38,8 @@ struct RefData {
   std::vector<double> K;      // 3*L*L
   std::vector<double> Om;     // Nt*Nt
   std::vector<double> F;      // 4*6*Ns*L
+  std::vector<double> Psi;    // M*Ns, M = (N+1)(N+2)/2
+  std::vector<double> R;      // 4*6*L*M
   std::vector<int> deg;       // L total degrees
 };
 
@@ -43,7 +49,6 @@ extern const int kPerm3[6][3];
 extern const int kFaceVerts[4][3];
 
 int n_modes(int N);
-void gauss_jacobi(int n, double alpha, std::vector<double>& t, std::vector<double>& w);
 void basis_eval(int N, const double xi[3], double* phi, double* dphi /* 3*L or null */);
 RefData build_reference(int N);
 
