@@ -416,11 +416,17 @@ dgd_status build_step_packs(dgd_handle* h) {
       if constexpr (SL::TAIL)
         tail(kt, [&](int n, int g) { return K(e, mperm<N, M>(t, n), 32 * SL::WIDE + g); });
     }
-  constexpr auto list = kt_list<N, M>();
-  for (int k = 0; k < list.n; ++k)
-    append_frag<M>(ktw, [&](int n, int g, int j) {
-      return K(list.e[k], mode(list.s[k], g, j), 16 * list.t[k] + n);
-    });
+  if constexpr (PointStiffness<N>::value) {
+    for (int s = 0; s < PointStiffness<N>::steps; ++s)
+      for (int e = 0; e < 3; ++e)
+        append_frag<M>(ktw, [&](int n, int g, int) { return Sw(e, n, 16 * (s / 4) + 4 * g + s % 4); });
+  } else {
+    constexpr auto list = kt_list<N, M>();
+    for (int k = 0; k < list.n; ++k)
+      append_frag<M>(ktw, [&](int n, int g, int j) {
+        return K(list.e[k], mode(list.s[k], g, j), 16 * list.t[k] + n);
+      });
+  }
   for (int c = 0; c < NCH; ++c)
     for (int s = 0; s < (X3 ? 2 : 16); ++s)
       for (int t = 0; t < MT; ++t) {

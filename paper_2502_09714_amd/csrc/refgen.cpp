@@ -208,9 +208,15 @@ RefData build_reference(int N) {
       }
       psi.push_back(v);
     }
-  const int M = (int)psi.size();
+  // (degree 1: the point values)
+  const int M = N == 1 ? Ns : (int)psi.size();
+  std::vector<real> Psi((size_t)M * Ns, 0), lift((size_t)M * Ns, 0);   // R = lift F
   for (int m = 0; m < M; ++m)
-    for (int i = 0; i < Ns; ++i) r.Psi.push_back((double)(beta[i] * psi[m][i]));
+    for (int i = 0; i < Ns; ++i) {
+      Psi[m * Ns + i] = N == 1 ? real(m == i) : beta[i] * psi[m][i];
+      lift[m * Ns + i] = N == 1 ? (m == i ? beta[i] : 0) : Psi[m * Ns + i];
+    }
+  r.Psi.assign(Psi.begin(), Psi.end());
   r.F.assign((size_t)4 * 6 * Ns * L, 0.0);
   r.R.assign((size_t)4 * 6 * L * M, 0.0);
   for (int f = 0; f < 4; ++f)
@@ -227,7 +233,7 @@ RefData build_reference(int N) {
         basis_real(N, xi, phi.data(), nullptr);
         for (int l = 0; l < L; ++l) {
           r.F[(((size_t)f * 6 + s) * Ns + i) * L + l] = (double)phi[l];
-          for (int m = 0; m < M; ++m) R[(size_t)l * M + m] += beta[i] * psi[m][i] * phi[l];
+          for (int m = 0; m < M; ++m) R[(size_t)l * M + m] += lift[m * Ns + i] * phi[l];
         }
       }
       std::copy(R.begin(), R.end(), r.R.begin() + ((size_t)f * 6 + s) * L * M);

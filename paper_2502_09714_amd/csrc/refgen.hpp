@@ -17,6 +17,8 @@
 //   Psi[m][i]  = beta_i psi_m(eta_i)               projection on the face modes psi_m,
 //                                                  orthonormal, of degree <= N in the plane
 //   R[f][s][l][m] = sum_i Psi[m][i] F[f][s][i][l]  lift of face mode m
+//                   (degree 1: point values in the place of modes, Psi the identity,
+//                   R[f][s][l][i] = beta_i F[f][s][i][l])
 //   Om[z][j]   = int_0^tau_z l_j(s) ds             time integration of the Lagrange
 //                                                  polynomials of the time points
 #pragma once
@@ -38,7 +40,7 @@ struct RefData {
   std::vector<double> K;      // 3*L*L
   std::vector<double> Om;     // Nt*Nt
   std::vector<double> F;      // 4*6*Ns*L
-  std::vector<double> Psi;    // M*Ns, M = (N+1)(N+2)/2
+  std::vector<double> Psi;    // M*Ns, M = (N+1)(N+2)/2, 4 at degree 1
   std::vector<double> R;      // 4*6*L*M
   std::vector<int> deg;       // L total degrees
 };

@@ -752,9 +752,19 @@ template <int N, int P> struct UpdLDS {
 
 // Modes of a face flux on its face: orthonormal polynomials of degree <= N in the
 // plane.  The basis restricted to a face is such a polynomial, so the lift of
-// the (N + 1)^2 point values is the lift of their NM2 projections.
+// the (N + 1)^2 point values is the lift of their NM2 projections.  At degree 1 the
+// point values themselves (see PointStiffness).
 template <int N> struct FaceModes {
-  static constexpr int value = (N + 1) * (N + 2) / 2;
+  static constexpr int value = N == 1 ? 4 : (N + 1) * (N + 2) / 2;
+};
+// Degree 1 applies the stiffness to the point values, too, not to the projection.  There
+// it acts on one mode and the lift would on three: what FP32 leaves of so few entries
+// does not average out, and the waves after four steps were 14 % further from 64 bits
+// than with point sums (3.0e-7 against 2.6e-7, rms over 100 states).  The products are as
+// many (12 and 4 against 16 and 3, the 8 points being two of a chunk's 16 steps).
+template <int N> struct PointStiffness {
+  static constexpr bool value = N == 1;
+  static constexpr int steps = 4 * ((Dims<N>::Q + 15) / 16);   // of a chunk's 16, those with points
 };
 // Modes projected one per 16-row tile by matrix products; the few left over
 // (3 at degree 4, 4 at degree 3), which only the damage source needs, by a sum
@@ -884,6 +894,10 @@ __device__ inline void update_element(const StepArgs<P>& a, long long e, const i
     for (int s = 0; s < WL; ++s)
       if (M != PREC_X3 || DV::rows(16 * ct) > 4) dzw[ct][s] = wide_op<M>(dzr[ct], s);
 
+  constexpr bool PS = PointStiffness<N>::value;
+  Acc Z[3][MT];
+#pragma unroll
+  for (int ee = 0; ee < 3; ++ee) zero_C<M, MT>(Z[ee]);
   typename PA::Acc X[MTP];
   zero_C<P, MTP>(X);
   T left[LEFT > 0 ? LEFT : 1];
@@ -992,12 +1006,21 @@ __device__ inline void update_element(const StepArgs<P>& a, long long e, const i
       T4 xv[4];
 #pragma unroll
       for (int k = 0; k < 4; ++k) xv[k] = *(const T4*)(xs + 16 * k + 4 * g);
-      stream<PD, 16 * MTP, AF>(
+      constexpr int NS = PS ? PointStiffness<N>::steps : 16;
+      stream<PD, NS * MTP, AF>(
           [&](int k) { return load_frag<M>(Pw, c * 16 * MTP + k, lane); },
           [&](int k, const AF& aa) {
             const int s = k / MTP;
             X[k % MTP] = PR::mma(aa, xv[s >> 2][s & 3], X[k % MTP]);
           });
+      if constexpr (PS) {
+        static_assert(NCH == 1 && MT == 1, "one chunk, one tile");
+        stream<PD, 3 * NS, AF>([&](int k) { return load_frag<M>(Ktw, k, lane); },
+                               [&](int k, const AF& b) {
+                                 const int s = k / 3;
+                                 Z[k % 3][0] = PR::mma(xv[s >> 2][s & 3], b, Z[k % 3][0]);
+                               });
+      }
     }
   }
   // the projected source (times dt) leaves through LDS, one mode per lane
@@ -1019,7 +1042,7 @@ __device__ inline void update_element(const StepArgs<P>& a, long long e, const i
     }
   const double ua = a.Ua[e * L + (lane < L ? lane : L - 1)];
   // stiffness on modes, then the Jacobian and the material on quantities
-  {
+  if constexpr (!PS) {
     using S1 = Steps<M, modes_upto(N - 1)>;
     constexpr int NX = S1::NREG > 4 * MTP ? S1::NREG : 4 * MTP;
     T xm[NX];
@@ -1029,14 +1052,13 @@ __device__ inline void update_element(const StepArgs<P>& a, long long e, const i
 #pragma unroll
     for (int s = 0; s < S1::WIDE; ++s) xw[s] = wide_op<M>(xm, s);
     constexpr auto list = kt_list<N, M>();
-    Acc Z[3][MT];
-#pragma unroll
-    for (int ee = 0; ee < 3; ++ee) zero_C<M, MT>(Z[ee]);
     stream<PD, list.n, AF>([&](int k) { return load_frag<M>(Ktw, k, lane); },
                            [&](int k, const AF& b) {
                              Acc& z = Z[list.e[k]][list.t[k]];
                              z = PR::mma(xw[list.s[k]], b, z);
                            });
+  }
+  {
     const T rs = (T)a.dt * (p >= 6 ? m.ir : T(1));
     if constexpr (SL::KEEP) {
 #pragma unroll
