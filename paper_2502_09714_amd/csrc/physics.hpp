@@ -421,6 +421,14 @@ __device__ inline double rcp1(double x) {
   r = fma(fma(-x, r, 1.0), r, r);
   return fma(fma(-x, r, 1.0), r, r);
 }
+// alpha clamped to [0, hi]; a NaN stays one (fmin and fmax would turn it into 0 and hide
+// it from stress, flux and speed)
+__device__ inline float clamp_alpha(float a, float hi) {
+  return __builtin_elementwise_minimum(__builtin_elementwise_maximum(a, 0.0f), hi);
+}
+__device__ inline double clamp_alpha(double a, double hi) {
+  return a < 0.0 ? 0.0 : (a > hi ? hi : a);
+}
 __device__ inline float sqrt1(float x) { return __builtin_amdgcn_sqrtf(x); }
 __device__ inline double sqrt1(double x) { return sqrt(x); }
 
@@ -464,7 +472,7 @@ struct CdmStep {
     v.I1p = e0 + e1 + e2;
     v.xi = v.I1p * v.is;
     v.I1 = u[0] + u[1] + u[2];
-    v.ac = fmin(fmax(u[9], T(0)), law.amax);
+    v.ac = clamp_alpha(u[9], law.amax);
     return v;
   }
   template <class T>
@@ -558,7 +566,7 @@ struct IvmStep {
     v.I1 = u[0] + u[1] + u[2];
     v.I2 = u[0] * u[0] + u[1] * u[1] + u[2] * u[2] +
            T(2) * (u[3] * u[3] + u[4] * u[4] + u[5] * u[5]);
-    v.ac = fmin(fmax(u[9], T(0)), law.amax);
+    v.ac = clamp_alpha(u[9], law.amax);
     v.g = T(1) - v.ac;
     return v;
   }
@@ -588,12 +596,13 @@ struct IvmStep {
       return -(m.mu2 * acc[1 + k] + (k < 3 ? m.lam * (acc[1] + acc[2] + acc[3]) : T(0)));
     return acc[0] * ((k == q ? m.mu2 : T(0)) + (k < 3 && q < 3 ? m.lam : T(0)));
   }
-  // the acoustic tensor is that of the damaged isotropic moduli
+  // the acoustic tensor is that of the damaged isotropic moduli (a negative or NaN
+  // modulus has to end as NaN in the flux, which flags the step)
   template <class T>
   __device__ static T speed2(const T* u, const T*, const StepMat<T>& ma, const StepMat<T>& mb, bool,
                              const Law<T>& law) {
-    const T g = T(1) - fmin(fmax(u[9], T(0)), law.amax);
-    return fmax(g * fmax((ma.lam + ma.mu2) * ma.ir, (mb.lam + mb.mu2) * mb.ir), T(0));
+    const T g = T(1) - clamp_alpha(u[9], law.amax);
+    return g * fmax((ma.lam + ma.mu2) * ma.ir, (mb.lam + mb.mu2) * mb.ir);
   }
 };
 
