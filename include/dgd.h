@@ -342,10 +342,11 @@ dgd_status dgd_energy_noalloc(dgd_handle* h, double* E /* device, 1 double */);
 dgd_status dgd_set_profiling(dgd_handle* h, int on);
 dgd_status dgd_get_kernel_times(dgd_handle* h, double* ms /* 10 */, int64_t* launches /* 10 */);
 
-/* Intermediate results of the last dgd_step call for testing: the time-point
- * states U(t_n + tau_z dt) of its last step (the Taylor sums of Eq.
+/* Intermediate results of the last dgd_step or dgd_step_lts call for testing: the
+ * time-point states U(t_n + tau_z dt) of its last step (the Taylor sums of Eq.
  * taylor_expansion at the Gauss-Legendre points tau_z), [ne][Nt][10][L] FP64
- * host.  Synchronises; ESTATE before a state is set. */
+ * host; after dgd_step_lts those of each element's own last step.  Zeros before
+ * the first step.  Synchronises; ESTATE before a state is set. */
 dgd_status dgd_get_time_point_states(dgd_handle* h, double* out);
 
 /* ---------------------------------------------------------------------------

@@ -79,8 +79,13 @@ struct dgd_handle {
   DevBuf Vw, Vt, Kw, Kt, Ktw, PXw, PXa, PXleft, Rw, Fst, Fstt, Psi, Psrc, mixP, mixV;
   DevBuf PVw, PVt, VTa, STw, STt;   // transposed (discrete adjoint)
   size_t dz_elem = 0;     // bytes of one element's time derivatives
-  double points_dt = 0.0;      // step of the last step's derivatives
-  bool points_in_uz = false;   // the last step left time-point states in Uz, not derivatives in Dz
+  // what the last step left: its time-point states in Uz, or derivatives in Dz and the
+  // step they belong to (element e: dt 2^cluster[e] after local time stepping)
+  struct Points {
+    bool in_uz = false, clustered = false;
+    double dt = 0.0;
+  } points;
+  DevBuf points_ecl;      // its clusters, where dgd_set_clusters has replaced them since
   int predictor = 0;      // 0: linearised Cauchy-Kovalevskaya, 1: Picard iteration
   int picard_iters = 0;
   // host copies of the connectivity (neighbour of every element face, face list)
@@ -145,7 +150,7 @@ struct dgd_handle {
                      &p_elem, &p_range, &p_order, &s_M6, &s_dphi, &s_onset, &s_param, &s_rhoJ, &r_elem, &r_phi, &seis,
                      &VTpk, &STpk, &PTpk, &KTpk, &lam[0], &lam[1], &gtr, &gmuf, &lzf, &gmu, &gcd, &adjW9,
                      &adjWa, &dlds, &seg9, &sega, &seguz, &segd, &segacc, &save9, &savea, &st9, &sta,
-                     &ecl, &facc, &Vw, &Vt, &Kw, &Kt, &Ktw, &PXw, &PXa,
+                     &ecl, &points_ecl, &facc, &Vw, &Vt, &Kw, &Kt, &Ktw, &PXw, &PXa,
                      &PXleft, &Rw, &Fst, &Fstt, &Psi, &Psrc, &mixP, &mixV, &PVw, &PVt, &VTa, &STw, &STt,
                       &Dz, &Vpk32, &Kpk32, &Spk32, &Fpk32, &Lpk32, &Ppk32};
     for (DevBuf* b : all) b->release();
@@ -745,8 +750,7 @@ dgd_status step_impl(dgd_handle* h, long long nsteps) {
   using T = typename Prec<P>::T;
   const bool ivm = h->law == 1;
   for (long long it = 0; it < nsteps; ++it) {
-    h->points_in_uz = h->predictor == 1;
-    h->points_dt = h->dt;
+    h->points = {h->predictor == 1, false, h->dt};
     if (h->predictor == 1) {
       const StepArgs<P> a = make_args<N, P>(h);
       if (ivm)
@@ -825,9 +829,10 @@ dgd_status lts_advance(dgd_handle* h, int c, double t) {
 template <int N, int P> struct LtsFn {
   static dgd_status run(dgd_handle* h, long long nmacro) {
     using T = typename Prec<P>::T;
-    h->points_in_uz = false;
     const double mdt = h->lts_dt0 * (double)(1LL << (h->nclusters - 1));
     for (long long k = 0; k < nmacro; ++k) {
+      h->points = {false, true, h->lts_dt0};
+      h->points_ecl.release();
       constexpr int SP = StepPrec<P>::value;
       dgd_status s = h->law == 1 ? lts_advance<N, SP, IvmStep>(h, h->nclusters - 1, h->t)
                                  : lts_advance<N, SP, CdmStep>(h, h->nclusters - 1, h->t);
@@ -883,7 +888,9 @@ template <int N, int P> struct TimePointsFn {
   static dgd_status run(dgd_handle* h, double* out) {
     constexpr int SP = StepPrec<P>::value;
     StepArgs<SP> a = make_args<N, SP>(h);
-    set_dt<SP>(a, h->points_dt);
+    a.dt = h->points.dt;
+    if (h->points.clustered)
+      a.ecl = (const signed char*)(h->points_ecl.p ? h->points_ecl.p : h->ecl.p);
     hipLaunchKernelGGL((k_time_points<N, SP>), dim3((unsigned)h->ne), dim3(64), 0, h->stream, a, out);
     HIPCHK(h, hipGetLastError());
     return DGD_OK;
@@ -1197,7 +1204,8 @@ dgd_status alloc_state(dgd_handle* h) {
   }
   if ((s = dalloc(h, h->Dz, E * h->dz_elem))) return s;
   HIPCHK(h, hipMemsetAsync(h->Dz.p, 0, h->Dz.n, h->stream));
-  h->points_in_uz = false;
+  h->points = {};
+  h->points_ecl.release();
   // time-point states: only the Picard predictor and the adjoint keep them
   if (h->predictor == 1) {
     if ((s = alloc_uz(h, h->Uz, 1))) return s;
@@ -1663,6 +1671,8 @@ dgd_status dgd_set_clusters(dgd_handle* h, const int32_t* cluster, double dt0) {
   if (!h) return DGD_EINVAL;
   if (!h->have_mesh) return fail(h, DGD_ESTATE, "set_mesh first");
   invalidate_tape(h);
+  // (the derivatives of the last step stay those of its clusters)
+  if (h->points.clustered && !h->points_ecl.p) std::swap(h->ecl, h->points_ecl);
   for (auto* v : {&h->lts_el, &h->lts_fl, &h->lts_acc})
     for (DevBuf& b : *v) b.release();
   h->nclusters = 0;
@@ -2033,7 +2043,7 @@ dgd_status dgd_get_kernel_times(dgd_handle* h, double* ms, int64_t* launches) {
 dgd_status dgd_get_time_point_states(dgd_handle* h, double* out) {
   if (!h || !out) return DGD_EINVAL;
   if (!h->have_state) return fail(h, DGD_ESTATE, "no state");
-  if (!h->points_in_uz) {
+  if (!h->points.in_uz) {
     const size_t n = (size_t)h->ne * h->ref.Nt * 10 * h->ref.L;
     dgd_status s = dalloc(h, h->tmp, n * sizeof(double));
     if (s || (s = dispatch<TimePointsFn>(h, (double*)h->tmp.p))) return s;

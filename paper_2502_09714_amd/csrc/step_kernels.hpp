@@ -1556,7 +1556,8 @@ void k_face(StepArgs<P> a, const int* faces, long long nfaces, typename Prec<P>:
 }
 
 // Time-point states of the derivatives in Dz (the Taylor sums of Eq.
-// taylor_expansion), [E][Nt][10][L] FP64, for dgd_get_time_point_states.
+// taylor_expansion), [E][Nt][10][L] FP64, for dgd_get_time_point_states; with
+// clusters (a.ecl) each element over its own step.
 template <int N, int P>
 __global__ __launch_bounds__(64) void k_time_points(StepArgs<P> a, double* out) {
   using T = typename Prec<P>::T;
@@ -1564,6 +1565,7 @@ __global__ __launch_bounds__(64) void k_time_points(StepArgs<P> a, double* out) 
   using DV = Deriv<N>;
   constexpr int L = DM::L, Nt = DM::Nt;
   const long long e = blockIdx.x;
+  const T dt = (T)(a.ecl ? a.dt * (double)(1 << a.ecl[e]) : a.dt);
   auto at = [&](int l, int j) -> T {
     const int c = j >> 4, f0 = DV::frag0(c);
     if (l >= DV::rows(j)) return T(0);
@@ -1572,7 +1574,7 @@ __global__ __launch_bounds__(64) void k_time_points(StepArgs<P> a, double* out) 
   for (int idx = threadIdx.x; idx < 10 * L; idx += 64) {
     const int p = idx / L, l = idx - p * L;
     for (int z = 0; z < Nt; ++z) {
-      const T h = a.hz[z];
+      const T h = a.tau[z] * dt;
       T v;
       if (p == 9) {
         v = at(l, 9) + h * at(l, 10);

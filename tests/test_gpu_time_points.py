@@ -1,0 +1,58 @@
+"""dgd_get_time_point_states: what it returns after each kind of call."""
+import numpy as np
+import pytest
+
+from oracle.quadrature import time_rule
+from workloads import make_workload
+
+pytestmark = pytest.mark.gpu
+
+# one prediction from states that agree to rounding; FP32 states are extrapolated to the step's start from the
+# N + 1 time points (Lebesgue constant below 10), so a factor 10 above the rounding of the states
+TOL = {"fp64": 1e-13, "fp32": 2e-5}
+
+
+def _sim(w, prec):
+    from paper_2502_09714_amd import api
+    return api.from_workload(w, prec)
+
+
+def _rel(a, b):
+    """Largest relative difference over the quantity groups, of (E, Nt, 10, L) arrays."""
+    return max(np.linalg.norm((a - b)[:, :, g]) / np.linalg.norm(b[:, :, g])
+               for g in (slice(0, 6), slice(6, 9), slice(9, 10)))
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("N", [1, 2, 3, 4])
+def test_after_clustered_steps(N, prec):
+    """The prediction is local to the element: each element's states are those that a global step of the
+    length of its own predicts from the state at its start (the value at tau = 0 of the polynomial through
+    them).  Clusters that are replaced afterwards do not change them."""
+    w = make_workload("c2", n=3, N=N)
+    sim = _sim(w, prec)
+    cent = w.mesh["xyz"][w.mesh["tets"]].mean(axis=1)
+    cl = (cent[:, 0] < 0.5 * w.mesh["length"]).astype(np.int32)
+    dt0 = 0.5 * w.dt
+    sim.set_clusters(cl, dt0)
+    sim.step_lts(2)
+    got = sim.get_time_point_states()
+    sim.set_clusters(1 - cl, 0.25 * dt0)
+    assert np.array_equal(sim.get_time_point_states(), got)
+    sim.set_clusters(None)
+    sim.set_params(3.0 * w.dt, w.alpha_max)
+    assert np.array_equal(sim.get_time_point_states(), got)
+    sim.close()
+    tau = time_rule(N)[0].numpy()
+    at0 = np.array([np.prod([-tau[k] / (tau[j] - tau[k]) for k in range(N + 1) if k != j]) for j in range(N + 1)])
+    start = np.einsum("z,ezpl->epl", at0, got)
+    ref = _sim(w, prec)
+    ref.set_state(np.ascontiguousarray(start))
+    for c in (0, 1):
+        ref.set_params(dt0 * 2 ** c, w.alpha_max)
+        ref.set_state(np.ascontiguousarray(start))
+        ref.step(1)
+        e = _rel(got[cl == c], ref.get_time_point_states()[cl == c])
+        print(N, prec, "cluster", c, e, flush=True)
+        assert e < TOL[prec]
+    ref.close()
