@@ -885,13 +885,13 @@ template <int N, int P> struct PredictFn {
 };
 
 template <int N, int P> struct TimePointsFn {
-  static dgd_status run(dgd_handle* h, double* out) {
+  static dgd_status run(dgd_handle* h, long long e0, long long count, double* out) {
     constexpr int SP = StepPrec<P>::value;
     StepArgs<SP> a = make_args<N, SP>(h);
     a.dt = h->points.dt;
     if (h->points.clustered)
       a.ecl = (const signed char*)(h->points_ecl.p ? h->points_ecl.p : h->ecl.p);
-    hipLaunchKernelGGL((k_time_points<N, SP>), dim3((unsigned)h->ne), dim3(64), 0, h->stream, a, out);
+    hipLaunchKernelGGL((k_time_points<N, SP>), dim3((unsigned)count), dim3(64), 0, h->stream, a, e0, out);
     HIPCHK(h, hipGetLastError());
     return DGD_OK;
   }
@@ -2044,10 +2044,22 @@ dgd_status dgd_get_time_point_states(dgd_handle* h, double* out) {
   if (!h || !out) return DGD_EINVAL;
   if (!h->have_state) return fail(h, DGD_ESTATE, "no state");
   if (!h->points.in_uz) {
-    const size_t n = (size_t)h->ne * h->ref.Nt * 10 * h->ref.L;
-    dgd_status s = dalloc(h, h->tmp, n * sizeof(double));
-    if (s || (s = dispatch<TimePointsFn>(h, (double*)h->tmp.p))) return s;
-    HIPCHK(h, hipMemcpyAsync(out, h->tmp.p, n * sizeof(double), hipMemcpyDeviceToHost, h->stream));
+    // through a scratch buffer of at most 64 MiB, less where memory is short
+    const size_t per = (size_t)h->ref.Nt * 10 * h->ref.L;
+    long long chunk = std::min<long long>(h->ne, ((size_t)64 << 20) / (per * sizeof(double)));
+    dgd_status s;
+    while ((s = dalloc(h, h->tmp, (size_t)chunk * per * sizeof(double))) == DGD_ENOMEM && chunk > 1) {
+      (void)hipGetLastError();
+      h->err.clear();
+      chunk /= 2;
+    }
+    for (long long e0 = 0; e0 < h->ne && s == DGD_OK; e0 += chunk) {
+      const long long n = std::min(chunk, h->ne - e0);
+      if ((s = dispatch<TimePointsFn>(h, e0, n, (double*)h->tmp.p))) break;
+      HIPCHK(h, hipMemcpyAsync(out + (size_t)e0 * per, h->tmp.p, (size_t)n * per * sizeof(double),
+                               hipMemcpyDeviceToHost, h->stream));
+    }
+    if (s) return s;
     HIPCHK(h, hipStreamSynchronize(h->stream));
     h->tmp.release();
     return DGD_OK;

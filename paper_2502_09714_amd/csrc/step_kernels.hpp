@@ -1556,15 +1556,16 @@ void k_face(StepArgs<P> a, const int* faces, long long nfaces, typename Prec<P>:
 }
 
 // Time-point states of the derivatives in Dz (the Taylor sums of Eq.
-// taylor_expansion), [E][Nt][10][L] FP64, for dgd_get_time_point_states; with
-// clusters (a.ecl) each element over its own step.
+// taylor_expansion) of the elements from e0 on, [E][Nt][10][L] FP64, for
+// dgd_get_time_point_states; with clusters (a.ecl) each element over its own step.
 template <int N, int P>
-__global__ __launch_bounds__(64) void k_time_points(StepArgs<P> a, double* out) {
+__global__ __launch_bounds__(64) void k_time_points(StepArgs<P> a, long long e0, double* out) {
   using T = typename Prec<P>::T;
   using DM = Dims<N>;
   using DV = Deriv<N>;
   constexpr int L = DM::L, Nt = DM::Nt;
-  const long long e = blockIdx.x;
+  const long long e = e0 + blockIdx.x;
+  out -= (size_t)e0 * Nt * 10 * L;
   const T dt = (T)(a.ecl ? a.dt * (double)(1 << a.ecl[e]) : a.dt);
   auto at = [&](int l, int j) -> T {
     const int c = j >> 4, f0 = DV::frag0(c);

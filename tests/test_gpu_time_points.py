@@ -56,3 +56,20 @@ def test_after_clustered_steps(N, prec):
         print(N, prec, "cluster", c, e, flush=True)
         assert e < TOL[prec]
     ref.close()
+
+
+@pytest.mark.parametrize("N,n", [(4, 10), (3, 13)])
+def test_query_in_slices(N, n):
+    """More elements than one slice of the query's 64 MiB of scratch (4793 at degree 4, 10485 at degree 3):
+    every element's states extrapolate to the state it was set to."""
+    w = make_workload("c2", n=n, N=N)
+    sim = _sim(w, "fp64")
+    U = sim.get_state()
+    sim.step(1)
+    got = sim.get_time_point_states()
+    sim.close()
+    tau = time_rule(N)[0].numpy()
+    at0 = np.array([np.prod([-tau[k] / (tau[j] - tau[k]) for k in range(N + 1) if k != j]) for j in range(N + 1)])
+    start = np.einsum("z,ezpl->epl", at0, got)
+    scale = np.abs(got).max(axis=(0, 1, 3))[None, :, None]
+    assert (np.abs(start - U) / scale).max() < 1e-12
