@@ -132,6 +132,7 @@ struct dgd_handle {
   DevBuf lam[2], gtr, gmuf, lzf, gmu, gcd, adjW9, adjWa, dlds, seg9, sega, seguz, segd, segacc, save9, savea;
   DevBuf st9, sta;               // the state U^n handed to dgd_adjoint_step, working precision
   void* uz_override = nullptr;   // time-point states of the step being replayed
+  void* dz_override = nullptr;   // and where its derivatives go
   void* d_keep = nullptr;        // where that replay keeps D^1..D^N (or null)
   void* acc_keep = nullptr;      // where it keeps the cell-averaged tangents (or null)
   std::vector<DevBuf> ck9, cka;
@@ -615,7 +616,7 @@ StepArgs<P> make_args(dgd_handle* h) {
   a.ecl = nullptr;
   a.lts_c = -1;
   a.facc = nullptr;
-  a.Dz = (T*)h->Dz.p;
+  a.Dz = (T*)(h->dz_override ? h->dz_override : h->Dz.p);
   a.Vw = h->Vw.p;
   a.Vt = (const T*)h->Vt.p;
   a.Kw = h->Kw.p;
@@ -2260,6 +2261,8 @@ dgd_status dgd_backward(dgd_handle* h, const double* dl_dseis, double* grad_mu0,
   if ((s = copy_state(h, h->save9.p, h->savea.p, h->U9[h->cur].p, h->Ua[h->cur].p))) return s;
   const double t_save = h->t;
   const bool prof = h->profiling;
+  const auto points = h->points;
+  if (h->gtr.n < E * h->dz_elem) return fail(h, DGD_ESTATE, "no room for the replay's derivatives");
   int lc = 0;
   h->nrec = 0;   // the replay records nothing
   const long long nck = (long long)h->ck9.size();
@@ -2281,8 +2284,15 @@ dgd_status dgd_backward(dgd_handle* h, const double* dl_dseis, double* grad_mu0,
         s = dispatch<PredictFn>(h);
         h->uz_override = h->d_keep = h->acc_keep = nullptr;
       }
-      // (the segment's last state is not stepped further)
-      if (s == DGD_OK && j + 1 < j1) s = dispatch<StepFn>(h, 1);
+      // (the segment's last state is not stepped further.  The replayed steps'
+      // derivatives go where the adjoint's trace cotangents will: the last step's stay
+      // for dgd_get_time_point_states)
+      if (s == DGD_OK && j + 1 < j1) {
+        h->dz_override = h->gtr.p;
+        s = dispatch<StepFn>(h, 1);
+        h->dz_override = nullptr;
+        h->points = points;
+      }
     }
     h->profiling = prof;
     for (long long j = j1 - 1; j >= j0 && s == DGD_OK; --j) {

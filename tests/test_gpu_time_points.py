@@ -73,3 +73,22 @@ def test_query_in_slices(N, n):
     start = np.einsum("z,ezpl->epl", at0, got)
     scale = np.abs(got).max(axis=(0, 1, 3))[None, :, None]
     assert (np.abs(start - U) / scale).max() < 1e-12
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("N", [1, 2, 4])
+def test_backward_leaves_the_last_steps(N, prec):
+    """Replayed steps of dgd_backward are not the solver's last one."""
+    w = make_workload("c4", n=3, N=N)
+    sim = _sim(w, prec)
+    sim.forward_checkpointed(5, 2)
+    run = sim.get_time_point_states()
+    cot = np.ones((5, sim.nrec, 3))
+    grad = sim.backward(cot)
+    assert np.array_equal(sim.get_time_point_states(), run)
+    sim.step(2)
+    later = sim.get_time_point_states()
+    again = sim.backward(cot)
+    assert np.array_equal(sim.get_time_point_states(), later)
+    assert np.array_equal(again[0], grad[0]) and np.array_equal(again[1], grad[1])
+    sim.close()
