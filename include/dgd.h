@@ -206,8 +206,11 @@ dgd_status dgd_get_time(const dgd_handle* h, double* t);
  * U_z = U^n + dt sum_j Om_zj R(U_j), Om_zj = int_0^tau_z l_j, from U_z = U^n
  * (iterations = 0 means N + 1).  The corrector is unchanged.  The discrete
  * adjoint is that of the Cauchy-Kovalevskaya predictor: its calls return
- * EINVAL under this one.  EINVAL for another kind or iterations < 0.  Drops
- * a checkpointed run. */
+ * EINVAL under this one.  EINVAL for another kind or iterations < 0; ENOMEM
+ * (with the predictor unchanged) if the time-point states that
+ * DGD_PREDICT_PICARD keeps cannot be allocated: they take the place of the
+ * smaller derivatives kept for DGD_PREDICT_CK, here or in dgd_set_mesh.
+ * Drops a checkpointed run. */
 typedef enum { DGD_PREDICT_CK = 0, DGD_PREDICT_PICARD = 1 } dgd_predictor;
 dgd_status dgd_set_predictor(dgd_handle* h, int kind, int iterations);
 
@@ -346,7 +349,11 @@ dgd_status dgd_get_kernel_times(dgd_handle* h, double* ms /* 10 */, int64_t* lau
  * time-point states U(t_n + tau_z dt) of its last step (the Taylor sums of Eq.
  * taylor_expansion at the Gauss-Legendre points tau_z), [ne][Nt][10][L] FP64
  * host; after dgd_step_lts those of each element's own last step.  Zeros before
- * the first step.  Synchronises; ESTATE before a state is set. */
+ * the first step.  An adjoint step that predicts for itself (dgd_adjoint_step,
+ * dgd_adjoint_step_host; dgd_backward on DGD_BF16 handles or when short of
+ * memory) leaves the states of the step that it differentiates in their place.
+ * Synchronises; ESTATE before a state is set, or where a later first call of
+ * the Picard predictor or the adjoint found no memory to keep them. */
 dgd_status dgd_get_time_point_states(dgd_handle* h, double* out);
 
 /* ---------------------------------------------------------------------------

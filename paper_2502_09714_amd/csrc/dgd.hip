@@ -79,11 +79,12 @@ struct dgd_handle {
   DevBuf Vw, Vt, Kw, Kt, Ktw, PXw, PXa, PXleft, Rw, Fst, Fstt, Psi, Psrc, mixP, mixV;
   DevBuf PVw, PVt, VTa, STw, STt;   // transposed (discrete adjoint)
   size_t dz_elem = 0;     // bytes of one element's time derivatives
-  // what the last step left: its time-point states in Uz, or derivatives in Dz and the
-  // step they belong to (element e: dt 2^cluster[e] after local time stepping)
+  // what the last step left: its time-point states in Uz, or derivatives (derivs()) and
+  // the step they belong to (element e: dt 2^cluster[e] after local time stepping)
   struct Points {
     bool in_uz = false, clustered = false;
     double dt = 0.0;
+    bool lost = false;    // given up to make room for Uz
   } points;
   DevBuf points_ecl;      // its clusters, where dgd_set_clusters has replaced them since
   int predictor = 0;      // 0: linearised Cauchy-Kovalevskaya, 1: Picard iteration
@@ -111,7 +112,8 @@ struct dgd_handle {
   std::vector<double> rho_h;
   int law = 0;   // 0: continuum damage (Eq. cdb-model), 1: internal variable (Eq. ivm-model)
   // state
-  DevBuf U9[2], Ua[2], Dz, Uz, flag, tmp;   // tmp: per-call host transfers
+  DevBuf U9[2], Ua[2], flag, tmp;   // tmp: per-call host transfers
+  DevBuf Dz, Uz;          // derivatives; or, once time-point states are needed, both (need_uz)
   int cur = 0;
   double dt = 0.0, amax = 0.5, t = 0.0;
   long long steps_since_check = 0, check_every = 64;
@@ -577,6 +579,24 @@ template <int P> void set_dt(StepArgs<P>& a, double dt) {
   }
 }
 
+// bytes of the time-point states of all elements, [E][Nt][L][10], and of the
+// zeroed tail after them that the matrix cores' in-place reads of the last
+// element's padding rows reach (KPL * 16 entries)
+size_t uz_bytes(const dgd_handle* h) {
+  return (size_t)h->ne * h->ref.Nt * h->ref.L * 10 * h->tsize;
+}
+size_t uz_tail(const dgd_handle* h) { return (size_t)h->kpl * 16 * h->tsize; }
+
+// Derivatives of a Cauchy-Kovalevskaya step and time-point states (Picard predictor,
+// adjoint) are never live together: where Uz exists the derivatives use its memory,
+// from its start if they fit (degree 2 and up), else after it.
+size_t dz_offset(const dgd_handle* h) {
+  return (size_t)h->ne * h->dz_elem <= uz_bytes(h) ? 0 : uz_bytes(h) + uz_tail(h);
+}
+void* derivs(const dgd_handle* h) {
+  return h->Uz.p ? (char*)h->Uz.p + dz_offset(h) : h->Dz.p;
+}
+
 template <int N, int P>
 StepArgs<P> make_args(dgd_handle* h) {
   using T = typename Prec<P>::T;
@@ -616,7 +636,7 @@ StepArgs<P> make_args(dgd_handle* h) {
   a.ecl = nullptr;
   a.lts_c = -1;
   a.facc = nullptr;
-  a.Dz = (T*)(h->dz_override ? h->dz_override : h->Dz.p);
+  a.Dz = (T*)(h->dz_override ? h->dz_override : derivs(h));
   a.Vw = h->Vw.p;
   a.Vt = (const T*)h->Vt.p;
   a.Kw = h->Kw.p;
@@ -929,14 +949,6 @@ dgd_status ensure_adjoint_packs(dgd_handle* h) {
   return s;
 }
 
-// bytes of the time-point states of all elements, [E][Nt][L][10], and of the
-// zeroed tail after them that the matrix cores' in-place reads of the last
-// element's padding rows reach (KPL * 16 entries)
-size_t uz_bytes(const dgd_handle* h) {
-  return (size_t)h->ne * h->ref.Nt * h->ref.L * 10 * h->tsize;
-}
-size_t uz_tail(const dgd_handle* h) { return (size_t)h->kpl * 16 * h->tsize; }
-
 // a buffer of `slots` consecutive time-point-state arrays and the zeroed tail
 dgd_status alloc_uz(dgd_handle* h, DevBuf& b, size_t slots) {
   dgd_status s = dalloc(h, b, slots * uz_bytes(h) + uz_tail(h));
@@ -945,11 +957,43 @@ dgd_status alloc_uz(dgd_handle* h, DevBuf& b, size_t slots) {
   return DGD_OK;
 }
 
+// Uz, with the last step's derivatives moved into it.  Where there is no memory for both
+// at a time the derivatives are given up (only dgd_get_time_point_states misses them).
+dgd_status need_uz(dgd_handle* h) {
+  if (h->Uz.p) return DGD_OK;
+  const size_t dz = (size_t)h->ne * h->dz_elem, at = dz_offset(h);
+  const size_t bytes = uz_bytes(h) + uz_tail(h) + (at ? dz : 0);
+  DevBuf u;
+  dgd_status s = dalloc(h, u, bytes);
+  if (s == DGD_ENOMEM && h->Dz.p) {
+    (void)hipGetLastError();
+    HIPCHK(h, hipStreamSynchronize(h->stream));
+    h->Dz.release();
+    h->points = {};
+    h->points.lost = true;
+    if ((s = dalloc(h, u, bytes))) {
+      (void)hipGetLastError();
+      const std::string err = h->err;
+      if (dalloc(h, h->Dz, dz)) h->have_mesh = h->have_state = false;
+      h->err = err;
+    }
+  }
+  if (s) return s;
+  std::swap(h->Uz, u);
+  HIPCHK(h, hipMemsetAsync(h->Uz.p, 0, bytes, h->stream));
+  if (h->Dz.p) {
+    HIPCHK(h, hipMemcpyAsync((char*)h->Uz.p + at, h->Dz.p, dz, hipMemcpyDeviceToDevice, h->stream));
+    HIPCHK(h, hipStreamSynchronize(h->stream));
+    h->Dz.release();
+  }
+  return DGD_OK;
+}
+
 dgd_status alloc_adjoint(dgd_handle* h) {
   const size_t E = (size_t)h->ne, L = h->ref.L;
   dgd_status s;
   if ((s = ensure_adjoint_packs(h))) return s;
-  if (!h->Uz.p && (s = alloc_uz(h, h->Uz, 1))) return s;
+  if ((s = need_uz(h))) return s;
   if ((s = dalloc(h, h->lam[0], lam_elems(h) * h->tsize)) ||
       (s = dalloc(h, h->lam[1], lam_elems(h) * h->tsize)) ||
       (s = dalloc(h, h->gtr, (size_t)h->nfaces * 2 * h->ref.Nt * h->ref.Ns * 10 * h->tsize)) ||
@@ -1016,8 +1060,10 @@ dgd_status adjoint_step_impl(dgd_handle* h, const void* U9, const double* Ua, co
     A.gmu = gmu ? gmu : (double*)h->gmu.p;
     A.gcd = gcd ? gcd : (double*)h->gcd.p;
     // time-point states of this step: recomputed unless the replay kept them
-    if (!uz)
+    if (!uz) {
+      h->points = {true, false, h->dt};
       timed(h, 4, [&] { hipLaunchKernelGGL((k_predict<N, P>), grid, block, 0, h->stream, a); });
+    }
     const long long fper = (h->nfaces + 7) / 8;
     timed(h, 5, [&] {
       hipLaunchKernelGGL((k_adj_face<N, P>), dim3((unsigned)(8 * fper)), block, 0, h->stream, A,
@@ -1203,15 +1249,15 @@ dgd_status alloc_state(dgd_handle* h) {
     if ((s = dalloc(h, h->U9[i], E * 9 * L * h->tsize))) return s;
     if ((s = dalloc(h, h->Ua[i], E * L * sizeof(double)))) return s;
   }
-  if ((s = dalloc(h, h->Dz, E * h->dz_elem))) return s;
-  HIPCHK(h, hipMemsetAsync(h->Dz.p, 0, h->Dz.n, h->stream));
   h->points = {};
   h->points_ecl.release();
-  // time-point states: only the Picard predictor and the adjoint keep them
+  h->Uz.release();
   if (h->predictor == 1) {
-    if ((s = alloc_uz(h, h->Uz, 1))) return s;
+    h->Dz.release();
+    if ((s = need_uz(h))) return s;
   } else {
-    h->Uz.release();
+    if ((s = dalloc(h, h->Dz, E * h->dz_elem))) return s;
+    HIPCHK(h, hipMemsetAsync(h->Dz.p, 0, h->Dz.n, h->stream));
   }
   if ((s = dalloc(h, h->fflux, (size_t)h->nfaces * h->ref.Ns * 10 * h->tsize))) return s;
   if ((s = dalloc(h, h->flag, sizeof(int)))) return s;
@@ -1659,8 +1705,8 @@ dgd_status dgd_set_predictor(dgd_handle* h, int kind, int iterations) {
   if ((kind != DGD_PREDICT_CK && kind != DGD_PREDICT_PICARD) || iterations < 0)
     return fail(h, DGD_EINVAL, "predictor kind 0 or 1 and iterations >= 0 needed");
   invalidate_tape(h);
-  if (kind == DGD_PREDICT_PICARD && h->have_mesh && !h->Uz.p) {
-    const dgd_status s = alloc_uz(h, h->Uz, 1);
+  if (kind == DGD_PREDICT_PICARD && h->have_mesh) {
+    const dgd_status s = need_uz(h);
     if (s) return s;
   }
   h->predictor = kind;
@@ -2044,6 +2090,7 @@ dgd_status dgd_get_kernel_times(dgd_handle* h, double* ms, int64_t* launches) {
 dgd_status dgd_get_time_point_states(dgd_handle* h, double* out) {
   if (!h || !out) return DGD_EINVAL;
   if (!h->have_state) return fail(h, DGD_ESTATE, "no state");
+  if (h->points.lost) return fail(h, DGD_ESTATE, "the last step's derivatives were given up for memory");
   if (!h->points.in_uz) {
     // through a scratch buffer of at most 64 MiB, less where memory is short
     const size_t per = (size_t)h->ref.Nt * 10 * h->ref.L;
