@@ -76,8 +76,12 @@ struct dgd_handle {
   // reference data on the device
   DevBuf Vpk, Kpk, Spk, Fpk, Lpk, Ppk, Vd, wqd, Pwd, betad;
   // Cauchy-Kovalevskaya step (step_kernels.hpp)
-  DevBuf Vw, Vt, Kw, Kt, Ktw, PXw, PXa, PXleft, Rw, Fst, Fstt, Psi, Psrc, mixP, mixV;
-  DevBuf PVw, PVt, VTa, STw, STt;   // transposed (discrete adjoint)
+  DevBuf step_tab;        // all of them, one after the other
+  const void *Vw = nullptr, *Vt = nullptr, *Kw = nullptr, *Kt = nullptr, *Ktw = nullptr, *PXw = nullptr,
+             *PXa = nullptr, *PXleft = nullptr, *Rw = nullptr, *Fst = nullptr, *Fstt = nullptr,
+             *Psi = nullptr, *Psrc = nullptr, *mixP = nullptr, *mixV = nullptr;
+  DevBuf adj_tab;         // transposed, for k_adj_points: packed by the first adjoint call
+  const void *PVw = nullptr, *PVt = nullptr, *VTa = nullptr, *STw = nullptr, *STt = nullptr;
   size_t dz_elem = 0;     // bytes of one element's time derivatives
   // what the last step left: its time-point states in Uz, or derivatives (derivs()) and
   // the step they belong to (element e: dt 2^cluster[e] after local time stepping)
@@ -153,9 +157,8 @@ struct dgd_handle {
                      &p_elem, &p_range, &p_order, &s_M6, &s_dphi, &s_onset, &s_param, &s_rhoJ, &r_elem, &r_phi, &seis,
                      &VTpk, &STpk, &PTpk, &KTpk, &lam[0], &lam[1], &gtr, &gmuf, &lzf, &gmu, &gcd, &adjW9,
                      &adjWa, &dlds, &seg9, &sega, &seguz, &segd, &segacc, &save9, &savea, &st9, &sta,
-                     &ecl, &points_ecl, &facc, &Vw, &Vt, &Kw, &Kt, &Ktw, &PXw, &PXa,
-                     &PXleft, &Rw, &Fst, &Fstt, &Psi, &Psrc, &mixP, &mixV, &PVw, &PVt, &VTa, &STw, &STt,
-                      &Dz, &Vpk32, &Kpk32, &Spk32, &Fpk32, &Lpk32, &Ppk32};
+                     &ecl, &points_ecl, &facc, &step_tab, &adj_tab,
+                     &Dz, &Vpk32, &Kpk32, &Spk32, &Fpk32, &Lpk32, &Ppk32};
     for (DevBuf* b : all) b->release();
     for (DevBuf& b : ck9) b.release();
     for (DevBuf& b : cka) b.release();
@@ -208,6 +211,30 @@ dgd_status upload(dgd_handle* h, DevBuf& b, const std::vector<V>& v) {
   if (v.empty()) return DGD_OK;
   HIPCHK(h, hipMemcpyAsync(b.p, v.data(), v.size() * sizeof(V), hipMemcpyHostToDevice, h->stream));
   HIPCHK(h, hipStreamSynchronize(h->stream));
+  return DGD_OK;
+}
+
+// several arrays in one buffer, one allocation and one copy; *at receives each one's
+// address (256-byte aligned)
+struct Part {
+  const void* data;
+  size_t bytes;
+  const void** at;
+  template <class V>
+  Part(const std::vector<V>& v, const void** a) : data(v.data()), bytes(v.size() * sizeof(V)), at(a) {}
+};
+dgd_status upload_parts(dgd_handle* h, DevBuf& b, std::initializer_list<Part> parts) {
+  std::vector<char> all;
+  std::vector<size_t> off;
+  for (const Part& p : parts) {
+    off.push_back(all.size());
+    all.insert(all.end(), (const char*)p.data, (const char*)p.data + p.bytes);
+    all.resize((all.size() + 255) / 256 * 256);
+  }
+  const dgd_status s = upload(h, b, all);
+  if (s) return s;
+  size_t k = 0;
+  for (const Part& p : parts) *p.at = (const char*)b.p + off[k++];
   return DGD_OK;
 }
 
@@ -324,7 +351,7 @@ dgd_status build_packed(dgd_handle* h) {
                      4, KSL));
     }
     for (int e = 0; e < 3; ++e) {
-      for (int c = 0; c < DM::NCH; ++c)
+      for (int c = 0; c < DM::NCH && !AdjSplit<N>::value; ++c)
         append(stt, pack_A<P>(
                         [&](int m, int kk) {
                           int q = 64 * c + m;
@@ -391,32 +418,18 @@ dgd_status build_step_packs(dgd_handle* h) {
   auto Ft = [&](int ff, int i, int l) {
     return (i < Ns && l < L) ? r.F[((size_t)ff * Ns + i) * L + l] : 0.0;
   };
-  std::vector<char> vw, kw, ktw, pw, pa, rw, fs, pv, vta, sw;
-  std::vector<T> vt, kt, pl, ft, pvt, stl, psi, ps((size_t)Q4 * L * 4, T(0));
+  std::vector<char> vw, kw, ktw, pw, pa, rw, fs;
+  std::vector<T> vt, kt, pl, ft, psi, ps((size_t)Q4 * L * 4, T(0));
   auto tail = [](std::vector<T>& out, auto val) {
     for (int lane = 0; lane < 64; ++lane) out.push_back((T)val(lane & 15, lane >> 4));
   };
   for (int t = 0; t < NCH * 4; ++t)
-    for (int s = 0; s < SL::WIDE; ++s) {
+    for (int s = 0; s < SL::WIDE; ++s)
       append_frag<M>(vw, [&](int n, int g, int j) { return V(16 * t + n, mode(s, g, j)); });
-      append_frag<M>(pv, [&](int n, int g, int j) { return Pw(mode(s, g, j), 16 * t + n); });
-    }
   if constexpr (SL::TAIL)
-    for (int t = 0; t < NCH * 4; ++t) {
-      tail(vt, [&](int n, int g) { return V(16 * t + n, 32 * SL::WIDE + g); });
-      tail(pvt, [&](int n, int g) { return Pw(32 * SL::WIDE + g, 16 * t + n); });
-    }
+    for (int t = 0; t < NCH * 4; ++t) tail(vt, [&](int n, int g) { return V(16 * t + n, 32 * SL::WIDE + g); });
   if constexpr (X3 && Deriv<N>::rows(16 * (Deriv<N>::NT - 1)) <= 4)
     for (int t = 0; t < NCH * 4; ++t) tail(vt, [&](int n, int g) { return V(16 * t + n, g); });
-  auto Sw = [&](int e, int l, int q) {
-    return (l < L && q < Q) ? r.Sw[((size_t)e * L + l) * Q + q] : 0.0;
-  };
-  for (int e = 0; e < 3; ++e)
-    for (int t = 0; t < NCH * 4; ++t) {
-      for (int s = 0; s < SL::WIDE; ++s)
-        append_frag<M>(sw, [&](int n, int g, int j) { return Sw(e, mode(s, g, j), 16 * t + n); });
-      if constexpr (SL::TAIL) tail(stl, [&](int n, int g) { return Sw(e, 32 * SL::WIDE + g, 16 * t + n); });
-    }
   for (int e = 0; e < 3; ++e)
     for (int t = 0; t < NT1; ++t) {
       for (int s = 0; s < SL::WIDE; ++s)
@@ -427,7 +440,10 @@ dgd_status build_step_packs(dgd_handle* h) {
   if constexpr (PointStiffness<N>::value) {
     for (int s = 0; s < PointStiffness<N>::steps; ++s)
       for (int e = 0; e < 3; ++e)
-        append_frag<M>(ktw, [&](int n, int g, int) { return Sw(e, n, 16 * (s / 4) + 4 * g + s % 4); });
+        append_frag<M>(ktw, [&](int n, int g, int) {
+          const int q = 16 * (s / 4) + 4 * g + s % 4;
+          return (n < L && q < Q) ? r.Sw[((size_t)e * L + n) * Q + q] : 0.0;
+        });
   } else {
     constexpr auto list = kt_list<N, M>();
     for (int k = 0; k < list.n; ++k)
@@ -443,10 +459,6 @@ dgd_status build_step_packs(dgd_handle* h) {
           return Pw(mperm<N, M>(t, n), q);
         };
         append_frag<M>(pa, val);
-        append_frag<M>(vta, [&](int n, int g, int j) {
-          const int q = 64 * c + (X3 ? 32 * s + 8 * g + j : 16 * (s / 4) + 4 * g + s % 4);
-          return V(q, mperm<N, M>(t, n));
-        });
         if (t < ProjTiles<N>::MTP) append_frag<M>(pw, val);
       }
   for (int c = 0; c < NCH; ++c)
@@ -512,20 +524,55 @@ dgd_status build_step_packs(dgd_handle* h) {
           if (j >= 3 && j < 9 && j - 3 == sym_idx(p - 6, d)) mv[at] = T(-1);
         }
       }
-  dgd_status st;
-  if ((st = upload(h, h->PVw, pv)) || (st = upload(h, h->PVt, pvt)) ||
-      (st = upload(h, h->VTa, vta)) || (st = upload(h, h->STw, sw)) || (st = upload(h, h->STt, stl)))
-    return st;
-  if ((st = upload(h, h->Vw, vw)) || (st = upload(h, h->Vt, vt)) || (st = upload(h, h->Kw, kw)) ||
-      (st = upload(h, h->Kt, kt)) || (st = upload(h, h->Ktw, ktw)) || (st = upload(h, h->PXw, pw)) ||
-      (st = upload(h, h->PXa, pa)) ||
-      (st = upload(h, h->PXleft, pl)) || (st = upload(h, h->Rw, rw)) || (st = upload(h, h->Fst, fs)) ||
-      (st = upload(h, h->Fstt, ft)) ||
-      (st = upload(h, h->Psi, psi)) || (st = upload(h, h->Psrc, ps)) || (st = upload(h, h->mixP, mp)) ||
-      (st = upload(h, h->mixV, mv)))
-    return st;
+  const dgd_status st =
+      upload_parts(h, h->step_tab,
+                   {{vw, &h->Vw}, {vt, &h->Vt}, {kw, &h->Kw}, {kt, &h->Kt}, {ktw, &h->Ktw}, {pw, &h->PXw},
+                    {pa, &h->PXa}, {pl, &h->PXleft}, {rw, &h->Rw}, {fs, &h->Fst}, {ft, &h->Fstt},
+                    {psi, &h->Psi}, {ps, &h->Psrc}, {mp, &h->mixP}, {mv, &h->mixV}});
+  if (st) return st;
   h->dz_elem = (size_t)Deriv<N>::NF * 64 * sizeof(T);
   return DGD_OK;
+}
+
+// transposed projection, evaluation and stiffness over the points (k_adj_points)
+template <int N, int P>
+dgd_status build_adjoint_tables(dgd_handle* h) {
+  using DM = Dims<N>;
+  using T = typename Prec<P>::T;
+  constexpr int M = MatForm<N, P>::value;
+  constexpr bool X3 = M == PREC_X3;
+  constexpr int L = DM::L, Q = DM::Q, MT = DM::MT, NCH = DM::NCH;
+  using SL = Steps<M, L>;
+  const RefData& r = h->ref;
+  auto mode = [](int s, int g, int j) { return X3 ? 32 * s + 16 * (j >> 2) + 4 * g + (j & 3) : 4 * s + g; };
+  std::vector<char> pv, vta, sw;
+  std::vector<T> pvt, stl;
+  auto Pw = [&](int l, int q) { return (l < L && q < Q) ? r.Pw[(size_t)l * Q + q] : 0.0; };
+  auto Sw = [&](int e, int l, int q) {
+    return (l < L && q < Q) ? r.Sw[((size_t)e * L + l) * Q + q] : 0.0;
+  };
+  // wide fragments, then the FP32 step of leftover modes, of val(mode, point)
+  auto add = [&](std::vector<char>& w, std::vector<T>& t, auto val) {
+    for (int k = 0; k < NCH * 4; ++k) {
+      for (int s = 0; s < SL::WIDE; ++s)
+        append_frag<M>(w, [&](int n, int g, int j) { return val(mode(s, g, j), 16 * k + n); });
+      if constexpr (SL::TAIL)
+        for (int lane = 0; lane < 64; ++lane)
+          t.push_back((T)val(32 * SL::WIDE + (lane >> 4), 16 * k + (lane & 15)));
+    }
+  };
+  add(pv, pvt, Pw);
+  for (int e = 0; e < 3; ++e) add(sw, stl, [&](int l, int q) { return Sw(e, l, q); });
+  for (int c = 0; c < NCH; ++c)
+    for (int s = 0; s < (X3 ? 2 : 16); ++s)
+      for (int t = 0; t < MT; ++t)
+        append_frag<M>(vta, [&](int n, int g, int j) {
+          const int q = 64 * c + (X3 ? 32 * s + 8 * g + j : 16 * (s / 4) + 4 * g + s % 4);
+          const int l = mperm<N, M>(t, n);
+          return (q < Q && l < L) ? r.V[(size_t)q * L + l] : 0.0;
+        });
+  return upload_parts(h, h->adj_tab,
+                      {{pv, &h->PVw}, {pvt, &h->PVt}, {vta, &h->VTa}, {sw, &h->STw}, {stl, &h->STt}});
 }
 
 hipEvent_t take_event(dgd_handle* h) {
@@ -637,26 +684,26 @@ StepArgs<P> make_args(dgd_handle* h) {
   a.lts_c = -1;
   a.facc = nullptr;
   a.Dz = (T*)(h->dz_override ? h->dz_override : derivs(h));
-  a.Vw = h->Vw.p;
-  a.Vt = (const T*)h->Vt.p;
-  a.Kw = h->Kw.p;
-  a.Kt = (const T*)h->Kt.p;
-  a.Ktw = h->Ktw.p;
-  a.PXw = h->PXw.p;
-  a.PXleft = (const T*)h->PXleft.p;
-  a.Rw = h->Rw.p;
-  a.PXa = h->PXa.p;
-  a.PVw = h->PVw.p;
-  a.PVt = (const T*)h->PVt.p;
-  a.VTa = h->VTa.p;
-  a.STw = h->STw.p;
-  a.STt = (const T*)h->STt.p;
-  a.Fst = h->Fst.p;
-  a.Fstt = (const T*)h->Fstt.p;
-  a.Psi = (const T*)h->Psi.p;
-  a.Psrc = (const T*)h->Psrc.p;
-  a.mixP = (const int*)h->mixP.p;
-  a.mixV = (const T*)h->mixV.p;
+  a.Vw = h->Vw;
+  a.Vt = (const T*)h->Vt;
+  a.Kw = h->Kw;
+  a.Kt = (const T*)h->Kt;
+  a.Ktw = h->Ktw;
+  a.PXw = h->PXw;
+  a.PXleft = (const T*)h->PXleft;
+  a.Rw = h->Rw;
+  a.PXa = h->PXa;
+  a.PVw = h->PVw;
+  a.PVt = (const T*)h->PVt;
+  a.VTa = h->VTa;
+  a.STw = h->STw;
+  a.STt = (const T*)h->STt;
+  a.Fst = h->Fst;
+  a.Fstt = (const T*)h->Fstt;
+  a.Psi = (const T*)h->Psi;
+  a.Psrc = (const T*)h->Psrc;
+  a.mixP = (const int*)h->mixP;
+  a.mixV = (const T*)h->mixV;
   set_dt<P>(a, h->dt);
   return a;
 }
@@ -929,7 +976,17 @@ size_t lam_elems(const dgd_handle* h) { return (size_t)h->ne * adj_kpl(h) * 16; 
 // FP32 forward operators of a split-BF16 handle (its own packs hold BF16
 // hi/lo pairs), packed once beside them; the transposed adjoint operators
 // come with them.
+template <int N, int P> struct AdjTablesFn {
+  static dgd_status run(dgd_handle* h) {
+    if constexpr (AdjSplit<N>::value) return build_adjoint_tables<N, StepPrec<P>::value>(h);
+    return DGD_OK;
+  }
+};
 dgd_status ensure_adjoint_packs(dgd_handle* h) {
+  if (!h->adj_tab.p) {
+    const dgd_status s = dispatch<AdjTablesFn>(h);
+    if (s) return s;
+  }
   if (h->prec != DGD_BF16 || h->Vpk32.p) return DGD_OK;
   DevBuf* fw[] = {&h->Vpk, &h->Kpk, &h->Spk, &h->Fpk, &h->Lpk, &h->Ppk};
   DevBuf* f32[] = {&h->Vpk32, &h->Kpk32, &h->Spk32, &h->Fpk32, &h->Lpk32, &h->Ppk32};
