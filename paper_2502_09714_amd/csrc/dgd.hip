@@ -66,12 +66,13 @@ struct DevBuf {
 }  // namespace
 
 struct dgd_handle {
+  explicit dgd_handle(const RefData& r) : ref(r) {}
   int N = 0, prec = 0, device = 0;
   int ncu = 256;          // compute units of the device
   hipStream_t stream = nullptr;
   double* noalloc_part = nullptr;   // this device's static partial-sum buffer
   std::string err;
-  RefData ref;
+  const RefData& ref;     // constants of the degree
   size_t tsize = 8;  // bytes of the working type
   // reference data on the device
   DevBuf Vpk, Kpk, Spk, Fpk, Lpk, Ppk, Vd, wqd, Pwd, betad;
@@ -1346,8 +1347,14 @@ dgd_status dgd_create(int N, int precision, void* hip_stream, dgd_handle** out) 
   if (!out) return DGD_EINVAL;
   *out = nullptr;
   if (N < 1 || N > 4 || precision < 0 || precision > 2) return DGD_EINVAL;
-  dgd_handle* h = new (std::nothrow) dgd_handle();
-  if (!h) return DGD_ENOMEM;
+  dgd_handle* h = nullptr;
+  try {
+    h = new dgd_handle(build_reference(N));
+  } catch (const std::bad_alloc&) {
+    return DGD_ENOMEM;
+  } catch (...) {
+    return DGD_EINVAL;
+  }
   h->N = N;
   h->prec = precision;
   h->stream = (hipStream_t)hip_stream;
@@ -1357,12 +1364,6 @@ dgd_status dgd_create(int N, int precision, void* hip_stream, dgd_handle** out) 
       scratch_address(h->device, &h->noalloc_part) != hipSuccess) {
     delete h;
     return DGD_EDEVICE;
-  }
-  try {
-    h->ref = build_reference(N);
-  } catch (...) {
-    delete h;
-    return DGD_EINVAL;
   }
   double ws = 0.0;
   for (double w : h->ref.wq) ws += w;

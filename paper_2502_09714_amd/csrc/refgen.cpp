@@ -3,6 +3,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <mutex>
 #include <stdexcept>
 #include <tuple>
 
@@ -21,38 +22,38 @@ int n_modes(int N) { return (N + 1) * (N + 2) * (N + 3) / 6; }
 
 // P_n^(a,b)(x) and its derivative by the three-term recurrence;
 // d/dx P_n^(a,b) = (n+a+b+1)/2 P_{n-1}^(a+1,b+1).
-static real jacobi(int n, real a, real b, real x) {
-  if (n == 0) return 1.0;
-  real p0 = 1.0, p1 = 0.5 * ((a - b) + (a + b + 2.0) * x);
+template <class R> static R jacobi(int n, R a, R b, R x) {
+  if (n == 0) return 1;
+  R p0 = 1, p1 = ((a - b) + (a + b + 2) * x) / 2;
   for (int k = 2; k <= n; ++k) {
-    real c = 2.0 * k + a + b;
-    real a1 = 2.0 * k * (k + a + b) * (c - 2.0);
-    real a2 = (c - 1.0) * (c * (c - 2.0) * x + a * a - b * b);
-    real a3 = 2.0 * (k + a - 1.0) * (k + b - 1.0) * c;
-    real p2 = (a2 * p1 - a3 * p0) / a1;
+    R c = 2 * k + a + b;
+    R a1 = 2 * k * (k + a + b) * (c - 2);
+    R a2 = (c - 1) * (c * (c - 2) * x + a * a - b * b);
+    R a3 = 2 * (k + a - 1) * (k + b - 1) * c;
+    R p2 = (a2 * p1 - a3 * p0) / a1;
     p0 = p1;
     p1 = p2;
   }
   return p1;
 }
 
-static real djacobi(int n, real a, real b, real x) {
-  if (n == 0) return 0.0;
-  return 0.5 * (n + a + b + 1.0) * jacobi(n - 1, a + 1.0, b + 1.0, x);
+template <class R> static R djacobi(int n, R a, R b, R x) {
+  if (n == 0) return 0;
+  return (n + a + b + 1) / 2 * jacobi<R>(n - 1, a + 1, b + 1, x);
 }
 
 static void gauss_jacobi(int n, real alpha, std::vector<real>& t, std::vector<real>& w) {
-  t.assign(n, 0.0);
-  w.assign(n, 0.0);
+  t.assign(n, 0);
+  w.assign(n, 0);
   for (int k = 0; k < n; ++k) {
     // Chebyshev-like start, refined by Newton with deflation of found roots
     real x = -std::cos((2.0 * k + 1.0) * M_PI / (2.0 * n));
-    if (k > 0 && x <= t[k - 1]) x = 0.5 * (t[k - 1] + 1.0);
+    if (k > 0 && x <= t[k - 1]) x = (t[k - 1] + 1) / 2;
     for (int it = 0; it < 200; ++it) {
-      real p = jacobi(n, alpha, 0.0, x);
-      real dp = djacobi(n, alpha, 0.0, x);
-      real defl = 0.0;
-      for (int j = 0; j < k; ++j) defl += 1.0 / (x - t[j]);
+      real p = jacobi<real>(n, alpha, 0, x);
+      real dp = djacobi<real>(n, alpha, 0, x);
+      real defl = 0;
+      for (int j = 0; j < k; ++j) defl += 1 / (x - t[j]);
       real dx = p / (dp - p * defl);
       x -= dx;
       if (std::fabs(dx) < 2e-19L) break;
@@ -61,8 +62,8 @@ static void gauss_jacobi(int n, real alpha, std::vector<real>& t, std::vector<re
   }
   std::sort(t.begin(), t.end());
   for (int k = 0; k < n; ++k) {
-    real dp = djacobi(n, alpha, 0.0, t[k]);
-    w[k] = std::pow(real(2), alpha + 1.0) / ((1.0 - t[k] * t[k]) * dp * dp);
+    real dp = djacobi<real>(n, alpha, 0, t[k]);
+    w[k] = std::pow(real(2), alpha + 1) / ((1 - t[k] * t[k]) * dp * dp);
   }
 }
 
@@ -80,60 +81,87 @@ static std::vector<Mode> modes(int N) {
   return m;
 }
 
-static real ipow(real x, int n) {
-  real r = 1.0;
+template <class R> static R ipow(R x, int n) {
+  R r = 1;
   for (int k = 0; k < n; ++k) r *= x;
   return r;
 }
 
-static void basis_real(int N, const real xi[3], real* phi, real* dphi) {
-  const real x = xi[0], y = xi[1], z = xi[2];
-  const real omyz = 1.0 - y - z, omz = 1.0 - z;
-  const real a = 2.0 * x / omyz - 1.0, b = 2.0 * y / omz - 1.0, c = 2.0 * z - 1.0;
-  const real hb = 0.5 * (1.0 - b), hc = 0.5 * (1.0 - c);
-  std::vector<Mode> ms = modes(N);
+// The orthonormal basis phi_ijk = nrm A_i(a) B_ij(b) C_(i+j)k(c) at collapsed
+// coordinates (a, b, c), hb = (1 - b)/2, hc = (1 - c)/2: its factors
+//   A_i = P_i^(0,0)(a), B_ij = hb^i P_j^(2i+1,0)(b), C_mk = hc^m P_k^(2m+2,0)(c)
+// and their derivatives with respect to a, b, c.
+template <class R> struct Factors {
+  R A[7], B[7][7], C[7][7], dA[7], dB[7][7], dC[7][7];
+  void eval_a(int N, R a, bool grad) {
+    for (int i = 0; i <= N; ++i) {
+      A[i] = jacobi<R>(i, 0, 0, a);
+      if (grad) dA[i] = djacobi<R>(i, 0, 0, a);
+    }
+  }
+  void eval_b(int N, R b, R hb, bool grad) { fill(N, 1, b, hb, grad, B, dB); }
+  void eval_c(int N, R c, R hc, bool grad) { fill(N, 2, c, hc, grad, C, dC); }
+
+ private:
+  static void fill(int N, int add, R x, R h, bool grad, R (*F)[7], R (*dF)[7]) {
+    for (int i = 0; i <= N; ++i)
+      for (int j = 0; i + j <= N; ++j) {
+        const R al = 2 * i + add, p = jacobi<R>(j, al, 0, x), hi = ipow(h, i);
+        F[i][j] = hi * p;
+        if (grad)
+          dF[i][j] = (i > 0 ? -R(i) / 2 * ipow(h, i - 1) * p : R(0)) + hi * djacobi<R>(j, al, 0, x);
+      }
+  }
+};
+
+template <class R>
+static void combine(const std::vector<Mode>& ms, const R* nrm, const Factors<R>& f, R a, R b, R hb,
+                    R hc, R* phi, R* dphi) {
   const int L = (int)ms.size();
   for (int l = 0; l < L; ++l) {
     const int i = ms[l].i, j = ms[l].j, k = ms[l].k;
-    const real nrm = std::sqrt((real)((2 * i + 1) * (2 * i + 2 * j + 2) * (2 * i + 2 * j + 2 * k + 3)));
-    const real fa = jacobi(i, 0.0, 0.0, a);
-    const real gb = jacobi(j, 2.0 * i + 1.0, 0.0, b);
-    const real hcv = jacobi(k, 2.0 * i + 2.0 * j + 2.0, 0.0, c);
-    const real Bv = ipow(hb, i) * gb;
-    const real Cv = ipow(hc, i + j) * hcv;
-    phi[l] = nrm * fa * Bv * Cv;
+    const R Av = f.A[i], Bv = f.B[i][j], Cv = f.C[i + j][k];
+    phi[l] = nrm[l] * Av * Bv * Cv;
     if (dphi) {
-      const real dfa = djacobi(i, 0.0, 0.0, a);
-      const real dgb = djacobi(j, 2.0 * i + 1.0, 0.0, b);
-      const real dhc = djacobi(k, 2.0 * i + 2.0 * j + 2.0, 0.0, c);
-      const real Bp = (i > 0 ? -0.5 * i * ipow(hb, i - 1) * gb : 0.0) + ipow(hb, i) * dgb;
-      const real Cp = (i + j > 0 ? -0.5 * (i + j) * ipow(hc, i + j - 1) * hcv : 0.0) +
-                        ipow(hc, i + j) * dhc;
-      const real pa = dfa * Bv * Cv, pb = fa * Bp * Cv, pc = fa * Bv * Cp;
-      // a(x,y,z), b(y,z), c(z): chain rule
-      const real dx = pa * 2.0 / omyz;
-      const real dy = pa * (1.0 + a) / omyz + pb * 2.0 / omz;
-      const real dz = pa * (1.0 + a) / omyz + pb * (1.0 + b) / omz + pc * 2.0;
-      dphi[0 * L + l] = nrm * dx;
-      dphi[1 * L + l] = nrm * dy;
-      dphi[2 * L + l] = nrm * dz;
+      // a(x,y,z), b(y,z), c(z): chain rule, 1 - y - z = hb hc, 1 - z = hc
+      const R pa = f.dA[i] * Bv * Cv, pb = Av * f.dB[i][j] * Cv, pc = Av * Bv * f.dC[i + j][k];
+      const R om = hb * hc;
+      dphi[0 * L + l] = nrm[l] * (pa * 2 / om);
+      dphi[1 * L + l] = nrm[l] * (pa * (1 + a) / om + pb * 2 / hc);
+      dphi[2 * L + l] = nrm[l] * (pa * (1 + a) / om + pb * (1 + b) / hc + pc * 2);
     }
   }
 }
 
+template <class R> static std::vector<R> norms(const std::vector<Mode>& ms) {
+  std::vector<R> n;
+  for (const Mode& m : ms)
+    n.push_back(std::sqrt((R)((2 * m.i + 1) * (2 * m.i + 2 * m.j + 2) * (2 * m.i + 2 * m.j + 2 * m.k + 3))));
+  return n;
+}
+
+// at a point of the reference tetrahedron
+template <class R>
+static void basis_at(int N, const std::vector<Mode>& ms, const R* nrm, const R xi[3], R* phi, R* dphi) {
+  const R x = xi[0], y = xi[1], z = xi[2];
+  const R omyz = 1 - y - z, omz = 1 - z;
+  const R a = 2 * x / omyz - 1, b = 2 * y / omz - 1, c = 2 * z - 1;
+  const R hb = (1 - b) / 2, hc = (1 - c) / 2;
+  Factors<R> f;
+  f.eval_a(N, a, dphi);
+  f.eval_b(N, b, hb, dphi);
+  f.eval_c(N, c, hc, dphi);
+  combine(ms, nrm, f, a, b, hb, hc, phi, dphi);
+}
+
 void basis_eval(int N, const double xi[3], double* phi, double* dphi) {
-  const int L = n_modes(N);
-  const real x[3] = {xi[0], xi[1], xi[2]};
-  std::vector<real> p(L), d(3 * (size_t)L);
-  basis_real(N, x, p.data(), dphi ? d.data() : nullptr);
-  std::copy(p.begin(), p.end(), phi);
-  if (dphi) std::copy(d.begin(), d.end(), dphi);
+  const std::vector<Mode> ms = modes(N);
+  basis_at<double>(N, ms, norms<double>(ms).data(), xi, phi, dphi);
 }
 
 static const int kRefVerts[4][3] = {{0, 0, 0}, {1, 0, 0}, {0, 1, 0}, {0, 0, 1}};
 
-RefData build_reference(int N) {
-  if (N < 1 || N > 6) throw std::invalid_argument("degree out of range");
+static RefData generate(int N) {
   RefData r;
   r.N = N;
   r.L = n_modes(N);
@@ -173,19 +201,42 @@ RefData build_reference(int N) {
   r.V.assign((size_t)Q * L, 0.0);
   r.Pw.assign((size_t)L * Q, 0.0);
   r.Sw.assign((size_t)3 * L * Q, 0.0);
+  const std::vector<Mode> ms = modes(N);
+  const std::vector<real> nrm = norms<real>(ms);
+  for (const Mode& m : ms) r.deg.push_back(m.i + m.j + m.k);
   std::vector<real> K((size_t)3 * L * L, 0), phi(L), dphi(3 * L);
+  std::vector<Factors<real>> at(n);        // the factors at the points of the one-dimensional rules
+  for (int k = 0; k < n; ++k) {
+    at[k].eval_a(N, ta[k], true);
+    at[k].eval_b(N, tb[k], (1 - tb[k]) / 2, true);
+    at[k].eval_c(N, tc[k], (1 - tc[k]) / 2, true);
+  }
   for (int q = 0; q < Q; ++q) {
-    basis_real(N, &xq[3 * q], phi.data(), dphi.data());
+    const int ia = q / (n * n), ib = q / n % n, ic = q % n;
+    Factors<real> f;
+    for (int i = 0; i <= N; ++i) {
+      f.A[i] = at[ia].A[i];
+      f.dA[i] = at[ia].dA[i];
+      for (int j = 0; i + j <= N; ++j) {
+        f.B[i][j] = at[ib].B[i][j];
+        f.dB[i][j] = at[ib].dB[i][j];
+        f.C[i][j] = at[ic].C[i][j];
+        f.dC[i][j] = at[ic].dC[i][j];
+      }
+    }
+    combine<real>(ms, nrm.data(), f, ta[ia], tb[ib], (1 - tb[ib]) / 2, (1 - tc[ic]) / 2, phi.data(), dphi.data());
     for (int l = 0; l < L; ++l) {
       r.V[(size_t)q * L + l] = (double)phi[l];
       r.Pw[(size_t)l * Q + q] = (double)(wq[q] * phi[l]);
       for (int e = 0; e < 3; ++e)
         r.Sw[((size_t)e * L + l) * Q + q] = (double)(wq[q] * dphi[e * L + l]);
     }
+    // (a derivative lowers the degree: the other entries are zero)
     for (int e = 0; e < 3; ++e)
-      for (int k = 0; k < L; ++k)
-        for (int l = 0; l < L; ++l)
-          K[((size_t)e * L + k) * L + l] += wq[q] * phi[k] * dphi[e * L + l];
+      for (int k = 0; k < L; ++k) {
+        const real wp = wq[q] * phi[k];
+        for (int l = n_modes(r.deg[k]); l < L; ++l) K[((size_t)e * L + k) * L + l] += wp * dphi[e * L + l];
+      }
   }
   r.K.assign(K.begin(), K.end());
   // orthonormal polynomials of degree <= N on the face with respect to beta, at its
@@ -230,10 +281,12 @@ RefData build_reference(int N) {
         real xi[3] = {0, 0, 0};
         for (int j = 0; j < 3; ++j)
           for (int d = 0; d < 3; ++d) xi[d] += loc[j] * kRefVerts[kFaceVerts[f][j]][d];
-        basis_real(N, xi, phi.data(), nullptr);
+        basis_at<real>(N, ms, nrm.data(), xi, phi.data(), nullptr);
         for (int l = 0; l < L; ++l) {
           r.F[(((size_t)f * 6 + s) * Ns + i) * L + l] = (double)phi[l];
-          for (int m = 0; m < M; ++m) R[(size_t)l * M + m] += lift[m * Ns + i] * phi[l];
+          // (psi_m is orthogonal to polynomials of lower degree)
+          const int top = N == 1 ? M : (r.deg[l] + 1) * (r.deg[l] + 2) / 2;
+          for (int m = 0; m < top; ++m) R[(size_t)l * M + m] += lift[m * Ns + i] * phi[l];
         }
       }
       std::copy(R.begin(), R.end(), r.R.begin() + ((size_t)f * 6 + s) * L * M);
@@ -262,9 +315,16 @@ RefData build_reference(int N) {
       r.Om[(size_t)z * n + j] = (double)acc;
     }
   }
-  std::vector<Mode> ms = modes(N);
-  for (auto& m : ms) r.deg.push_back(m.i + m.j + m.k);
   return r;
+}
+
+// (constants of the degree: generated by the first handle of a process)
+const RefData& build_reference(int N) {
+  if (N < 1 || N > 6) throw std::invalid_argument("degree out of range");
+  static std::once_flag once[7];
+  static RefData data[7];
+  std::call_once(once[N], [&] { data[N] = generate(N); });
+  return data[N];
 }
 
 }  // namespace dgd

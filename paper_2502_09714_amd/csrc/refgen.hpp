@@ -52,6 +52,6 @@ extern const int kFaceVerts[4][3];
 
 int n_modes(int N);
 void basis_eval(int N, const double xi[3], double* phi, double* dphi /* 3*L or null */);
-RefData build_reference(int N);
+const RefData& build_reference(int N);
 
 }  // namespace dgd
