@@ -125,11 +125,22 @@ struct dgd_handle {
   // sources and receivers
   int nsrc = 0, srckind = 0;
   std::vector<long long> src_elem, rec_elem;   // their elements
-  int npt = 0, npt_src = 0;                    // elements with either; the first npt_src have sources
-  DevBuf p_elem, p_range, p_order;             // (PointArgs)
-  DevBuf s_M6, s_dphi, s_onset, s_param, s_rhoJ;
+  // Each of the two setters uploads its table and the groups of both in one buffer;
+  // the groups in use are those of the later one.
+  struct Groups {                              // by element (PointArgs)
+    const void *elem = nullptr, *range = nullptr, *order = nullptr;
+    int n = 0, nsrc = 0;                       // elements with either; the first nsrc have sources
+  } grp;
+  struct Sources {
+    DevBuf tab;
+    const void *M6 = nullptr, *dphi = nullptr, *onset = nullptr, *param = nullptr, *rhoJ = nullptr;
+  } src;
   int nrec = 0;
-  DevBuf r_elem, r_phi, seis;
+  struct Receivers {
+    DevBuf tab;
+    const void *elem = nullptr, *phi = nullptr;
+  } rec;
+  DevBuf seis;
   long long nrec_steps = 0, seis_cap = 0;
   // profiling: event pairs per kernel class
   // discrete adjoint: transposed reference data, adjoint state, checkpoints
@@ -155,7 +166,7 @@ struct dgd_handle {
   ~dgd_handle() {
     DevBuf* all[] = {&Vpk, &Kpk, &Spk, &Fpk, &Lpk, &Ppk, &Vd, &wqd, &Pwd, &betad, &geo, &fgeo,
                      &conn, &mat, &faces, &fmap, &fflux, &U9[0], &U9[1], &Ua[0], &Ua[1], &Uz, &flag, &tmp,
-                     &p_elem, &p_range, &p_order, &s_M6, &s_dphi, &s_onset, &s_param, &s_rhoJ, &r_elem, &r_phi, &seis,
+                     &src.tab, &rec.tab, &seis,
                      &VTpk, &STpk, &PTpk, &KTpk, &lam[0], &lam[1], &gtr, &gmuf, &lzf, &gmu, &gcd, &adjW9,
                      &adjWa, &dlds, &seg9, &sega, &seguz, &segd, &segacc, &save9, &savea, &st9, &sta,
                      &ecl, &points_ecl, &facc, &step_tab, &adj_tab,
@@ -224,7 +235,7 @@ struct Part {
   template <class V>
   Part(const std::vector<V>& v, const void** a) : data(v.data()), bytes(v.size() * sizeof(V)), at(a) {}
 };
-dgd_status upload_parts(dgd_handle* h, DevBuf& b, std::initializer_list<Part> parts) {
+dgd_status upload_parts(dgd_handle* h, DevBuf& b, const std::vector<Part>& parts) {
   std::vector<char> all;
   std::vector<size_t> off;
   for (const Part& p : parts) {
@@ -731,26 +742,26 @@ void launch_ck(dgd_handle* h, const StepArgs<P>& a) {
 // buf, then the receivers (out != nullptr)
 template <class T>
 void launch_points(dgd_handle* h, int nsrc, double t0, double t1, int cluster, int buf, double* out) {
-  const int n = out ? h->npt : (nsrc > 0 ? h->npt_src : 0);
+  const int n = out ? h->grp.n : (nsrc > 0 ? h->grp.nsrc : 0);
   if (n == 0) return;
   PointArgs s;
   s.L = h->ref.L;
   s.nsrc = nsrc;
   s.nrec = out ? h->nrec : 0;
-  s.elem = (const long long*)h->p_elem.p;
-  s.range = (const int*)h->p_range.p;
-  s.order = (const int*)h->p_order.p;
-  s.M6 = (const double*)h->s_M6.p;
-  s.dphi = (const double*)h->s_dphi.p;
-  s.onset = (const double*)h->s_onset.p;
-  s.param = (const double*)h->s_param.p;
-  s.rhoJ = (const double*)h->s_rhoJ.p;
+  s.elem = (const long long*)h->grp.elem;
+  s.range = (const int*)h->grp.range;
+  s.order = (const int*)h->grp.order;
+  s.M6 = (const double*)h->src.M6;
+  s.dphi = (const double*)h->src.dphi;
+  s.onset = (const double*)h->src.onset;
+  s.param = (const double*)h->src.param;
+  s.rhoJ = (const double*)h->src.rhoJ;
   s.kind = h->srckind;
   s.t0 = t0;
   s.t1 = t1;
   s.ecl = cluster >= 0 ? (const signed char*)h->ecl.p : nullptr;
   s.only_cluster = cluster;
-  s.phi = (const double*)h->r_phi.p;
+  s.phi = (const double*)h->rec.phi;
   s.out = out;
   timed(h, nsrc > 0 ? 2 : 3, [&] {
     hipLaunchKernelGGL((k_points<T>), dim3(n), dim3(128), 0, h->stream, s, (T*)h->U9[buf].p);
@@ -1338,6 +1349,44 @@ void launch_to_f64(dgd_handle* h, double* dst) {
                      dst);
 }
 
+// Puts a table of sources or receivers (buffer `old`, host arrays `parts`) and the
+// groups of both by element, those with sources first, in place of what there is.  On
+// failure everything stays as it was.
+dgd_status set_points(dgd_handle* h, const std::vector<long long>& src_elem,
+                      const std::vector<long long>& rec_elem, DevBuf& old, std::vector<Part> parts) {
+  std::map<long long, std::vector<int>> src, rec;
+  for (size_t k = 0; k < src_elem.size(); ++k) src[src_elem[k]].push_back((int)k);
+  for (size_t r = 0; r < rec_elem.size(); ++r) rec[rec_elem[r]].push_back((int)r);
+  std::vector<long long> elem;
+  std::vector<int> range, order, rorder;
+  const int ns = (int)src_elem.size();
+  auto add = [&](long long e, const std::vector<int>& s, const std::vector<int>& r) {
+    elem.push_back(e);
+    range.push_back((int)order.size());
+    order.insert(order.end(), s.begin(), s.end());
+    range.push_back((int)order.size());
+    range.push_back(ns + (int)rorder.size());
+    rorder.insert(rorder.end(), r.begin(), r.end());
+    range.push_back(ns + (int)rorder.size());
+  };
+  for (const auto& s : src) add(s.first, s.second, rec[s.first]);
+  for (const auto& r : rec)
+    if (!src.count(r.first)) add(r.first, {}, r.second);
+  order.insert(order.end(), rorder.begin(), rorder.end());
+  parts.insert(parts.end(), {{elem, &h->grp.elem}, {range, &h->grp.range}, {order, &h->grp.order}});
+  DevBuf made;
+  const dgd_status s = upload_parts(h, made, parts);
+  if (s) {
+    made.release();
+    return s;
+  }
+  h->grp.n = (int)elem.size();
+  h->grp.nsrc = (int)src.size();
+  std::swap(old, made);
+  made.release();                // (the stream is idle after the upload)
+  return DGD_OK;
+}
+
 }  // namespace
 
 // ================================================================== C interface
@@ -1545,7 +1594,7 @@ dgd_status dgd_set_mesh(dgd_handle* h, int64_t nv, const double* xyz, int64_t ne
   h->nrec = 0;
   h->src_elem.clear();
   h->rec_elem.clear();
-  h->npt = h->npt_src = 0;
+  h->grp.n = h->grp.nsrc = 0;
   h->nrec_steps = 0;
   return DGD_OK;
 }
@@ -1889,37 +1938,6 @@ dgd_status dgd_step_lts(dgd_handle* h, int64_t nmacro) {
   return dgd_synchronize(h);
 }
 
-// groups of point sources and receivers by element, those with sources first
-static dgd_status group_points(dgd_handle* h) {
-  h->npt = h->npt_src = 0;
-  std::map<long long, std::vector<int>> src, rec;
-  for (size_t k = 0; k < h->src_elem.size(); ++k) src[h->src_elem[k]].push_back((int)k);
-  for (size_t r = 0; r < h->rec_elem.size(); ++r) rec[h->rec_elem[r]].push_back((int)r);
-  std::vector<long long> elem;
-  std::vector<int> range, order, rorder;
-  const int ns = (int)h->src_elem.size();
-  auto add = [&](long long e, const std::vector<int>& s, const std::vector<int>& r) {
-    elem.push_back(e);
-    range.push_back((int)order.size());
-    order.insert(order.end(), s.begin(), s.end());
-    range.push_back((int)order.size());
-    range.push_back(ns + (int)rorder.size());
-    rorder.insert(rorder.end(), r.begin(), r.end());
-    range.push_back(ns + (int)rorder.size());
-  };
-  for (const auto& s : src) add(s.first, s.second, rec[s.first]);
-  for (const auto& r : rec)
-    if (!src.count(r.first)) add(r.first, {}, r.second);
-  order.insert(order.end(), rorder.begin(), rorder.end());
-  dgd_status s;
-  if ((s = upload(h, h->p_elem, elem)) || (s = upload(h, h->p_range, range)) ||
-      (s = upload(h, h->p_order, order)))
-    return s;
-  h->npt = (int)elem.size();
-  h->npt_src = (int)src.size();
-  return DGD_OK;
-}
-
 dgd_status dgd_set_point_sources(dgd_handle* h, int n, const double* xyz, const double* M6,
                                  const double* t_onset, const double* stf_param, int stf_kind) {
   if (!h) return DGD_EINVAL;
@@ -1950,13 +1968,12 @@ dgd_status dgd_set_point_sources(dgd_handle* h, int n, const double* xyz, const 
       }
     rhoJ[k] = h->rho_h[e] * h->detJ[e];
   }
-  dgd_status s;
-  if ((s = upload(h, h->s_M6, m6)) ||
-      (s = upload(h, h->s_dphi, dphi)) || (s = upload(h, h->s_onset, on)) ||
-      (s = upload(h, h->s_param, par)) || (s = upload(h, h->s_rhoJ, rhoJ)))
-    return s;
+  const dgd_status s =
+      set_points(h, elem, h->rec_elem, h->src.tab,
+                 {{m6, &h->src.M6}, {dphi, &h->src.dphi}, {on, &h->src.onset}, {par, &h->src.param},
+                  {rhoJ, &h->src.rhoJ}});
+  if (s) return s;
   h->src_elem = std::move(elem);
-  if ((s = group_points(h))) return s;
   h->nsrc = n;
   h->srckind = stf_kind;
   return DGD_OK;
@@ -1977,10 +1994,10 @@ dgd_status dgd_set_receivers(dgd_handle* h, int nrec, const double* xyz) {
     elem[r] = e;
     basis_eval(h->N, xi, &phi[(size_t)r * L], nullptr);
   }
-  dgd_status s;
-  if ((s = upload(h, h->r_elem, elem)) || (s = upload(h, h->r_phi, phi))) return s;
+  const dgd_status s = set_points(h, h->src_elem, elem, h->rec.tab,
+                                  {{elem, &h->rec.elem}, {phi, &h->rec.phi}});
+  if (s) return s;
   h->rec_elem = std::move(elem);
-  if ((s = group_points(h))) return s;
   h->nrec = nrec;
   h->nrec_steps = 0;
   h->seis.release();
@@ -2218,11 +2235,11 @@ dgd_status dgd_adjoint_step(dgd_handle* h, const double* state_n, double* lam,
   if (dJ_dseis_n && h->nrec > 0) {
     if (h->prec == DGD_FP64)
       hipLaunchKernelGGL((k_adj_receivers<double>), dim3(1), dim3(3 * L), 0, h->stream, h->nrec,
-                         (int)L, adj_kpl(h), (const long long*)h->r_elem.p, (const double*)h->r_phi.p,
+                         (int)L, adj_kpl(h), (const long long*)h->rec.elem, (const double*)h->rec.phi,
                          dJ_dseis_n, (double*)h->lam[0].p);
     else
       hipLaunchKernelGGL((k_adj_receivers<float>), dim3(1), dim3(3 * L), 0, h->stream, h->nrec,
-                         (int)L, adj_kpl(h), (const long long*)h->r_elem.p, (const double*)h->r_phi.p,
+                         (int)L, adj_kpl(h), (const long long*)h->rec.elem, (const double*)h->rec.phi,
                          dJ_dseis_n, (float*)h->lam[0].p);
   }
   HIPCHK(h, hipGetLastError());
@@ -2406,12 +2423,12 @@ dgd_status dgd_backward(dgd_handle* h, const double* dl_dseis, double* grad_mu0,
         timed(h, 7, [&] {
           if (h->prec == DGD_FP64)
             hipLaunchKernelGGL((k_adj_receivers<double>), dim3(1), dim3(3 * L), 0, h->stream, nrec,
-                               (int)L, adj_kpl(h), (const long long*)h->r_elem.p,
-                               (const double*)h->r_phi.p, g, (double*)h->lam[lc].p);
+                               (int)L, adj_kpl(h), (const long long*)h->rec.elem,
+                               (const double*)h->rec.phi, g, (double*)h->lam[lc].p);
           else
             hipLaunchKernelGGL((k_adj_receivers<float>), dim3(1), dim3(3 * L), 0, h->stream, nrec,
-                               (int)L, adj_kpl(h), (const long long*)h->r_elem.p,
-                               (const double*)h->r_phi.p, g, (float*)h->lam[lc].p);
+                               (int)L, adj_kpl(h), (const long long*)h->rec.elem,
+                               (const double*)h->rec.phi, g, (float*)h->lam[lc].p);
         });
       }
       const char* u9 = (const char*)h->seg9.p + (size_t)(j - j0) * E * 9 * L * h->tsize;
