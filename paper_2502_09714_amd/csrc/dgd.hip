@@ -81,7 +81,7 @@ struct dgd_handle {
   const void *Vw = nullptr, *Vt = nullptr, *Kw = nullptr, *Kt = nullptr, *Ktw = nullptr, *PXw = nullptr,
              *PXa = nullptr, *PXleft = nullptr, *Rw = nullptr, *Fst = nullptr, *Fstt = nullptr,
              *Psi = nullptr, *Psrc = nullptr, *mixP = nullptr, *mixV = nullptr;
-  DevBuf adj_tab;         // transposed, for k_adj_points: packed by the first adjoint call
+  DevBuf adj_tab;         // transposed, for k_adj_points (degree 4)
   const void *PVw = nullptr, *PVt = nullptr, *VTa = nullptr, *STw = nullptr, *STt = nullptr;
   size_t dz_elem = 0;     // bytes of one element's time derivatives
   // what the last step left: its time-point states in Uz, or derivatives (derivs()) and
@@ -944,8 +944,11 @@ dgd_status dispatch(dgd_handle* h, Args... args) {
 
 template <int N, int P> struct BuildFn {
   static dgd_status run(dgd_handle* h) {
-    const dgd_status s = build_packed<N, P>(h);
-    return s ? s : build_step_packs<N, StepPrec<P>::value>(h);
+    dgd_status s = build_packed<N, P>(h);
+    if (s == DGD_OK) s = build_step_packs<N, StepPrec<P>::value>(h);
+    if constexpr (AdjSplit<N>::value)
+      if (s == DGD_OK) s = build_adjoint_tables<N, StepPrec<P>::value>(h);
+    return s;
   }
 };
 template <int N, int P> struct StepFn {
@@ -988,17 +991,7 @@ size_t lam_elems(const dgd_handle* h) { return (size_t)h->ne * adj_kpl(h) * 16; 
 // FP32 forward operators of a split-BF16 handle (its own packs hold BF16
 // hi/lo pairs), packed once beside them; the transposed adjoint operators
 // come with them.
-template <int N, int P> struct AdjTablesFn {
-  static dgd_status run(dgd_handle* h) {
-    if constexpr (AdjSplit<N>::value) return build_adjoint_tables<N, StepPrec<P>::value>(h);
-    return DGD_OK;
-  }
-};
 dgd_status ensure_adjoint_packs(dgd_handle* h) {
-  if (!h->adj_tab.p) {
-    const dgd_status s = dispatch<AdjTablesFn>(h);
-    if (s) return s;
-  }
   if (h->prec != DGD_BF16 || h->Vpk32.p) return DGD_OK;
   DevBuf* fw[] = {&h->Vpk, &h->Kpk, &h->Spk, &h->Fpk, &h->Lpk, &h->Ppk};
   DevBuf* f32[] = {&h->Vpk32, &h->Kpk32, &h->Spk32, &h->Fpk32, &h->Lpk32, &h->Ppk32};
