@@ -304,7 +304,8 @@ dgd_status build_packed(dgd_handle* h) {
                     return (q < Q && kk < L) ? r.V[(size_t)q * L + kk] : 0.0;
                   },
                   4, KSL));
-  k = pack_A<P>(
+  // (the prediction on these operators is the adjoint's, which is not BF16)
+  if constexpr (P != PREC_BF16) k = pack_A<P>(
       [&](int m, int kk) {
         int e = kk / KPL, l = kk % KPL;
         return (m < L && l < L) ? r.K[((size_t)e * L + m) * L + l] : 0.0;
@@ -957,13 +958,17 @@ template <int N, int P> struct StepFn {
 
 // the adjoint's prediction of the current state (time-point states and, when
 // the handle asks for them, the kept derivatives); state and time unchanged
+// (not on BF16 handles, whose adjoint steps predict for themselves)
 template <int N, int P> struct PredictFn {
   static dgd_status run(dgd_handle* h) {
-    const long long per = (h->ne + 7) / 8;
-    StepArgs<P> a = make_args<N, P>(h);
-    hipLaunchKernelGGL((k_predict<N, P>), dim3((unsigned)(8 * per)), dim3(64), 0, h->stream, a);
-    HIPCHK(h, hipGetLastError());
-    return DGD_OK;
+    if constexpr (P == PREC_BF16) return fail(h, DGD_EINVAL, "no kept prediction in BF16 form");
+    else {
+      const long long per = (h->ne + 7) / 8;
+      StepArgs<P> a = make_args<N, P>(h);
+      hipLaunchKernelGGL((k_predict<N, P>), dim3((unsigned)(8 * per)), dim3(64), 0, h->stream, a);
+      HIPCHK(h, hipGetLastError());
+      return DGD_OK;
+    }
   }
 };
 
@@ -981,10 +986,8 @@ template <int N, int P> struct TimePointsFn {
 };
 
 // ---------------------------------------------------------------- discrete adjoint
-// The adjoint arithmetic is FP64 on FP64 handles and FP32 on the others (a
-// split-BF16 handle runs its forward steps in that form and their adjoint in
-// FP32, at the states of its own trajectory): mode rows of the adjoint
-// states padded to the FP32/FP64 matrix-core k-step.
+// The adjoint arithmetic is FP64 on FP64 handles and FP32 on the others: mode rows
+// of the adjoint states padded to the FP32/FP64 matrix-core k-step.
 int adj_kpl(const dgd_handle* h) { return round_up(h->ref.L, 4); }
 size_t lam_elems(const dgd_handle* h) { return (size_t)h->ne * adj_kpl(h) * 16; }
 
@@ -1086,9 +1089,8 @@ dgd_status adjoint_step_impl(dgd_handle* h, const void* U9, const double* Ua, co
     const dim3 grid((unsigned)(8 * per)), block(64);
     StepArgs<P> a = make_args<N, P>(h);
     if (h->prec == DGD_BF16) {
-      // the FP32 operators packed beside the handle's BF16 ones; the
-      // time-point states are recomputed in FP32 (uz, dk, ak are null)
-      if (uz || dk || ak) return fail(h, DGD_EINVAL, "kept BF16 predictions in an FP32 adjoint");
+      // the FP32 operators packed beside the handle's BF16 ones (uz, dk, ak are null)
+      if (uz || dk || ak) return fail(h, DGD_EINVAL, "kept predictions on a BF16 handle");
       a.Vpk = (const AF*)h->Vpk32.p;
       a.Kpk = (const AF*)h->Kpk32.p;
       a.Spk = (const AF*)h->Spk32.p;
@@ -2347,9 +2349,9 @@ dgd_status dgd_backward(dgd_handle* h, const double* dl_dseis, double* grad_mu0,
       (s = dalloc(h, h->sega, (size_t)every * E * L * sizeof(double))))
     return s;
   // time-point states of every step of a segment, kept from the replay so
-  // that the adjoint need not recompute them (skipped if memory is short,
-  // and under a split-BF16 forward, whose predictions are not the FP32
-  // adjoint's)
+  // that the adjoint need not recompute them (skipped if memory is short, and
+  // on BF16 handles, whose adjoint steps predict from the FP32 operators packed
+  // beside their own)
   const size_t uzb = uz_bytes(h);
   bool keep_uz = h->prec != DGD_BF16 && alloc_uz(h, h->seguz, (size_t)every) == DGD_OK;
   if (!keep_uz) {

@@ -83,7 +83,7 @@ template <int P> struct StepArgs {
   // local time stepping: the elements a launch covers (null: all E), the
   // cluster of every element, the cluster being corrected (-1: global step)
   // and the flux integrals accumulated for the coarser side of cluster
-  // boundaries [face][Ns][10]
+  // boundaries, in face modes [face][NM2][10]
   const int* elist;
   long long nlist;
   const signed char* ecl;
@@ -115,17 +115,6 @@ template <int P> struct StepArgs {
   T hzi[5][4];          // tau_z dt / (i + 1)
   T wint[8];            // sum_z gamma_z hz^i / i!
 };
-
-// element of this workgroup (-1: none), through the element list if any
-template <int P>
-__device__ inline long long elem_index(const StepArgs<P>& a) {
-  const long long n = a.elist ? a.nlist : a.E;
-  const long long per = (n + 7) / 8;
-  const long long b = blockIdx.x;
-  const long long i = (b % 8) * per + b / 8;
-  if (i >= n) return -1;
-  return a.elist ? (long long)a.elist[i] : i;
-}
 
 __device__ inline long long elem_of_block(long long E) {
   const long long per = (E + 7) / 8;
@@ -230,7 +219,7 @@ __device__ inline void build_Astar(PredLDS<N, P, ND, AW>& S, const MatP<typename
 // (REGS false, ND = N + 1; dreg unused and may be null), or in
 // dreg[i * DPL + j] = D^i[lane + 64 j] (REGS true, ND = 1).  With AW, S.A is
 // not kept past the recursion.
-template <int N, int P, int ND, bool REGS, int AW = 0, class LW = CdmLaw>
+template <int N, int P, int ND, bool REGS, int AW = 0>
 __device__ inline void predictor_stage(const StepArgs<P>& a, long long e, PredLDS<N, P, ND, AW>& S,
                                        const MatP<typename Prec<P>::T>& m, int lane,
                                        typename Prec<P>::T* dreg) {
@@ -281,8 +270,8 @@ __device__ inline void predictor_stage(const StepArgs<P>& a, long long e, PredLD
       T u[10];
 #pragma unroll
       for (int k = 0; k < 10; ++k) u[k] = sX[lane * R + k];
-      LW::tangent(u, m, law, ds);
-      r = -LW::rate(u, m, law);   // negated: it joins the CK contraction stored with -1
+      cdm_tangent(u, m, law, ds);
+      r = -cdm_rate(u, m, law);   // negated: it joins the CK contraction stored with -1
       const T wq = (T)a.wq[q];
 #pragma unroll
       for (int k = 0; k < 6; ++k)
@@ -446,7 +435,7 @@ template <int N, int P> struct VolWaves {
 // written to HBM in the [l][16] fragment layout (padding rows and columns
 // zero); the derivatives and the cell-averaged tangent also go to Dkeep /
 // Akeep when the adjoint's replay asks for them.
-template <int N, int P, class LW = CdmLaw>
+template <int N, int P>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(PredWaves<N, P>::value)))
 void k_predict(StepArgs<P> a) {
   using PR = Prec<P>;
@@ -463,10 +452,10 @@ void k_predict(StepArgs<P> a) {
   T dreg[(N + 1) * DPL];
 
   const int lane = threadIdx.x;
-  const long long e = elem_index(a);
-  if (e < 0) return;
+  const long long e = elem_of_block(a.E);
+  if (e >= a.E) return;
   const MatP<T> m = load_mat<T>(a.mat + e * 8);
-  predictor_stage<N, P, ND, REGS, 2, LW>(a, e, S, m, lane, dreg);
+  predictor_stage<N, P, ND, REGS, 2>(a, e, S, m, lane, dreg);
   // D^i[idx] for idx = lane + 64 j
   auto Dv = [&](int i, int j) -> T {
     if constexpr (REGS)
@@ -538,8 +527,8 @@ void k_volume(StepArgs<P> a) {
   T* const sR = S.R_;
 
   const int lane = threadIdx.x;
-  const long long e = elem_index(a);
-  if (e < 0) return;
+  const long long e = elem_of_block(a.E);
+  if (e >= a.E) return;
   const Law<T> law{a.amax, a.smin};
   const MatP<T> m = load_mat<T>(a.mat + e * 8);
   T Ji[9];
@@ -799,8 +788,8 @@ __global__ __launch_bounds__(64) void k_lift_update(StepArgs<P> a, const int* fm
   constexpr int WPL = (9 * L + 63) / 64;     // partial-update values per lane
 
   const int lane = threadIdx.x;
-  const long long e = elem_index(a);
-  if (e < 0) return;
+  const long long e = elem_of_block(a.E);
+  if (e >= a.E) return;
   // every HBM load is issued before the first use: the four faces' fluxes
   // (gathered by face) and the partial update
   T fv[4][FPL], sc[4];

@@ -250,8 +250,10 @@ __device__ inline void wave_gemm(const typename Prec<P>::AF* __restrict__ Apk,
     }
     return;
   }
-  // A fragments of step s + PD requested before the products of step s (see
-  // below)
+  // A fragments come from L2/HBM: those of step s + PD are requested before the
+  // products of step s are issued (the scheduling barrier keeps the compiler from
+  // sinking the loads down to their use), so that PD steps of products cover
+  // their latency
   constexpr int PD = DGD_PF_STEPS, NB = PD + 1;
   AF a[NB][MT];
 #pragma unroll
@@ -281,7 +283,7 @@ __device__ inline void wave_gemm_shared_a(const typename Prec<P>::AF* __restrict
   using PR = Prec<P>;
   using AF = typename PR::AF;
   // A and B fragments (A from L2/HBM, B from HBM or LDS) PD steps ahead (see
-  // below); the NZ x MT products of a step cover their latency
+  // wave_gemm); the NZ x MT products of a step cover their latency
   constexpr int PD = DGD_PF_SHARED, NB = PD + 1;
   AF a[NB][MT], b[NB][NZ];
 #pragma unroll
@@ -339,7 +341,7 @@ __device__ inline void wave_gemm_col9(const typename Prec<P>::AF* __restrict__ A
   using PR = Prec<P>;
   using AF = typename PR::AF;
   // A fragments of step s + PD requested before the products of step s (see
-  // below)
+  // wave_gemm)
   constexpr int PD = DGD_PF_STEPS, NB = PD + 1;
   AF a[NB][MT];
 #pragma unroll

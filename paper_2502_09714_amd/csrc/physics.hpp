@@ -219,14 +219,6 @@ struct CdmLaw {
     return cdm_stress_rate(u, m, law, sig);
   }
   template <class T>
-  __device__ static T rate(const T* u, const MatP<T>& m, const Law<T>& law) {
-    return cdm_rate(u, m, law);
-  }
-  template <class T>
-  __device__ static void tangent(const T* u, const MatP<T>& m, const Law<T>& law, T ds[6][7]) {
-    cdm_tangent(u, m, law, ds);
-  }
-  template <class T>
   __device__ static T speed(const T* u, const T n[3], const MatP<T>& m, const Law<T>& law) {
     return llf_speed(u, n, m, law);
   }
@@ -246,7 +238,7 @@ struct CdmLaw {
 // cd = 1 / (gamma_b tau_b) (xi0 unused).
 struct IvmLaw {
   template <class T> struct Pt {
-    T I1, I2, g, ac, dac;
+    T I1, I2, g, ac;
   };
   template <class T>
   __device__ static Pt<T> parts(const T* u, const Law<T>& law) {
@@ -256,7 +248,6 @@ struct IvmLaw {
            T(2) * (u[3] * u[3] + u[4] * u[4] + u[5] * u[5]);
     const T a = u[9];
     p.ac = a < T(0) ? T(0) : (a > law.amax ? law.amax : a);
-    p.dac = (a >= T(0) && a <= law.amax) ? T(1) : T(0);
     p.g = T(1) - p.ac;
     return p;
   }
@@ -280,22 +271,6 @@ struct IvmLaw {
     const Pt<T> p = parts(u, law);
     stress_p(p, u, m, sig);
     return rate_p(p, m);
-  }
-  template <class T>
-  __device__ static T rate(const T* u, const MatP<T>& m, const Law<T>& law) {
-    return rate_p(parts(u, law), m);
-  }
-  // d sigma_k / d u_q (q < 6 strain entries, q = 6 alpha)
-  template <class T>
-  __device__ static void tangent(const T* u, const MatP<T>& m, const Law<T>& law, T ds[6][7]) {
-    const Pt<T> p = parts(u, law);
-#pragma unroll
-    for (int k = 0; k < 6; ++k) {
-#pragma unroll
-      for (int q = 0; q < 6; ++q)
-        ds[k][q] = p.g * ((k == q ? T(2) * m.mu : T(0)) + (k < 3 && q < 3 ? m.lam : T(0)));
-      ds[k][6] = -p.dac * (T(2) * m.mu * u[k] + (k < 3 ? m.lam * p.I1 : T(0)));
-    }
   }
   // the acoustic tensor is that of the damaged isotropic moduli
   template <class T>

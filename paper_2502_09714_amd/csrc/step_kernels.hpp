@@ -526,7 +526,6 @@ __device__ inline void ck_element(const StepArgs<P>& a, long long e, CkLDS<N, P>
   wave_sync();
   if (lane < 48) {
     const T v = lane < 42 ? LW::tangent_entry(S.ext, m, lane / 7, lane % 7) : T(0);
-    if (a.Akeep) a.Akeep[e * 48 + lane] = v;
     S.tg[lane] = lane < 42 ? v * m.ir : (lane == 43 ? T(0.5) : (lane == 44 ? T(1) : T(0)));
   }
   // damage source at t_n projected on the modes, one mode per lane
