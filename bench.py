@@ -6,9 +6,10 @@ boundaries, update, point sources, receivers) over the synthetic workload.
 Default workload: the largest configuration, c5 -- 96^3 cubes x 6 =
 5,308,416 tetrahedra, degree 4 (35 modes, 350 DOFs per element), 24 km box,
 3 km gradient basin over rock, free top, absorbing sides, 64 subfault point
-sources, 16 receivers.  The FP32 form is the headline value; the BF16-MFMA
-(split operands, FP32 accumulation) and FP64 forms run the same steps and
-are reported beside it with their device-memory footprint.
+sources, 16 receivers.  The FP32 form is the headline value; the FP64 form and a
+BF16 handle run the same steps and are reported beside it with their
+device-memory footprint.  (A BF16 handle's Cauchy-Kovalevskaya step is the FP32
+one, so its rate and errors repeat FP32's; only its Picard corrector differs.)
 
 Precision errors: the precision-form configuration c3 (64^3 cubes x 6 =
 1,572,864 tets, N = 4, lognormal moduli) is run in FP64, FP32 and BF16 from
@@ -35,6 +36,8 @@ if ROOT not in sys.path:
 METRIC = "DG DOF-updates/s on 1 GPU, FP32/BF16 vs FP64 at stated L2 error; adjoint/forward cost"
 PEAK_TFLOPS = {"fp64": 78.6, "fp32": 157.3, "bf16": 2500.0}
 HBM_TBS = 8.0
+# FLOP of one matrix instruction: 16x16x32 BF16; 16x16x4 FP32 and FP64
+MFMA_FLOP = {"bf16": 16 * 16 * 32 * 2, "fp32": 16 * 16 * 4 * 2, "fp64": 16 * 16 * 4 * 2}
 KERNELS = ("predict", "face_flux", "sources", "receivers",
            "adj_predict_recompute", "adj_face", "adj_volume", "adj_receivers", "lift_update",
            "volume")
@@ -74,6 +77,88 @@ def flops_per_launch(w):
     ff = ni * (2 * trace + Ns * Nt * 470 + Ns * Nt * 10 * 2) + nb * (trace + Ns * Nt * 300 + Ns * Nt * 10 * 2)
     lift = ne * (4 * 2 * L * Ns * 10 + 4 * Ns * 10 + 10 * L)
     return {"predict": kp * ne, "volume": kv * ne, "face_flux": ff, "lift_update": lift}
+
+
+def matrix_products(N, prec):
+    """Matrix instructions that the Cauchy-Kovalevskaya step's kernels issue, per
+    element (predict, volume) or interior face (face_flux):
+    {kernel: {unit: count}}, unit the type of the operands.  In FP32 (and on
+    BF16 handles, which run the same kernels) contractions with the reference
+    matrices are six BF16 products of split operands from degree 3 on (face
+    traces from degree 4 on); what is left over of a 32-mode step, the mixing of
+    the quantities and the face-mode projection are products of the working
+    type.  The tiles and zero blocks are those of csrc/step_kernels.hpp; at
+    degree 4 the hardware counter gives the same sums (233, 317 and 83)."""
+    L, Q, Ns, _ = dims(N)
+    upto = [dims(d)[0] if d >= 0 else 0 for d in range(-1, N + 2)]      # upto[d + 1]: modes of degree <= d
+    up = lambda d: upto[d + 1]                                          # noqa: E731
+    degree = lambda l: next(d for d in range(N + 1) if l < up(d))       # noqa: E731
+    nch, mt, nst, nt1 = -(-Q // 64), -(-L // 16), -(-Ns // 16), -(-up(N - 1) // 16)
+    native = "fp64" if prec == "fp64" else "fp32"
+    split = native == "fp32" and N >= 3
+    # columns of the derivative matrix by falling mode count, in tiles of 16
+    modes = [L] * 11 + [up(N - 1)] * 9 + [up(N + 1 - i) for i in range(2, N + 1) for _ in range(9)]
+    tiles = modes[::16]
+    nm2 = 4 if N == 1 else (N + 1) * (N + 2) // 2
+    mtp = L // 16 if L > 16 and L % 16 <= 4 else mt
+    out = {k: {"bf16": 0, native: 0} for k in ("predict", "volume", "face_flux")}
+
+    def steps(rows, x3):
+        tail = x3 and 0 < rows % 32 <= 4
+        return (rows // 32 if tail else -(-rows // (32 if x3 else 4))), int(tail)
+
+    def add(kernel, wide, rest, x3):
+        out[kernel]["bf16" if x3 else native] += wide * (6 if x3 else 1)
+        out[kernel][native] += rest
+
+    def evaluate(kernel, n, x3):
+        """The derivative matrix at n 16-point tiles."""
+        wl, _ = steps(L, x3)
+        for rows in tiles:
+            if x3:
+                add(kernel, n * wl if rows > 4 else 0, n if rows % 32 <= 4 else 0, True)
+            else:
+                add(kernel, n * -(-rows // 4), 0, False)
+
+    def stiffness(kernel, rows, nto):
+        """K^e of `rows` modes to nto tiles, without the zero blocks."""
+        wl, tail = steps(rows, split)
+        ks = 32 if split else 4
+        n = sum(3 for s in range(wl) for t in range(nto) if ks * (s + 1) > up(degree(16 * t)))
+        add(kernel, n, 3 * nto * tail, split)
+
+    # prediction: nodal values, then orders 1..N, contraction and mixing
+    wl, tail = steps(L, split)
+    add("predict", nch * 4 * wl, nch * 4 * tail, split)
+    stiffness("predict", L, nt1)
+    out["predict"][native] += 9 * nt1
+    if N >= 2:
+        out["predict"][native] += sum(3 * (1 if 16 * t >= up(N - 1) else 3) for t in range(mt))
+        stiffness("predict", L, nt1)
+    if N >= 3:
+        stiffness("predict", up(N - 1), 1)
+        out["predict"][native] += 9
+    if N >= 4:
+        out["predict"][native] += 9 * -(-up(N - 2) // 16)
+        stiffness("predict", up(N - 2), 1)
+    # corrector: lift, evaluation, projection, stiffness, mixing
+    add("volume", 2 * mt if split else 4 * mt * -(-nm2 // 4), 0, split)
+    evaluate("volume", 4 * nch, split)
+    if N == 1:
+        add("volume", 4 + 12, 0, False)
+    else:
+        add("volume", nch * (2 if split else 16) * mtp, 0, split)
+        wl, _ = steps(up(N - 1), split)
+        ks = 32 if split else 4
+        add("volume", sum(3 for s in range(wl) for t in range(mt)
+                          if ks * s < up(degree(min(16 * t + 15, L - 1)) - 1)), 0, split)
+    out["volume"][native] += 9 * mt
+    # faces: both sides' traces, projection on the face modes
+    fsplit = native == "fp32" and N >= 4
+    for _ in range(2):
+        evaluate("face_flux", nst, fsplit)
+    out["face_flux"][native] += -(-Ns // 4)
+    return out
 
 
 def bytes_per_launch(w, prec):
@@ -534,7 +619,7 @@ def main():
     # adjoint reads them instead of repeating the prediction
     ap.add_argument("--adjoint-runs", default="c4:400:20,c3:200:10,c3:200:20:bf16",
                     help="checkpointed adjoint runs workload:steps:every[:bf16] (FP32 "
-                         "adjoint arithmetic; bf16: split-BF16 forward) ('' for none)")
+                         "adjoint arithmetic; bf16: a BF16 handle, whose step is the FP32 one) ('' for none)")
     ap.add_argument("--adjoint-fd", type=int, default=0,
                     help="central differences on this many elements for the last adjoint run")
     ap.add_argument("--ivm-precisions", default="fp32",
@@ -590,16 +675,33 @@ def main():
     nbytes = per_launch(bytes_per_launch(w, main_prec), kl)
     flop_launch = flops[dom]
     achieved = flop_launch / (avg_ms * 1e-3) / 1e12
+    # matrix work that the kernels issue (a boundary face issues what an interior
+    # one does) over the peak of the unit that runs it, and algorithmic bytes over
+    # the HBM peak: the largest share names the bound
+    products = matrix_products(w.N, main_prec)
+    items = {"predict": ne, "volume": ne, "face_flux": sum(face_counts(w))}
+
+    def shares(k):
+        t = km[k] / max(kl[k], 1) * 1e-3
+        out = {f"{u} matrix": (n * items[k] * MFMA_FLOP[u] / t / 1e12, PEAK_TFLOPS[u], "TFLOP/s")
+               for u, n in products[k].items() if n}
+        out["hbm"] = (nbytes[k] / t / 1e12, HBM_TBS, "TB/s")
+        return out
+
     traffic = load_traffic(dom, args.workload, main_prec)
-    roof = {"bound": "mfma", "achieved": achieved, "peak": PEAK_TFLOPS[main_prec],
-            "unit": "TFLOP/s", "frac": achieved / PEAK_TFLOPS[main_prec], "traffic": traffic,
-            "kernel": dom, "avg_launch_ms": avg_ms, "flop_per_launch": flop_launch,
+    sh = shares(dom)
+    unit = max(sh, key=lambda u: sh[u][0] / sh[u][1])
+    roof = {"bound": "hbm" if unit == "hbm" else "mfma", "of": unit, "achieved": sh[unit][0],
+            "peak": sh[unit][1], "unit": sh[unit][2], "frac": sh[unit][0] / sh[unit][1],
+            "traffic": traffic, "kernel": dom, "avg_launch_ms": avg_ms,
+            "dense_flop_per_launch": flop_launch, "dense_equivalent_tflops": achieved,
             "algorithmic_bytes_per_launch": nbytes[dom]}
     other = {}
     for k in flops:
         t = km[k] / max(kl[k], 1)
-        other[k] = {"avg_launch_ms": t, "tflops": flops[k] / (t * 1e-3) / 1e12,
-                    "hbm_tbs_algorithmic": nbytes[k] / (t * 1e-3) / 1e12}
+        other[k] = {"avg_launch_ms": t, "dense_equivalent_tflops": flops[k] / (t * 1e-3) / 1e12,
+                    "hbm_tbs_algorithmic": nbytes[k] / (t * 1e-3) / 1e12,
+                    "frac_of": {u: a / p for u, (a, p, _) in shares(k).items()}}
 
     line = {
         "metric": METRIC, "value": rate(main_prec), "unit": "DOF-updates/s", "n_gpus": 1,
@@ -665,7 +767,7 @@ def main():
         wa = make_workload(name)
         a, grads = run_adjoint(wa, aprec, int(steps), int(every), observed=True)
         if aprec == "bf16":
-            a["arithmetic"] = "split-BF16 forward, FP32 adjoint"
+            a["arithmetic"] = "BF16 handle: FP32 step and adjoint, each adjoint step predicting for itself"
         if args.adjoint_fd and i == len(runs) - 1:
             a["fd_check"] = fd_check(wa, int(steps), grads, args.adjoint_fd)
         print(f"adjoint {name} {aprec}: {a}", file=sys.stderr, flush=True)
