@@ -207,9 +207,9 @@ dgd_status dgd_get_time(const dgd_handle* h, double* t);
  * (iterations = 0 means N + 1).  The corrector is unchanged.  The discrete
  * adjoint is that of the Cauchy-Kovalevskaya predictor: its calls return
  * EINVAL under this one.  EINVAL for another kind or iterations < 0; ENOMEM
- * (with the predictor unchanged) if the time-point states that
- * DGD_PREDICT_PICARD keeps cannot be allocated: they take the place of the
- * smaller derivatives kept for DGD_PREDICT_CK, here or in dgd_set_mesh.
+ * (with the predictor unchanged) for DGD_PREDICT_PICARD if dgd_set_mesh found no
+ * memory for the time-point states, only for the smaller derivatives that
+ * DGD_PREDICT_CK keeps.
  * Drops a checkpointed run. */
 typedef enum { DGD_PREDICT_CK = 0, DGD_PREDICT_PICARD = 1 } dgd_predictor;
 dgd_status dgd_set_predictor(dgd_handle* h, int kind, int iterations);
@@ -352,8 +352,7 @@ dgd_status dgd_get_kernel_times(dgd_handle* h, double* ms /* 10 */, int64_t* lau
  * the first step.  An adjoint step that predicts for itself (dgd_adjoint_step,
  * dgd_adjoint_step_host; dgd_backward on DGD_BF16 handles or when short of
  * memory) leaves the states of the step that it differentiates in their place.
- * Synchronises; ESTATE before a state is set, or where a later first call of
- * the Picard predictor or the adjoint found no memory to keep them. */
+ * Synchronises; ESTATE before a state is set. */
 dgd_status dgd_get_time_point_states(dgd_handle* h, double* out);
 
 /* ---------------------------------------------------------------------------
@@ -370,10 +369,9 @@ dgd_status dgd_get_time_point_states(dgd_handle* h, double* out);
  * tie of the two sides' Lax-Friedrichs speeds (Eq. rusanov-flux) each side
  * takes half of the derivative.  Point sources do not depend on the state or
  * on mu0, C_d.  The adjoint arithmetic is FP64 on DGD_FP64 handles and FP32
- * on the others: a DGD_BF16 handle runs its forward (and replayed) steps in
- * its own form and differentiates them with the FP32 adjoint of the
- * step, taken at the states of that trajectory (its FP32 operators are
- * packed on the first adjoint call).  CDM law only.
+ * on the others: a DGD_BF16 handle, whose step is the FP32 one, takes the
+ * FP32 adjoint of the step (its FP32 operators are packed on the first adjoint
+ * call; each adjoint step predicts for itself).  CDM law only.
  *
  * dgd_adjoint_step: one reverse step on the device, asynchronous on the
  * solver's stream.  state_n: U^n, device [ne][10][L] FP64 (borrowed).

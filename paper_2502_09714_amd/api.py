@@ -223,9 +223,11 @@ class Simulation:
         self._chk(self._L.dgd_set_profiling(self.h, int(bool(on))))
 
     def get_kernel_times(self):
-        """(ms[10], launches[10]) for the predictor, face fluxes, sources,
-        receivers, the adjoint's predictor recomputation, faces, volume,
-        receivers, the lift + update, and the volume integrals."""
+        """(ms[10], launches[10]) for the predictor, face fluxes, sources
+        (with the receivers, one launch), receivers where there are no
+        sources, the adjoint's predictor recomputation, faces, volume,
+        receivers, the lift + update (Picard step only), and the volume
+        integrals (with the lift and the update in the other steps)."""
         ms = np.zeros(NUM_KERNEL_CLASSES)
         n = np.zeros(NUM_KERNEL_CLASSES, dtype=np.int64)
         self._chk(self._L.dgd_get_kernel_times(self.h, _dp(ms), n.ctypes.data_as(c_i64p)))

@@ -89,7 +89,6 @@ struct dgd_handle {
   struct Points {
     bool in_uz = false, clustered = false;
     double dt = 0.0;
-    bool lost = false;    // given up to make room for Uz
   } points;
   DevBuf points_ecl;      // its clusters, where dgd_set_clusters has replaced them since
   int predictor = 0;      // 0: linearised Cauchy-Kovalevskaya, 1: Picard iteration
@@ -118,7 +117,7 @@ struct dgd_handle {
   int law = 0;   // 0: continuum damage (Eq. cdb-model), 1: internal variable (Eq. ivm-model)
   // state
   DevBuf U9[2], Ua[2], flag, tmp;   // tmp: per-call host transfers
-  DevBuf Dz, Uz;          // derivatives; or, once time-point states are needed, both (need_uz)
+  DevBuf Uz, Dz;          // time-point states and derivatives in Uz; or Dz (derivs)
   int cur = 0;
   double dt = 0.0, amax = 0.5, t = 0.0;
   long long steps_since_check = 0, check_every = 64;
@@ -657,13 +656,15 @@ size_t uz_bytes(const dgd_handle* h) {
 size_t uz_tail(const dgd_handle* h) { return (size_t)h->kpl * 16 * h->tsize; }
 
 // Derivatives of a Cauchy-Kovalevskaya step and time-point states (Picard predictor,
-// adjoint) are never live together: where Uz exists the derivatives use its memory,
-// from its start if they fit (degree 2 and up), else after it.
+// adjoint) are never live together: the derivatives use the memory of Uz, from its
+// start if they fit (degree 2 and up), else after it.  Only a mesh too large for Uz
+// has them in a (smaller) buffer of their own, and no time-point states.
+size_t dz_bytes(const dgd_handle* h) { return (size_t)h->ne * h->dz_elem; }
 size_t dz_offset(const dgd_handle* h) {
-  return (size_t)h->ne * h->dz_elem <= uz_bytes(h) ? 0 : uz_bytes(h) + uz_tail(h);
+  return dz_bytes(h) <= uz_bytes(h) ? 0 : uz_bytes(h) + uz_tail(h);
 }
 void* derivs(const dgd_handle* h) {
-  return h->Uz.p ? (char*)h->Uz.p + dz_offset(h) : h->Dz.p;
+  return h->Dz.p ? h->Dz.p : (char*)h->Uz.p + dz_offset(h);
 }
 
 template <int N, int P>
@@ -1031,35 +1032,16 @@ dgd_status alloc_uz(dgd_handle* h, DevBuf& b, size_t slots) {
   return DGD_OK;
 }
 
-// Uz, with the last step's derivatives moved into it.  Where there is no memory for both
-// at a time the derivatives are given up (only dgd_get_time_point_states misses them).
+size_t uz_alloc(const dgd_handle* h) {
+  return uz_bytes(h) + uz_tail(h) + (dz_offset(h) ? dz_bytes(h) : 0);
+}
+
+// time-point states (dgd_set_mesh allocates them unless memory is short)
 dgd_status need_uz(dgd_handle* h) {
   if (h->Uz.p) return DGD_OK;
-  const size_t dz = (size_t)h->ne * h->dz_elem, at = dz_offset(h);
-  const size_t bytes = uz_bytes(h) + uz_tail(h) + (at ? dz : 0);
-  DevBuf u;
-  dgd_status s = dalloc(h, u, bytes);
-  if (s == DGD_ENOMEM && h->Dz.p) {
-    (void)hipGetLastError();
-    HIPCHK(h, hipStreamSynchronize(h->stream));
-    h->Dz.release();
-    h->points = {};
-    h->points.lost = true;
-    if ((s = dalloc(h, u, bytes))) {
-      (void)hipGetLastError();
-      const std::string err = h->err;
-      if (dalloc(h, h->Dz, dz)) h->have_mesh = h->have_state = false;
-      h->err = err;
-    }
-  }
+  const dgd_status s = dalloc(h, h->Uz, uz_alloc(h));
   if (s) return s;
-  std::swap(h->Uz, u);
-  HIPCHK(h, hipMemsetAsync(h->Uz.p, 0, bytes, h->stream));
-  if (h->Dz.p) {
-    HIPCHK(h, hipMemcpyAsync((char*)h->Uz.p + at, h->Dz.p, dz, hipMemcpyDeviceToDevice, h->stream));
-    HIPCHK(h, hipStreamSynchronize(h->stream));
-    h->Dz.release();
-  }
+  HIPCHK(h, hipMemsetAsync(h->Uz.p, 0, h->Uz.n, h->stream));
   return DGD_OK;
 }
 
@@ -1324,18 +1306,30 @@ dgd_status alloc_state(dgd_handle* h) {
   }
   h->points = {};
   h->points_ecl.release();
-  h->Uz.release();
-  if (h->predictor == 1) {
-    h->Dz.release();
-    if ((s = need_uz(h))) return s;
-  } else {
-    if ((s = dalloc(h, h->Dz, E * h->dz_elem))) return s;
-    HIPCHK(h, hipMemsetAsync(h->Dz.p, 0, h->Dz.n, h->stream));
-  }
   if ((s = dalloc(h, h->fflux, (size_t)h->nfaces * h->ref.Ns * 10 * h->tsize))) return s;
   if ((s = dalloc(h, h->flag, sizeof(int)))) return s;
   HIPCHK(h, hipMemsetAsync(h->flag.p, 0, sizeof(int), h->stream));
-  return DGD_OK;
+  h->Dz.release();
+  if (h->Uz.n == uz_alloc(h)) {
+    HIPCHK(h, hipMemsetAsync(h->Uz.p, 0, h->Uz.n, h->stream));
+    return DGD_OK;
+  }
+  h->Uz.release();
+  s = need_uz(h);
+  // (short as well: no room for the material and a state in FP64 beside it)
+  size_t left = 0, total = 0;
+  const bool look = h->predictor == 0 && uz_bytes(h) > ((size_t)1 << 32);
+  if (s == DGD_OK && look && hipMemGetInfo(&left, &total) == hipSuccess &&
+      left < E * (10 * L * sizeof(double) + 128) + ((size_t)64 << 20))
+    s = DGD_ENOMEM;
+  if (s == DGD_ENOMEM && h->predictor == 0) {
+    (void)hipGetLastError();
+    h->err.clear();
+    h->Uz.release();
+    if ((s = dalloc(h, h->Dz, dz_bytes(h)))) return s;
+    HIPCHK(h, hipMemsetAsync(h->Dz.p, 0, h->Dz.n, h->stream));
+  }
+  return s;
 }
 
 template <class T>
@@ -2169,7 +2163,6 @@ dgd_status dgd_get_kernel_times(dgd_handle* h, double* ms, int64_t* launches) {
 dgd_status dgd_get_time_point_states(dgd_handle* h, double* out) {
   if (!h || !out) return DGD_EINVAL;
   if (!h->have_state) return fail(h, DGD_ESTATE, "no state");
-  if (h->points.lost) return fail(h, DGD_ESTATE, "the last step's derivatives were given up for memory");
   if (!h->points.in_uz) {
     // through a scratch buffer of at most 64 MiB, less where memory is short
     const size_t per = (size_t)h->ref.Nt * 10 * h->ref.L;
@@ -2388,7 +2381,7 @@ dgd_status dgd_backward(dgd_handle* h, const double* dl_dseis, double* grad_mu0,
   const double t_save = h->t;
   const bool prof = h->profiling;
   const auto points = h->points;
-  if (h->gtr.n < E * h->dz_elem) return fail(h, DGD_ESTATE, "no room for the replay's derivatives");
+  if (h->gtr.n < dz_bytes(h)) return fail(h, DGD_ESTATE, "no room for the replay's derivatives");
   int lc = 0;
   h->nrec = 0;   // the replay records nothing
   const long long nck = (long long)h->ck9.size();

@@ -897,9 +897,9 @@ struct PointArgs {
 
 // Sources of an element, in the order they were given, then its receivers: one
 // workgroup per element.  (Two launches with all sources in one workgroup, one
-// after the other, took 65 + 16 us for 64 sources and 64 receivers, of a step of
-// 5.9 ms at 311040 elements of degree 4, and 6 + 7 us of one of 56 us at 3780 elements
-// of degree 3.)
+// after the other, took 63 + 14 us for 64 sources and 16 receivers, of a step of
+// 5.2 ms at 312132 elements of degree 4, where this takes 9, and 6 + 7 us for one source
+// and 16 receivers, of one of 54 us at 3780 elements of degree 3, where this takes 6.)
 template <class T>
 __global__ __launch_bounds__(128) void k_points(PointArgs s, T* U9) {
   const long long e = s.elem[blockIdx.x];

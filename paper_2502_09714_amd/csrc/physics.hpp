@@ -196,7 +196,8 @@ __device__ inline AcPlane<T> acoustic_plane(const Parts<T>& p, const T* u, const
 // c = sqrt(lambda_max / rho), lambda_max = h + max(0, larger eigenvalue of the
 // 2 x 2 matrix): one square root in place of the 3 x 3 trigonometric form
 // (acos and cos), and no loss where the two smaller eigenvalues coincide.  The
-// face kernel is bound by vector issue next to its matrix products: 304 -> 267 us
+// face kernel on time-point states is bound by vector issue next to its matrix
+// products: 304 -> 267 us
 // per launch on 82,944 tets at degree 3 in FP32, 1192 -> 1010 us on 48,000 tets
 // at degree 4 in FP64.
 template <class T>

@@ -100,7 +100,8 @@ template <int N> struct Deriv {
 // the 32 KB L1 and the wavefronts waited on its pending lines for 60 % of the
 // time).  Below degree 3 they fit the L1 and a wavefront takes one element.
 // pd_*: how many fragments ahead of their use they are requested.
-// Update at degree 4: 12 wavefronts 1970 us at 311040 elements, 8 wavefronts 2175;
+// (Times here and below: HIP events around warm launches.)
+// Update at degree 4: 12 wavefronts 1950 us at 312132 elements, 8 wavefronts 2175;
 // at degree 3 16 wavefronts 299 us at 82944 elements, 12 332, 8 379.  FP64 updates
 // spill 112 registers when staged or at two wavefronts per SIMD (1465 us for 48000
 // elements of degree 4, 990 as it is).
@@ -440,8 +441,8 @@ template <int N, int P> struct CkLDS {
 };
 
 // Prediction (Appendix A.1, Eqs. CKIter, CKIter-ref-matrix, CKIter-ref-source;
-// 311040 elements of degree 4: 1340 us, issue of vector ALUs and FP32 products for
-// 62 % of it; time-point states from dense FP32 products 4645):
+// 312132 elements of degree 4: 1340 us, issue of vector ALUs and FP32 products for
+// 62 % of it; time-point states from dense FP32 products 4640):
 // nodal values at t_n, pointwise tangent and its cell average, damage source,
 // recursion D^i = sum_e K^e D^{i-1} (-A*_e)^T; D^0..D^N to HBM.
 //
@@ -775,8 +776,8 @@ template <int N> struct ProjTiles {
 };
 
 // Corrector (Appendix A.2, Eqs. 2nd term, 3rd term, rhs term, time-integrated;
-// 311040 elements of degree 4: 1970 us, bound by dependency latency at three
-// wavefronts per SIMD; volume and lift kernels on time-point states 5949):
+// 312132 elements of degree 4: 1950 us, bound by dependency latency at three
+// wavefronts per SIMD; volume and lift kernels on time-point states 5940):
 // lift of the four face fluxes, volume and source terms, update.
 //
 // The derivative matrix is evaluated at 64 points at a time (columns in rows of
@@ -1375,8 +1376,8 @@ template <int N, int P> struct FaceLDS {
   alignas(16) T tr[2][Dims<N>::Ns * JS];   // derivative traces of both sides, [point][column]
 };
 
-// Face fluxes (Appendix A.2 Eq. 2nd term, A.3; 311040 elements of degree 4: 1750 us,
-// vector issue for 77 % of it; on time-point states 3467), interior faces once: traces of
+// Face fluxes (Appendix A.2 Eq. 2nd term, A.3; 312132 elements of degree 4: 1760 us,
+// vector issue for 77 % of it; on time-point states 3430, with the LLF speed by acos and cos), interior faces once: traces of
 // both sides' derivative matrices at the shared face points, Taylor sums per
 // (time point, face point), local Lax-Friedrichs or boundary flux, time
 // quadrature; sum_z gamma_z F* projected on the face modes, [face][NM2][10].

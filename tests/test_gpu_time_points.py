@@ -132,15 +132,25 @@ def test_first_picard_and_adjoint_call_keep_them(N, prec):
 
 
 def test_memory_of_the_time_point_states():
-    """Degree 4 FP32: 7000 bytes of time-point states an element in the place of 4352 of derivatives."""
+    """Derivatives and time-point states share one buffer, allocated with the mesh: neither the Picard
+    predictor nor the adjoint asks for either again (degree 4 FP32: 7000 and 4352 bytes an element)."""
     import torch
     w = make_workload("c2", n=14, N=4)
+
+    def free():
+        torch.cuda.synchronize()
+        return torch.cuda.mem_get_info()[0]
+
     sim = _sim(w, "fp32")
     sim.step(1)
-    torch.cuda.synchronize()
-    free = torch.cuda.mem_get_info()[0]
+    f0 = free()
     sim.set_predictor("picard")
-    torch.cuda.synchronize()
-    grown = free - torch.cuda.mem_get_info()[0]
-    assert grown <= w.ne * (7000 - 4352) + (8 << 20)        # allocations are rounded to 2 MiB
+    assert f0 - free() == 0
+    sim.set_predictor("ck")
+    lam = np.zeros((w.ne, 10, sim.L))
+    sim.adjoint_step_host(lam)
+    faces = 2 * w.ne + 6 * 14 * 14                  # interior ones and half of the boundary's twelve triangles a square
+    adjoint = 4 * (2 * 36 * 16 + 5 * 36 * 16 + 9 * 35) * w.ne + 8 * (2 + 35) * w.ne + \
+        4 * (2 * 5 * 25 * 10) * faces + 16 * faces
+    assert f0 - free() <= adjoint + (24 << 20)      # ten buffers, rounded to 2 MiB
     sim.close()
